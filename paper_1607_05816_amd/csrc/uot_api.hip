@@ -162,6 +162,11 @@ struct Plan {
   bool tf_axis[3] = {false, false, false};   // tile-factored pass used on this axis
   bool tf16_axis[3] = {false, false, false}; // ... with FP16 operands
   CostArgs cost{0, 0, 0.0};                  // squared Euclidean or WF with a cut locus
+  bool line = false;                         // grids: line passes (uot_grid_line.hip)
+  bool pair = false;                         // ... paired over the half-steps of a solve
+  int np_pair_y = 0;                         // ... blocks of the paired Y epilogue
+  double c_max[3] = {0, 0, 0};               // ... their c = h^2 log2(e) / eps at the schedule's smallest eps
+  int parts_room = 1;                        // residual partials the workspace holds
   int band[3] = {0, 0, 0};                   // grid axes: taps |i - j| < band can be non-zero
   int split1d = 1;                           // 1-D grids: tap slices of the (direct) pass
   mutable void* split_pm = nullptr;          // ... their partial LSEs (set by carve)
@@ -333,6 +338,15 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
       if (g.cost == UOT_COST_WF) P.band[k] = (int)std::min<double>((double)g.n[k], std::ceil(g.cut / g.h[k]));
     }
     if (g.dim == 1) P.split1d = grid_contig_splits((int)g.n[0], nb, P.band[0]);
+    // the line passes take every axis or none (squared Euclidean cost, the
+    // default choice or grid_kernel 2): what they leave to the older passes
+    // is kernels of a few cells (c above their limit), the WF cost, the
+    // direct and FP16 forms asked for by name, and 1-D grids
+    P.line = (grid_kernel == 0 || grid_kernel == 2) && g.cost == UOT_COST_SQEUCLID && g.dim >= 2 && eps_min > 0;
+    for (int k = 0; k < g.dim; ++k) {
+      P.c_max[k] = eps_min > 0 ? g.h[k] * g.h[k] * kLog2e / eps_min : INFINITY;
+      P.line = P.line && line_applies(dtype == UOT_F64, P.c_max[k]);
+    }
   } else {
     return fail(UOT_E_INVALID, "unknown geometry kind");
   }
@@ -389,8 +403,18 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
   const int parts_room = P.geom == UOT_GEOM_GRID
                              ? std::max(grid_final_parts_for(P, false), P.n[0] % 16 == 0 ? grid_final_parts_for(P, true) : 0)
                              : P.nparts_x;
-  P.o_parts = take(sizeof(ResPart) * std::max(parts_room, 1));
+  P.parts_room = std::max(parts_room, 1);
+  P.o_parts = take(sizeof(ResPart) * P.parts_room);
   P.nparts_y = P.geom == UOT_GEOM_GRID ? P.nparts_x : (int)((P.M + 255) / 256);
+  if (P.line) {
+    P.nparts_x = P.nparts_y = (int)line_blocks((int)P.n[0], P.nb, P.N / P.n[0], P.parts_room);
+    P.line = P.nparts_x <= P.parts_room;
+    if (!P.line) P.nparts_x = P.nparts_y = grid_final_parts(P);
+    // solves pair the half-steps: X epilogue on lines of axis 0, Y epilogue on
+    // lines of the last axis (2-D) or on planes (3-D)
+    P.np_pair_y = P.dim == 2 ? (int)line_blocks((int)P.n[1], P.nb, P.n[0], P.parts_room) : (int)(P.nb * P.n[0]);
+    P.pair = P.line && (P.dim == 2 || line_plane_fits(P.n[1], P.n[2])) && P.np_pair_y <= P.parts_room;
+  }
   P.o_mass = take(2 * e * std::max(std::max(parts_room, P.nparts_y), 1));
   for (int k = 0; k < 3; ++k) P.o_gtab[k] = take(P.geom == UOT_GEOM_GRID && k < P.dim ? e * (2 * P.n[k] - 1) * nst : 0);
   int64_t gmax = 1;
@@ -425,6 +449,7 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
   return UOT_OK;
 }
 
+static_assert(sizeof(Ctrl) <= 512, "the workspace sizes (the no-allocation entry point's limit) count 512 bytes for it");
 template <typename T> T* at(char* ws, size_t off) { return reinterpret_cast<T*>(ws + off); }
 
 int check_ws(const Plan& P, void* ws, size_t bytes) {
@@ -434,7 +459,8 @@ int check_ws(const Plan& P, void* ws, size_t bytes) {
   return UOT_OK;
 }
 
-Ctrl make_ctrl(double eps, double eps0, int stages, int ips, double tol, int64_t max_iter) {
+Ctrl make_ctrl(double eps, double eps0, int stages, int ips, double tol, int64_t max_iter, const uot_div& F1,
+               const uot_div& F2) {
   Ctrl c{};
   const bool anneal = eps0 > eps && stages > 0 && ips > 0;
   c.n_stages = anneal ? stages : 0;
@@ -444,8 +470,13 @@ Ctrl make_ctrl(double eps, double eps0, int stages, int ips, double tol, int64_t
     for (int k = 0; k < stages; ++k) c.eps_tab[k] = eps0 * std::pow(f, k);
   }
   c.eps_tab[c.n_stages] = eps;
-  c.stage[0] = c.stage[1] = 0;
-  c.eps[0] = c.eps[1] = c.eps_tab[0];
+  c.kind[0] = (int8_t)F1.kind;
+  c.kind[1] = (int8_t)F2.kind;
+  c.lam[0] = F1.lambda;
+  c.lam[1] = F2.lambda;
+  const CtrlSlot s0 = slot_values(&c, stage_at(&c, 0), stage_at(&c, 1), -1);
+  set_slot(&c, 0, s0);
+  set_slot(&c, 1, s0);
   c.tol = tol;
   c.max_iter = max_iter;
   c.iter = 0;
@@ -515,6 +546,17 @@ template <typename T> Bufs<T> carve(const Plan& P, char* ws) {
   return b;
 }
 
+// one line pass along `axis`
+template <typename T>
+void line_axis(const Plan& P, int axis, const T* w, int side, Ctrl* c, const EpiArgs<T>& ep, hipStream_t s) {
+  int64_t A = P.nb, B = 1;
+  for (int k = 0; k < axis; ++k) A *= P.n[k];
+  for (int k = axis + 1; k < P.dim; ++k) B *= P.n[k];
+  timed(axis == P.dim - 1 ? 0 : 1, [&] {
+    launch_line<T>(w, A, (int)P.n[axis], B, P.h[axis], P.c_max[axis], P.parts_room, side, c, ep, s);
+  });
+}
+
 // separable grid product on nb fields: input w (log2 units), per-axis tables
 // (direct passes) or the tile-factored MFMA pass where the plan selects it
 template <typename T>
@@ -557,12 +599,23 @@ struct CtlHost {
   const ResPart* parts = nullptr;
   int nparts = 0;
   double* hist = nullptr;
+  int nfields = 0;
 };
 
 template <typename T>
 void grid_chain(const Plan& P, const T* w, T* const* tabs, int side, Ctrl* c, const EpiArgs<T>& ep, T* tmp1,
                 T* tmp2, hipStream_t s, const CtlHost* host = nullptr) {
   const int64_t nb = P.nb;
+  if (P.line) {
+    EpiArgs<T> raw{};
+    raw.mode = EPI_RAW;
+    T* const tmp[2] = {tmp1, tmp2};
+    for (int k = P.dim - 1; k >= 0; --k) {
+      raw.out = tmp[k & 1];
+      line_axis<T>(P, k, k == P.dim - 1 ? w : tmp[(k + 1) & 1], side, c, k == 0 ? ep : raw, s);
+    }
+    return;
+  }
   // first pass (no epilogue on 2 or 3 axes): writes tmp1 and may host the
   // control step; only such a pass may, as an epilogue reads the slot the
   // control step writes
@@ -588,6 +641,56 @@ void grid_chain(const Plan& P, const T* w, T* const* tabs, int side, Ctrl* c, co
     strided_pass<T>(P, 1, tmp1, nb * P.n[0], P.n[2], tabs, side, c, mid, s);
     strided_pass<T>(P, 0, tmp2, nb, P.n[1] * P.n[2], tabs, side, c, ep, s);
   }
+}
+
+// Grid solves on paired line passes.  The X half-step's product takes the axes
+// last to first, the Y half-step's first to last, so the half-steps meet on the
+// same axis and their passes share a launch:
+//   pair_start: the passes of the first X product up to axis 0 (w -> t1)
+//   pair_x:     axis 0 of the X product, the X epilogue, axis 0 of the Y
+//               product (t1 -> t2)
+//   pair_y:     the other axes of the Y product, the Y epilogue (which may host
+//               the control step), the other axes of the next X product
+//               (t2 -> t1)
+// t1 and every array of the X epilogue (potential, log p, log dx) are stored
+// with axis 0 fastest, t2 and those of the Y epilogue row-major.
+template <typename T>
+void pair_rest(const Plan& P, const T* in, T* out, int side, Ctrl* c, const EpiArgs<T>* ep, hipStream_t s) {
+  timed(0, [&] {
+    if (P.dim == 2)
+      launch_line_pair<T>(in, P.nb, P.n[0], (int)P.n[1], P.h[1], P.c_max[1], P.parts_room, side, c, ep, out, s);
+    else
+      launch_plane_pair<T>(in, P.nb, (int)P.n[0], (int)P.n[1], (int)P.n[2], P.h[1], P.h[2], P.c_max[1], P.c_max[2],
+                           side, c, ep, out, s);
+  });
+}
+template <typename T> void pair_start(const Plan& P, Bufs<T>& B, hipStream_t s) {
+  pair_rest<T>(P, B.wv, B.t1, 0, B.ctrl, nullptr, s);
+}
+template <typename T> void pair_x(const Plan& P, Bufs<T>& B, int par, const EpiArgs<T>& ep, hipStream_t s) {
+  timed(1, [&] {
+    launch_line_pair<T>(B.t1, P.nb, P.N / P.n[0], (int)P.n[0], P.h[0], P.c_max[0], P.parts_room, 0 | par << 1, B.ctrl,
+                        &ep, B.t2, s);
+  });
+}
+template <typename T> EpiArgs<T> with_host(EpiArgs<T> ep, const CtlHost& host) {
+  ep.host_ctl = host.c;
+  ep.host_parts = host.parts;
+  ep.host_nparts = host.nparts;
+  ep.host_hist = host.hist;
+  ep.host_fields = host.nfields;
+  return ep;
+}
+// the X side's inputs with axis 0 fastest, and u = 0 there (ut); `F` densities
+template <typename T>
+void pair_inputs(const Plan& P, Bufs<T>& B, const void* p, const void* dx, T* ut, hipStream_t s) {
+  const int64_t n0 = P.n[0], R = P.N / P.n[0];
+  launch_transpose<T>(static_cast<const T*>(p), B.logp, P.nb, n0, R, 1, s);
+  launch_transpose<T>(static_cast<const T*>(dx), B.logdx, 1, n0, R, 2, s);
+  launch_init_pot<T>(nullptr, B.logdx, ut, nullptr, P.nb * P.N, P.N, B.ctrl, 0, s);
+}
+template <typename T> void pair_output(const Plan& P, const T* ut, T* u, hipStream_t s) {
+  launch_transpose<T>(ut, u, P.nb, P.N / P.n[0], P.n[0], 0, s);
 }
 
 // WF point clouds: the work lists of both sides (the (row wave, column
@@ -991,6 +1094,7 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
   if (!u || !v) return fail(UOT_E_INVALID, "u and v output buffers are required");
   hipStream_t s = ctx->work;
   if ((rc = begin(ctx))) return rc;
+  if (P.pair) P.nparts_y = P.np_pair_y;
   Bufs<T> B = carve<T>(P, ws);
   // the iteration runs on pbs into uo / vo: the caller's problem and outputs,
   // or Morton-ordered copies whose potentials are scattered back at the end
@@ -1012,15 +1116,21 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
     return fail(UOT_E_UNSUPPORTED, "the mixed-precision grid passes switch under host control: solve synchronously");
   if (async && pr->kernel_ms) return fail(UOT_E_INVALID, "timed solves run synchronously");
   const double tol1 = mixed ? kMixedSwitchTol : pr->tol;
-  Ctrl init = make_ctrl(pr->eps, pr->eps0, pr->eps_stages, pr->iters_per_stage, tol1, pr->max_iter);
+  Ctrl init = make_ctrl(pr->eps, pr->eps0, pr->eps_stages, pr->iters_per_stage, tol1, pr->max_iter, pb->F1,
+                        pb->F2);
   launch_ctrl_init(B.ctrl, init, s);
-  log_into<T>(pb->p, B.logp, nb * P.N, 1, px, B.t1, s);
+  if (P.pair) {
+    uo = B.t3;   // u with axis 0 fastest
+    pair_inputs<T>(P, B, pb->p, pb->dx, uo, s);
+  } else {
+    log_into<T>(pb->p, B.logp, nb * P.N, 1, px, B.t1, s);
+    log_into<T>(pb->dx, B.logdx, P.N, 0, px, B.t1, s);
+  }
   log_into<T>(pb->q, B.logq, nb * P.M, 1, py, B.t1, s);
-  log_into<T>(pb->dx, B.logdx, P.N, 0, px, B.t1, s);
   log_into<T>(pb->dy, B.logdy, P.M, 0, py, B.t1, s);
-  if (P.geom == UOT_GEOM_GRID)
+  if (P.geom == UOT_GEOM_GRID && !P.line)
     for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, P.nst, P.cost, s);
-  launch_init_pot<T>(nullptr, B.logdx, uo, nullptr, nb * P.N, P.N, B.ctrl, 0, s);
+  if (!P.pair) launch_init_pot<T>(nullptr, B.logdx, uo, nullptr, nb * P.N, P.N, B.ctrl, 0, s);
   const T* v0 = static_cast<const T*>(pr->v0);
   if (v0 && py) {
     launch_gather<T>(v0, py, P.M, 1, vo, s);
@@ -1041,15 +1151,31 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
   // a single problem on a grid of 2 or 3 axes: the first Y pass (no
   // epilogue) hosts the control step; otherwise it is its own launch
   CtlHost host;
-  const bool hosted = nfields == 0 && P.geom == UOT_GEOM_GRID && P.dim >= 2;
+  // (paired passes host it for batches of fields too)
+  const bool hosted = P.pair || (nfields == 0 && P.geom == UOT_GEOM_GRID && P.dim >= 2 && !P.line);
   if (hosted) {
+    host.nfields = nfields;
     host.c = B.ctrl;
     host.parts = B.parts;
     host.nparts = P.nparts_x;
     host.hist = pr->res_hist;
   }
+  if (P.pair) pair_start<T>(P, B, s);
   auto iteration_with = [&](const Plan& PP) {
     return [&, pp = &PP](int par) {
+      if (pp->pair) {
+        pair_x<T>(*pp, B, par, prox_epi<T>(uo, nullptr, B.logp, B.logdx, nullptr, B.parts, P.N, pbs.F1), s);
+        EpiArgs<T> ep = prox_epi<T>(vo, nullptr, B.logq, B.logdy, nullptr, nullptr, P.M, pbs.F2);
+        if (mass) {
+          ep.mass_m = B.mass_m;
+          ep.mass_s = B.mass_s;
+        }
+        const EpiArgs<T> eph = with_host<T>(ep, host);
+        pair_rest<T>(*pp, B.t2, B.t1, 1 | par << 1, B.ctrl, &eph, s);
+        if (mass)
+          timed(2, [&] { launch_mass_update<T>(B.ctrl, B.mass_m, B.mass_s, pp->nparts_y, mass->F3, mass->log_m0, par, s); });
+        return;
+      }
       half_step<T>(*pp, pbs, 0 | par << 1, B, uo, nullptr, true, s);
       if (!hosted) timed(2, [&] { launch_control(B.ctrl, B.parts, pp->nparts_x, pr->res_hist, s, nfields, par); });
       half_step<T>(*pp, pbs, 1 | par << 1, B, vo, nullptr, false, s, hosted ? &host : nullptr, mass != nullptr);
@@ -1071,6 +1197,10 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
     launch_scatter<T>(vo, py, P.M, v, s);
     HIP_TRY(hipGetLastError());
   }
+  if (P.pair) {
+    pair_output<T>(P, uo, u, s);
+    HIP_TRY(hipGetLastError());
+  }
   if (async) return finish(ctx);   // the result waits for uot_sync_result
   if (log_z) *log_z = ctx->pinned->zeta;
   if ((rc = finish(ctx))) return rc;
@@ -1090,13 +1220,13 @@ int half_step_t(uot_ctx* ctx, const uot_problem* pb, double eps, int side, const
   hipStream_t s = ctx->work;
   if ((rc = begin(ctx))) return rc;
   Bufs<T> B = carve<T>(P, ws);
-  Ctrl init = make_ctrl(eps, 0, 0, 0, 0, 1);
+  Ctrl init = make_ctrl(eps, 0, 0, 0, 0, 1, pb->F1, pb->F2);
   launch_ctrl_init(B.ctrl, init, s);
   launch_log<T>(static_cast<const T*>(pb->p), B.logp, P.N, 1, s);
   launch_log<T>(static_cast<const T*>(pb->q), B.logq, P.M, 1, s);
   launch_log<T>(static_cast<const T*>(pb->dx), B.logdx, P.N, 0, s);
   launch_log<T>(static_cast<const T*>(pb->dy), B.logdy, P.M, 0, s);
-  if (P.geom == UOT_GEOM_GRID)
+  if (P.geom == UOT_GEOM_GRID && !P.line)
     for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, 1, P.cost, s);
   if (side == 0) {
     launch_init_pot<T>(pot_in, B.logdy, nullptr, B.wv, P.M, P.M, B.ctrl, 0, s);
@@ -1129,79 +1259,150 @@ int objective_t(uot_ctx* ctx, const uot_problem* pb, double eps, const T* u, con
   hipStream_t s = ctx->work;
   if ((rc = begin(ctx))) return rc;
   Bufs<T> B = carve<T>(P, ws);
-  Ctrl init = make_ctrl(eps, 0, 0, 0, 0, 1);
+  const Ctrl init = make_ctrl(eps, 0, 0, 0, 0, 1, pb->F1, pb->F2);
   launch_ctrl_init(B.ctrl, init, s);
-  launch_log<T>(static_cast<const T*>(pb->dx), B.logdx, P.N, 0, s);
-  launch_log<T>(static_cast<const T*>(pb->dy), B.logdy, P.M, 0, s);
-  if (P.geom == UOT_GEOM_GRID)
-    for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, 1, P.cost, s);
-  // w fields of u and v, and of the zero potential (for m(K))
-  launch_init_pot<T>(v, B.logdy, nullptr, B.wv, P.M, P.M, B.ctrl, 0, s);
-  launch_init_pot<T>(u, B.logdx, nullptr, B.wu, P.N, P.N, B.ctrl, 0, s);
-  EpiArgs<T> raw{};
-  raw.mode = EPI_RAW;
-  auto product = [&](int side, const T* w, T* outp, T* const* tabs) {
-    raw.out = outp;
-    if (P.geom == UOT_GEOM_GRID) {
-      grid_chain<T>(P, w, tabs, side, B.ctrl, raw, B.t2, B.t3, s);
-    } else {
-      dense_half<T>(P, pb->geom, side, w, B, B.ctrl, raw, s);
-    }
-  };
-  // S(v) -> t1, T(u) -> pm region is busy in dense mode, so T goes to t2 after S is consumed
-  double* part = B.obj;
+  const T* pp = static_cast<const T*>(pb->p);
+  const T* qq = static_cast<const T*>(pb->q);
+  const T* dx = static_cast<const T*>(pb->dx);
+  const T* dy = static_cast<const T*>(pb->dy);
+  const DivDev F1 = to_dev(pb->F1), F2 = to_dev(pb->F2);
   const int64_t nbx = (P.N + 255) / 256, nby = (P.M + 255) / 256;
-  product(0, B.wv, B.t1, B.gtab);
-  launch_obj_side<T>(u, B.t1, static_cast<const T*>(pb->p), static_cast<const T*>(pb->dx), P.N, eps,
-                     to_dev(pb->F1), pi1, part, s);
-  product(1, B.wu, B.t1, B.gtab);
-  launch_obj_side<T>(v, B.t1, static_cast<const T*>(pb->q), static_cast<const T*>(pb->dy), P.M, eps,
-                     to_dev(pb->F2), pi2, part + 4 * nbx, s);
-  double* part2 = part + 4 * (nbx + nby);
-  // m(K) = sum_i dx_i e^{S0_i}, S0 = log K(dy):  w = log2 dy  (zero potential)
-  launch_init_pot<T>(nullptr, B.logdy, nullptr, B.t3, P.M, P.M, B.ctrl, 0, s);
-  launch_init_pot<T>(nullptr, B.logdx, nullptr, B.t2, P.N, P.N, B.ctrl, 0, s);
-  if (P.geom == UOT_GEOM_GRID) {
-    // product() uses t2/t3 as temporaries on grids: keep the two w fields in logp/logq
+  double* part = B.obj;
+  double sx[4] = {0, 0, 0, 0}, sy[4] = {0, 0, 0, 0}, mK = 0, cost = 0;
+  std::vector<double> h;
+  auto fetch = [&](int64_t tot) -> int {
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(hipStreamSynchronize(s));
+    h.resize(tot);
+    HIP_TRY(hipMemcpy(h.data(), part, sizeof(double) * tot, hipMemcpyDeviceToHost));
+    return UOT_OK;
+  };
+  auto sum = [&](int64_t first, int64_t n, int64_t step) {
+    double t = 0;
+    for (int64_t b = 0; b < n; ++b) t += h[first + b * step];
+    return t;
+  };
+  bool fp64 = P.geom == UOT_GEOM_GRID && P.cost.kind == UOT_COST_SQEUCLID;
+  for (int k = 0; k < P.dim && fp64; ++k) fp64 = line_applies(true, P.h[k] * P.h[k] * kLog2e / eps);
+  if (P.geom == UOT_GEOM_POINTS) {
+    // FP64 pairs; the row partials of every column split in the (FP32 or
+    // FP64) vectors and split partials of the workspace
+    double* rows = reinterpret_cast<double*>(ws + P.o_logp);
+    const int64_t room = (int64_t)((P.o_parts - P.o_logp) / sizeof(double));
+    auto splits = [&](int64_t Nr, int64_t Mc, int q) {
+      const int64_t want = std::min<int64_t>((2048 + (Nr + 255) / 256 - 1) / ((Nr + 255) / 256), (Mc + 63) / 64);
+      return (int)std::max<int64_t>(1, std::min(want, room / (q * Nr)));
+    };
+    const T* x = static_cast<const T*>(pb->geom.x);
+    const T* y = static_cast<const T*>(pb->geom.y);
+    launch_obj_points<T>(true, P.dim, x, P.N, y, v, dy, P.M, splits(P.N, P.M, 4), eps, P.cost, u, pp, dx, F1, pi1, rows,
+                         part, s);
+    launch_obj_points<T>(false, P.dim, y, P.M, x, u, dx, P.N, splits(P.M, P.N, 2), eps, P.cost, v, qq, dy, F2, pi2, rows,
+                         part + 6 * nbx, s);
+    if ((rc = fetch(6 * (nbx + nby)))) return rc;
+    for (int q = 0; q < 4; ++q) {
+      sx[q] = sum(q, nbx, 6);
+      sy[q] = sum(6 * nbx + q, nby, 6);
+    }
+    cost = sum(4, nbx, 6);
+    mK = sum(5, nbx, 6);
+  } else if (fp64) {
+    // FP64 line passes on four FP64 fields laid over the (FP32 or FP64)
+    // vectors of the workspace
+    double* D[4];
+    for (int k = 0; k < 4; ++k) D[k] = reinterpret_cast<double*>(ws + P.o_logp + align_up(8 * P.N) * k);
+    GridCells g{};
+    g.dim = P.dim;
+    for (int k = 0; k < 3; ++k) {
+      g.n[k] = P.n[k];
+      g.h[k] = P.h[k];
+    }
+    const double le = kLog2e / eps;
+    // product of the weights `in` into D[1] (D[2] is scratch)
+    auto product = [&](const double* in) {
+      EpiArgs<double> raw{};
+      raw.mode = EPI_RAW;
+      const double* src = in;
+      for (int k = P.dim - 1; k >= 0; --k) {
+        raw.out = (k & 1) ? D[2] : D[1];
+        int64_t A = 1, Bn = 1;
+        for (int j = 0; j < k; ++j) A *= P.n[j];
+        for (int j = k + 1; j < P.dim; ++j) Bn *= P.n[j];
+        launch_line<double>(src, A, (int)P.n[k], Bn, P.h[k], P.h[k] * P.h[k] * le, 1 << 30, 0, B.ctrl, raw, s);
+        src = raw.out;
+      }
+    };
+    auto weight = [&](const T* pot, const T* d, int axis, double* o) { launch_obj_weight<T>(pot, d, P.N, le, g, axis, o, s); };
+    double* o = part;
+    auto moment = [&](const T* pot, const T* d, int axis) {   // sum of D[1] against (pot, d) and a coordinate
+      weight(pot, d, axis, D[3]);
+      launch_obj_sum(D[3], D[1], P.N, o, s);
+      o += nbx;
+    };
+    weight(v, dy, -1, D[0]);
+    product(D[0]);
+    launch_obj_side64<T>(u, D[1], pp, dx, P.N, eps, F1, pi1, o, s);
+    o += 4 * nbx;
+    moment(u, dx, -2);
+    weight(u, dx, -1, D[0]);
+    product(D[0]);
+    launch_obj_side64<T>(v, D[1], qq, dy, P.N, eps, F2, pi2, o, s);
+    o += 4 * nbx;
+    moment(v, dy, -2);
+    weight(nullptr, dy, -1, D[0]);
+    product(D[0]);
+    moment(nullptr, dx, -1);
+    for (int k = 0; k < P.dim; ++k) {
+      weight(v, dy, k, D[0]);
+      product(D[0]);
+      moment(u, dx, k);
+    }
+    if ((rc = fetch(o - part))) return rc;
+    for (int q = 0; q < 4; ++q) {
+      sx[q] = sum(q, nbx, 4);
+      sy[q] = sum(5 * nbx + q, nbx, 4);
+    }
+    cost = sum(4 * nbx, nbx, 1) + sum(9 * nbx, nbx, 1);
+    mK = sum(10 * nbx, nbx, 1);
+    for (int k = 0; k < P.dim; ++k) cost -= 2.0 * sum((11 + k) * nbx, nbx, 1);
+  } else {
+    // grids of the WF cost, or of a few cells per kernel width
+    launch_log<T>(dx, B.logdx, P.N, 0, s);
+    launch_log<T>(dy, B.logdy, P.M, 0, s);
+    for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, 1, P.cost, s);
+    launch_init_pot<T>(v, B.logdy, nullptr, B.wv, P.M, P.M, B.ctrl, 0, s);
+    launch_init_pot<T>(u, B.logdx, nullptr, B.wu, P.N, P.N, B.ctrl, 0, s);
+    EpiArgs<T> raw{};
+    raw.mode = EPI_RAW;
+    auto product = [&](int side, const T* w, T* outp, T* const* tabs) {
+      raw.out = outp;
+      grid_chain<T>(P, w, tabs, side, B.ctrl, raw, B.t2, B.t3, s);
+    };
+    product(0, B.wv, B.t1, B.gtab);
+    launch_obj_side<T>(u, B.t1, pp, dx, P.N, eps, F1, pi1, part, s);
+    product(1, B.wu, B.t1, B.gtab);
+    launch_obj_side<T>(v, B.t1, qq, dy, P.M, eps, F2, pi2, part + 4 * nbx, s);
+    // m(K) = sum_i dx_i e^{S0_i}, S0 = log K(dy):  w = log2 dy  (zero potential)
     launch_init_pot<T>(nullptr, B.logdy, nullptr, B.logq, P.M, P.M, B.ctrl, 0, s);
     launch_init_pot<T>(nullptr, B.logdx, nullptr, B.logp, P.N, P.N, B.ctrl, 0, s);
     product(0, B.logq, B.t1, B.gtab);
-    launch_sum_exp2<T>(B.logp, B.t1, P.N, part2, s);
-  } else {
-    product(0, B.t3, B.t1, B.gtab);
-    launch_sum_exp2<T>(B.t2, B.t1, P.N, part2, s);
-  }
-  double* part3 = part2 + nbx;
-  // <C, R>: one product per axis with that axis' kernel times C (grid), or a direct pass (points)
-  int ncost = 0;
-  if (P.geom == UOT_GEOM_GRID) {
+    launch_sum_exp2<T>(B.logp, B.t1, P.N, part + 8 * nbx, s);
+    // <C, R>: one product per axis with that axis' kernel times C
     for (int a = 0; a < P.dim; ++a) {
       launch_gtab_cost<T>(B.gcost, (int)P.n[a], P.h[a], eps, P.cost, s);
       T* tabs[3] = {B.gtab[0], B.gtab[1], B.gtab[2]};
       tabs[a] = B.gcost;
       product(0, B.wv, B.t1, tabs);
-      launch_sum_exp2<T>(B.wu, B.t1, P.N, part3 + ncost * nbx, s);
-      ++ncost;
+      launch_sum_exp2<T>(B.wu, B.t1, P.N, part + (9 + a) * nbx, s);
     }
-  } else {
-    launch_dense_cost<T>(P.dim, static_cast<const T*>(pb->geom.x), P.N, static_cast<const T*>(pb->geom.y), B.wv, P.M,
-                         eps, B.t1, P.cost, s);
-    launch_sum_exp2<T>(B.wu, B.t1, P.N, part3, s);
-    ncost = 1;
+    if ((rc = fetch((9 + P.dim) * nbx))) return rc;
+    for (int q = 0; q < 4; ++q) {
+      sx[q] = sum(q, nbx, 4);
+      sy[q] = sum(4 * nbx + q, nbx, 4);
+    }
+    mK = sum(8 * nbx, nbx, 1);
+    cost = sum(9 * nbx, P.dim * nbx, 1);
   }
-  HIP_TRY(hipGetLastError());
-  HIP_TRY(hipStreamSynchronize(s));
-  const int64_t tot = 4 * (nbx + nby) + nbx * (1 + ncost);
-  std::vector<double> h(tot);
-  HIP_TRY(hipMemcpy(h.data(), part, sizeof(double) * tot, hipMemcpyDeviceToHost));
-  double sx[4] = {0, 0, 0, 0}, sy[4] = {0, 0, 0, 0}, mK = 0, cost = 0;
-  for (int64_t b = 0; b < nbx; ++b)
-    for (int q = 0; q < 4; ++q) sx[q] += h[b * 4 + q];
-  for (int64_t b = 0; b < nby; ++b)
-    for (int q = 0; q < 4; ++q) sy[q] += h[4 * nbx + b * 4 + q];
-  for (int64_t b = 0; b < nbx; ++b) mK += h[4 * (nbx + nby) + b];
-  for (int k = 0; k < ncost; ++k)
-    for (int64_t b = 0; b < nbx; ++b) cost += h[4 * (nbx + nby) + nbx * (1 + k) + b];
   out->mass1 = sx[0];
   out->mass2 = sy[0];
   out->massK = mK;
@@ -1226,31 +1427,47 @@ int bary_t(uot_ctx* ctx, const uot_bary_problem* pb, const uot_params* pr, T* u,
   if (!u || !v) return fail(UOT_E_INVALID, "u and v output buffers are required");
   hipStream_t s = ctx->work;
   if ((rc = begin(ctx))) return rc;
+  // paired line passes: the combine runs between the passes of a row's fields
+  const bool pair = P.pair && P.dim == 2 && line_bary_fits(pb->n, (int)P.n[1]);
   Bufs<T> B = carve<T>(P, ws);
   const int64_t size = P.N, nb = pb->n;
   const bool mixed = P.gk == 4 && has_tf16(P) && pr->tol < kMixedSwitchTol;
   Plan P2 = P;
   for (int k = 0; k < 3; ++k) P2.tf16_axis[k] = false;
   Ctrl init = make_ctrl(pr->eps, pr->eps0, pr->eps_stages, pr->iters_per_stage, mixed ? kMixedSwitchTol : pr->tol,
-                        pr->max_iter);
+                        pr->max_iter, pb->F1, pb->F2);
   launch_ctrl_init(B.ctrl, init, s);
-  launch_log<T>(static_cast<const T*>(pb->p), B.logp, nb * size, 1, s);
-  launch_log<T>(static_cast<const T*>(pb->dx), B.logdx, size, 0, s);
+  if (pair) {
+    pair_inputs<T>(P, B, pb->p, pb->dx, B.t3, s);
+  } else {
+    launch_log<T>(static_cast<const T*>(pb->p), B.logp, nb * size, 1, s);
+    launch_log<T>(static_cast<const T*>(pb->dx), B.logdx, size, 0, s);
+    launch_init_pot<T>(nullptr, B.logdx, u, nullptr, nb * size, size, B.ctrl, 0, s);
+  }
   launch_log<T>(static_cast<const T*>(pb->dy), B.logdy, size, 0, s);
-  for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, P.nst, P.cost, s);
-  launch_init_pot<T>(nullptr, B.logdx, u, nullptr, nb * size, size, B.ctrl, 0, s);
+  for (int k = 0; k < P.dim && !P.line; ++k)
+    launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, P.nst, P.cost, s);
   launch_init_pot<T>(static_cast<const T*>(pr->v0), B.logdy, v, B.wv, nb * size, size, B.ctrl, 0, s);
   HIP_TRY(hipGetLastError());
   BaryW la{};
-  double asum = 0;
   for (int k = 0; k < pb->n; ++k) {
-    la.v[k] = std::log(pb->alpha[k]);
     la.a[k] = pb->alpha[k];
-    asum += pb->alpha[k];
   }
   const DivDev F2 = to_dev(pb->F2);
+  CtlHost host;
+  host.c = B.ctrl;
+  host.parts = B.parts;
+  host.nparts = P.nparts_x;
+  host.hist = pr->res_hist;
+  if (pair) pair_start<T>(P, B, s);
   auto iteration_with = [&](const Plan& PP) {
     return [&, pp = &PP](int par) {
+      if (pair) {
+        pair_x<T>(*pp, B, par, prox_epi<T>(B.t3, nullptr, B.logp, B.logdx, nullptr, B.parts, size, pb->F1), s);
+        const EpiArgs<T> ep = with_host<T>(prox_epi<T>(v, nullptr, nullptr, B.logdy, logh, nullptr, size, pb->F2), host);
+        launch_line_bary<T>(B.t2, pb->n, P.n[0], (int)P.n[1], P.h[1], P.c_max[1], 1 | par << 1, B.ctrl, ep, B.t1, la, s);
+        return;
+      }
       EpiArgs<T> ep = prox_epi<T>(u, B.wu, B.logp, B.logdx, nullptr, B.parts, size, pb->F1);
       grid_chain<T>(*pp, B.wv, B.gtab, 0 | par << 1, B.ctrl, ep, B.t1, B.t2, s);
       launch_control(B.ctrl, B.parts, pp->nparts_x, pr->res_hist, s, 0, par);
@@ -1258,7 +1475,7 @@ int bary_t(uot_ctx* ctx, const uot_bary_problem* pb, const uot_params* pr, T* u,
       raw.mode = EPI_RAW;
       raw.out = B.t3;
       grid_chain<T>(*pp, B.wu, B.gtab, 1 | par << 1, B.ctrl, raw, B.t1, B.t2, s);
-      launch_bary_combine<T>(B.t3, pb->n, size, la, std::log(asum), F2, B.logdy, v, B.wv, logh, B.ctrl,
+      launch_bary_combine<T>(B.t3, pb->n, size, la, F2, B.logdy, v, B.wv, logh, B.ctrl,
                              1 | par << 1, s);
     };
   };
@@ -1267,6 +1484,10 @@ int bary_t(uot_ctx* ctx, const uot_bary_problem* pb, const uot_params* pr, T* u,
   const double final_tol = pr->tol;
   rc = run_loop(ctx, B.ctrl, pr, iteration, res, mixed ? &iteration2 : nullptr, &final_tol);
   if (rc) return rc;
+  if (pair) {
+    pair_output<T>(P, B.t3, u, s);
+    HIP_TRY(hipGetLastError());
+  }
   if ((rc = finish(ctx))) return rc;
   if (res->status == -3) return fail(UOT_E_NONFINITE, "non-finite residual");
   return res->status == 0 ? UOT_OK : UOT_NOT_CONVERGED;
@@ -1288,10 +1509,10 @@ int map_t(uot_ctx* ctx, const uot_problem* pb, double eps, const T* v, T* Tout, 
   hipStream_t s = ctx->work;
   if ((rc = begin(ctx))) return rc;
   Bufs<T> B = carve<T>(P, ws);
-  const Ctrl init = make_ctrl(eps, 0, 0, 0, 0, 1);
+  const Ctrl init = make_ctrl(eps, 0, 0, 0, 0, 1, pb->F1, pb->F2);
   launch_ctrl_init(B.ctrl, init, s);
   launch_log<T>(static_cast<const T*>(pb->dy), B.logdy, P.M, 0, s);
-  if (P.geom == UOT_GEOM_GRID)
+  if (P.geom == UOT_GEOM_GRID && !P.line)
     for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, 1, P.cost, s);
   launch_init_pot<T>(v, B.logdy, nullptr, B.wv, P.M, P.M, B.ctrl, 0, s);
   EpiArgs<T> raw{};
@@ -1378,12 +1599,13 @@ int flow_t(uot_ctx* ctx, const uot_flow_problem* fp, const FlowDivs& fd, const u
   T* u = at<T>(ws, o_u);
   const int S = fp->species;
   const int64_t N = P.N, SN = (int64_t)S * N;
-  const Ctrl init = make_ctrl(pr->eps, pr->eps0, pr->eps_stages, pr->iters_per_stage, pr->tol, pr->max_iter);
+  const Ctrl init = make_ctrl(pr->eps, pr->eps0, pr->eps_stages, pr->iters_per_stage, pr->tol, pr->max_iter, fd.F1,
+                              fd.F2);
   launch_ctrl_init(B.ctrl, init, s);
   launch_log<T>(static_cast<const T*>(fp->dx), B.logdx, N, 0, s);
   launch_log<T>(static_cast<const T*>(fp->dx), B.logdy, N, 0, s);
   launch_log<T>(static_cast<const T*>(fp->q), B.logq, N, 1, s);
-  if (P.geom == UOT_GEOM_GRID)
+  if (P.geom == UOT_GEOM_GRID && !P.line)
     for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, P.nst, P.cost, s);
   HIP_TRY(hipMemcpyAsync(dens, fp->p0, sizeof(T) * SN, hipMemcpyDeviceToDevice, s));
   if (pr->v0) HIP_TRY(hipMemcpyAsync(v, pr->v0, sizeof(T) * SN, hipMemcpyDeviceToDevice, s));
@@ -1464,7 +1686,7 @@ int time_half_step_t(uot_ctx* ctx, const uot_problem* pb, int nb, double eps, co
   hipStream_t s = ctx->work;
   if ((rc = begin(ctx))) return rc;
   Bufs<T> B = carve<T>(P, ws);
-  Ctrl init = make_ctrl(eps, 0, 0, 0, 0, 1);
+  Ctrl init = make_ctrl(eps, 0, 0, 0, 0, 1, pb->F1, pb->F2);
   launch_ctrl_init(B.ctrl, init, s);
   uot_problem pbs = *pb;
   const int32_t* px = nullptr;
@@ -1477,7 +1699,7 @@ int time_half_step_t(uot_ctx* ctx, const uot_problem* pb, int nb, double eps, co
   log_into<T>(pb->p, B.logp, nb * P.N, 1, px, B.t1, s);
   log_into<T>(pb->dx, B.logdx, P.N, 0, px, B.t1, s);
   log_into<T>(pb->dy, B.logdy, P.M, 0, py, B.t1, s);
-  if (P.geom == UOT_GEOM_GRID)
+  if (P.geom == UOT_GEOM_GRID && !P.line)
     for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, 1, P.cost, s);
   const T* vin = v;
   if (py) {
@@ -1497,7 +1719,14 @@ int time_half_step_t(uot_ctx* ctx, const uot_problem* pb, int nb, double eps, co
   raw.mode = EPI_RAW;
   bool count_pairs = false;   // the matrix-core product's pair counter, off while timed
   std::vector<std::function<void()>> ks;
-  if (P.geom == UOT_GEOM_GRID) {
+  if (P.line) {
+    T* const tmp[2] = {B.t1, B.t2};
+    for (int k = P.dim - 1; k >= 0; --k) {
+      raw.out = tmp[k & 1];
+      const T* in = k == P.dim - 1 ? B.wv : tmp[(k + 1) & 1];
+      ks.push_back([&, k, in, e = k == 0 ? ep : raw] { line_axis<T>(P, k, in, 0, B.ctrl, e, s); });
+    }
+  } else if (P.geom == UOT_GEOM_GRID) {
     const int64_t nbf = nb;
     if (P.dim == 1) {
       ks.push_back([&] { contig_pass<T>(P, 0, B.wv, nbf, B.gtab, 0, B.ctrl, ep, s); });
@@ -1767,7 +1996,7 @@ int gibbs_items(const BatchPlan& P, const uot_batch_problem* pb, int rows, int c
 template <typename T>
 void gibbs_launch(const BatchPlan& P, const uot_batch_problem* pb, const BatchGibbs& G, double eps, int rows, int cols,
                   const T* w, T* w2, T* out, char* ws, hipStream_t s) {
-  launch_ctrl_init(G.ctrl, make_ctrl(eps, 0, 0, 0, 0, 1), s);
+  launch_ctrl_init(G.ctrl, make_ctrl(eps, 0, 0, 0, 0, 1, pb->F1, pb->F2), s);
   launch_batch_init(G.bc_dev, (int)P.B, G.ctrl, s);
   launch_set_int(G.curs + rows, 1, G.n_items[rows], s);
   launch_set_int(G.curs + 2 + rows, 1, 0, s);
@@ -2075,7 +2304,8 @@ int batch_t(uot_ctx* ctx, const uot_batch_problem* pb, const uot_params* pr, T* 
     bbal.lam2 = pb->F2.lambda;
   }
   auto init_state = [&]() {
-    Ctrl init = make_ctrl(pr->eps, pr->eps0, pr->eps_stages, pr->iters_per_stage, pr->tol, pr->max_iter);
+    Ctrl init = make_ctrl(pr->eps, pr->eps0, pr->eps_stages, pr->iters_per_stage, pr->tol, pr->max_iter, pb->F1,
+                          pb->F2);
     launch_ctrl_init(ctrl, init, s);
     launch_batch_init(bc_dev, (int)P.B, ctrl, s);
     launch_batch_compact(ctrl, bc_dev, (int)P.B, lists, s);   // every problem's items

@@ -675,6 +675,7 @@ __global__ __launch_bounds__(kBlock, G == 4 ? 4 : 2) void k_batch_mf(const BItem
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int li = lane & 15, q = lane >> 4;
   const int n_items = *count;
+  const EpiK<float> K = epi_consts_of<float>(c, side, ep);
   const int32_t* __restrict__ skip = half_of(side) == 0 ? bc->stop : bc->yskip;
   while (true) {
     __syncthreads();   // the previous item's reads of the block's LDS are done
@@ -705,7 +706,7 @@ __global__ __launch_bounds__(kBlock, G == 4 ? 4 : 2) void k_batch_mf(const BItem
       const int row = wv * (16 * G) + (4 * h + q) * 16 + li;
       if (row < I.nrows) {
         const float lse = mg == -__builtin_inff() ? mg : mg + rg + __builtin_log2f(tg);
-        epi_elem<float>(rb + row, lse, c, side, ep, ra);
+        epi_elem<float>(rb + row, lse, K, ep, ra);
         if (bal) bal_elem<float>(rb + row, lse, c, side, ep, mb);
         pw[rb + row] = mg;
       }

@@ -26,6 +26,7 @@ template <> struct Num<float> {
   static __device__ __forceinline__ float exp2(float x) { return __builtin_amdgcn_exp2f(x); }
   static __device__ __forceinline__ float log2(float x) { return __builtin_amdgcn_logf(x); }
   static __device__ __forceinline__ float expm1(float x) { return ::expm1f(x); }
+  static __device__ __forceinline__ float log1p(float x) { return ::log1pf(x); }
   static __device__ __forceinline__ float exp(float x) { return ::expf(x); }
   static __device__ __forceinline__ float log(float x) { return ::logf(x); }
   static __device__ __forceinline__ float fmax(float a, float b) { return __builtin_fmaxf(a, b); }
@@ -39,12 +40,39 @@ template <> struct Num<double> {
   static __device__ __forceinline__ double exp2(double x) { return ::exp2(x); }
   static __device__ __forceinline__ double log2(double x) { return ::log2(x); }
   static __device__ __forceinline__ double expm1(double x) { return ::expm1(x); }
+  static __device__ __forceinline__ double log1p(double x) { return ::log1p(x); }
   static __device__ __forceinline__ double exp(double x) { return ::exp(x); }
   static __device__ __forceinline__ double log(double x) { return ::log(x); }
   static __device__ __forceinline__ double fmax(double a, double b) { return __builtin_fmax(a, b); }
   static __device__ __forceinline__ double fmin(double a, double b) { return __builtin_fmin(a, b); }
   static __device__ __forceinline__ double fma(double a, double b, double c) { return __builtin_fma(a, b, c); }
 };
+
+// 2^x: x = n + f with |f| <= 1/2, the Taylor polynomial of 2^f to degree 13
+// (remainder below 5e-18), scaled by 2^n; arguments below -1100 give 0
+__device__ __forceinline__ double exp2_f64(double x) {
+  const double xc = x < -1100.0 ? -1100.0 : x;
+  const double n = __builtin_rint(xc);
+  const double f = xc - n;
+  constexpr double L = kLn2;
+  constexpr double c2 = L * L / 2, c3 = c2 * L / 3, c4 = c3 * L / 4, c5 = c4 * L / 5, c6 = c5 * L / 6,
+                   c7 = c6 * L / 7, c8 = c7 * L / 8, c9 = c8 * L / 9, c10 = c9 * L / 10, c11 = c10 * L / 11,
+                   c12 = c11 * L / 12, c13 = c12 * L / 13;
+  // two interleaved chains in f^2 (even and odd powers)
+  const double g = f * f;
+  double a = __builtin_fma(c12, g, c10), b = __builtin_fma(c13, g, c11);
+  a = __builtin_fma(a, g, c8);
+  b = __builtin_fma(b, g, c9);
+  a = __builtin_fma(a, g, c6);
+  b = __builtin_fma(b, g, c7);
+  a = __builtin_fma(a, g, c4);
+  b = __builtin_fma(b, g, c5);
+  a = __builtin_fma(a, g, c2);
+  b = __builtin_fma(b, g, c3);
+  b = __builtin_fma(b, g, L);
+  const double r = __builtin_fma(b, f, __builtin_fma(a, g, 1.0));
+  return __builtin_amdgcn_ldexp(r, (int)n);
+}
 
 // ---------------------------------------------------------------------------
 // cos(sqrt(z)) on 0 <= z <= (pi/2)^2 from the Taylor series of cos in
@@ -143,16 +171,64 @@ struct Ctrl {
   double res;        // residual of the last iteration
   double du;         // max |u_new - u_old| of the last iteration (potential units)
   double eps[2];     // eps of the iteration of parity p
+  double le[2];      // log2(e) / eps
+  double coef[2][2]; // [p][side]: the proxdiv factor of that side's penalty at that eps (KL, growth)
+  double eps_after[2], le_after[2];  // eps, le of the iteration that follows the one of parity p
   double eps_tab[kMaxStages + 1];
+  double lam[2];     // weights of the two penalties (kinds below), for coef
   double zeta;       // log z of a total-mass penalty (Algorithm 4); 0 otherwise
   // ragged batches only
   int32_t active[2];  // problems still active after the last iteration (slot = iteration parity)
   int32_t nstop;      // problems stopped so far
   int32_t built[2];   // nstop when the item lists were last rebuilt (slot = iteration parity)
+  int8_t kind[2];     // kinds of the two penalties
+  int8_t pad0[2];
   uint64_t t0_clock;  // device wall clock at the start of the solve
   // timed solves: pair evaluations of the matrix-core products
   unsigned long long pairs;
 };
+
+// what the slot of an iteration holds: its stage, and the eps after it
+struct CtrlSlot {
+  int sn;
+  double eps, le, coef[2], eps_after, le_after;
+};
+__host__ __device__ inline double ctrl_coef(const Ctrl* c, int side, double eps) {
+  return c->kind[side] == 1 ? eps * c->lam[side] / (c->lam[side] + eps) : eps / (1.0 + eps);
+}
+// the slot of an iteration of stage sn, followed by one of stage sa; the
+// quotients of slot `from` are taken over while eps stays the same
+__host__ __device__ inline CtrlSlot slot_values(const Ctrl* c, int sn, int sa, int from) {
+  CtrlSlot s;
+  s.sn = sn;
+  s.eps = c->eps_tab[sn];
+  s.eps_after = c->eps_tab[sa];
+  if (from >= 0 && s.eps == c->eps[from]) {
+    s.le = c->le[from];
+    s.coef[0] = c->coef[from][0];
+    s.coef[1] = c->coef[from][1];
+  } else {
+    s.le = kLog2e / s.eps;
+    s.coef[0] = ctrl_coef(c, 0, s.eps);
+    s.coef[1] = ctrl_coef(c, 1, s.eps);
+  }
+  s.le_after = s.eps_after == s.eps ? s.le : kLog2e / s.eps_after;
+  return s;
+}
+__host__ __device__ inline void set_slot(Ctrl* c, int p, const CtrlSlot& s) {
+  c->stage[p] = s.sn;
+  c->eps[p] = s.eps;
+  c->le[p] = s.le;
+  c->coef[p][0] = s.coef[0];
+  c->coef[p][1] = s.coef[1];
+  c->eps_after[p] = s.eps_after;
+  c->le_after[p] = s.le_after;
+}
+// annealing stage of iteration l
+__host__ __device__ inline int stage_at(const Ctrl* c, int64_t l) {
+  const int64_t sn = c->iters_per_stage > 0 ? l / c->iters_per_stage : c->n_stages;
+  return sn > c->n_stages ? c->n_stages : (int)sn;
+}
 
 // A kernel's `side` argument: bit 0 the half-step (0: X, 1: Y), bit 1 the
 // parity of the iteration it belongs to.
@@ -166,6 +242,7 @@ __device__ __forceinline__ int stage_of(const Ctrl* c, int side) { return c->sta
 __device__ __forceinline__ double eps_next_of(const Ctrl* c, int side) {
   return c->eps[par_of(side) ^ half_of(side)];
 }
+__device__ __forceinline__ double le_next_of(const Ctrl* c, int side) { return c->le[par_of(side) ^ half_of(side)]; }
 
 // per-problem state of a ragged batch (arrays of length B in the workspace)
 struct BCtrl {
@@ -218,33 +295,65 @@ struct DivDev {
   double lam, log_alpha, log_beta;   // growth: log_alpha = log(1 - lam)
 };
 
+// A factor carried in two parts c + cl.  The rows below multiply by eps, or by
+// eps lam / (lam + eps) (KL) and eps / (1 + eps) (growth): a KL iteration
+// multiplies the level of the potentials by lam / (lam + eps) each time, so a
+// rounding of its factor (2^-24 in FP32) moves the fixed point lam / eps times
+// as far (at lam 0.5, eps 2e-3: 1e-5 of the potentials, most of what a
+// barycentre's were off by), and one of eps changes the problem.
+template <typename T> struct ProxMul {
+  T c, cl;
+  __device__ __forceinline__ void set(double k) {
+    c = T(k);
+    cl = T(k - double(c));
+  }
+  __device__ __forceinline__ T mul(T d) const {
+    if constexpr (sizeof(T) == 8) return c * d;
+    return Num<T>::fma(c, d, Num<T>::fmax(d, -d) < Num<T>::pinf() ? cl * d : T(0));
+  }
+};
+template <typename T> struct ProxK {
+  ProxMul<T> eps, coef;
+  __device__ __forceinline__ void set(double e, double k) {
+    eps.set(e);
+    coef.set(k);
+  }
+  __device__ __forceinline__ void init(const DivDev& F, double e) {
+    set(e, F.kind == 1 ? e * F.lam / (F.lam + e) : e / (1.0 + e));
+  }
+};
+
 template <typename T>
-__device__ __forceinline__ T proxdiv_pot(const DivDev& F, T logp, T S, T eps) {
+__device__ __forceinline__ T proxdiv_pot(const DivDev& F, T logp, T S, const ProxK<T>& K) {
   // log(p/s): -inf where p = 0 (also where s = 0: 0/0 = 0), +inf where only s = 0
   const T d = (logp == Num<T>::ninf()) ? Num<T>::ninf() : logp - S;
   switch (F.kind) {
     case 0:
-      return eps * d;
-    case 1: {
-      const T lam = T(F.lam);
-      return (eps * lam / (lam + eps)) * d;
-    }
+      return K.eps.mul(d);
+    case 1:
+      return K.coef.mul(d);
     case 2: {
       const T lam = T(F.lam);
-      return Num<T>::fmin(Num<T>::fmax(eps * d, -lam), lam);
+      return Num<T>::fmin(Num<T>::fmax(K.eps.mul(d), -lam), lam);
     }
     case 3: {
-      const T lo = F.has_lo ? eps * (T(F.log_alpha) + d) : Num<T>::ninf();
-      const T hi = F.has_hi ? eps * (T(F.log_beta) + d) : Num<T>::pinf();
+      const T lo = F.has_lo ? K.eps.mul(T(F.log_alpha) + d) : Num<T>::ninf();
+      const T hi = F.has_hi ? K.eps.mul(T(F.log_beta) + d) : Num<T>::pinf();
       return Num<T>::fmin(hi, Num<T>::fmax(lo, T(0)));
     }
     default: {
       // growth functional (tumour example of the WF gradient flows): the
       // constant branch -log kappa below the switch, the KL(1)-like branch
       // eps (log p - log s) / (1 + eps) above it; p is the density cap
-      return Num<T>::fmin(-T(F.log_alpha), (eps / (T(1) + eps)) * d);
+      return Num<T>::fmin(-T(F.log_alpha), K.coef.mul(d));
     }
   }
+}
+template <typename T>
+__device__ __forceinline__ T proxdiv_pot(const DivDev& F, T logp, T S, T eps) {
+  ProxK<T> k;
+  k.init(F, double(eps));
+  return proxdiv_pot<T>(F, logp, S, k);
 }
 
 // relative residual num / den with 0/0 = 0 (a marginal that vanishes before
@@ -335,14 +444,14 @@ __device__ __forceinline__ void wave_res_reduce(float& m, float& den, float& num
   }
 }
 
-// Reduce (m, den, num) and the largest |du| over a block of 256 threads (m in
+// Reduce (m, den, num) and the largest |du| over a block of NT threads (m in
 // log2 units); thread 0 writes the result.  Every thread of the block must
 // call this.  The partials only feed the stopping test and the reported
 // sup-norm, so FP32 with the hardware exp2 is enough (relative error ~1e-7
 // on r; du is rounded once to FP32).
-template <typename T>
+template <typename T, int NT = 256>
 __device__ __forceinline__ void block_res_reduce(T m_in, T den_in, T num_in, T du_in, ResPart* out) {
-  __shared__ float sm[4][4];
+  __shared__ float sm[NT / 64][4];
   float m = float(m_in), den = float(den_in), num = float(num_in), du = float(du_in);
   wave_res_reduce(m, den, num, du);
   const int w = threadIdx.x >> 6;
@@ -355,7 +464,7 @@ __device__ __forceinline__ void block_res_reduce(T m_in, T den_in, T num_in, T d
   __syncthreads();
   if (threadIdx.x == 0) {
     float M = sm[0][0], D = sm[0][1], U = sm[0][2], X = sm[0][3];
-    for (int k = 1; k < (int)(blockDim.x >> 6); ++k) {
+    for (int k = 1; k < NT / 64; ++k) {
       res_merge<float>(M, D, U, sm[k][0], sm[k][1], sm[k][2]);
       X = fmaxf(X, sm[k][3]);
     }

@@ -47,50 +47,118 @@ __device__ __forceinline__ EpiIn<T> epi_load(int64_t e, const EpiArgs<T>& ep) {
   return x;
 }
 
+// The factors an epilogue multiplies by, once per thread: quotients by eps are
+// products with a reciprocal carried in two parts (k + kl, so that pot k is
+// rounded once), in place of an IEEE division per element and use.
+template <typename T> struct EpiK {
+  T zeta;
+  T ke, kel;   // log2(e) / eps
+  T kw, kwl;   // log2(e) / eps_w
+  ProxK<T> k;  // eps, and the factor of KL or growth
+};
+// k + kl = r
+template <typename T> __device__ __forceinline__ void epi_parts(double r, T& k, T& kl) {
+  k = T(r);
+  kl = T(r - double(k));
+}
+// from the control block's values (le: log2(e) / eps, le_w that of w)
 template <typename T>
-__device__ __forceinline__ void epi_apply(int64_t e, T S2, const EpiIn<T>& x, const Ctrl* __restrict__ c, int side,
-                                          const EpiArgs<T>& ep, ResAcc<T>& ra) {
-  if (ep.mode == EPI_RAW) {
-    ep.out[e] = S2;
-    return;
-  }
-  const T eps = T(eps_of(c, side));
-  const T eps_w = T(eps_next_of(c, side));   // w feeds the next half-step
+__device__ __forceinline__ EpiK<T> epi_consts(double eps, double le, double le_w, double coef, double zeta) {
+  EpiK<T> k;
+  k.zeta = T(zeta);
+  epi_parts<T>(le, k.ke, k.kel);
+  epi_parts<T>(le_w, k.kw, k.kwl);
+  k.k.set(eps, coef);
+  return k;
+}
+// pot (k + kl) + a
+template <typename T> __device__ __forceinline__ T epi_scale(T pot, T k, T kl, T a) {
+  return Num<T>::fma(pot, k, sizeof(T) == 4 ? Num<T>::fma(pot, kl, a) : a);
+}
+// the weight of a potential in the next product, (pot / eps + log d) log2(e)
+// with a = log d log2(e); infinite potentials stay what they are
+template <typename T> __device__ __forceinline__ T epi_weight(T pot, T k, T kl, T a) {
+  return Num<T>::fmax(pot, -pot) < Num<T>::pinf() ? epi_scale<T>(pot, k, kl, a) : pot;
+}
+// e^x - 1 at x = t ln 2: the Taylor polynomial to degree 7 for |x| < 1/4
+// (remainder below 4e-10 of x), else 2^t - 1
+__device__ __forceinline__ float expm1_log2(float t) {
+  const float x = t * float(kLn2);
+  float p = 1.f / 5040.f;
+  p = __builtin_fmaf(p, x, 1.f / 720.f);
+  p = __builtin_fmaf(p, x, 1.f / 120.f);
+  p = __builtin_fmaf(p, x, 1.f / 24.f);
+  p = __builtin_fmaf(p, x, 1.f / 6.f);
+  p = __builtin_fmaf(p, x, 0.5f);
+  p = __builtin_fmaf(p * x, x, x);
+  return __builtin_fabsf(x) < 0.25f ? p : __builtin_amdgcn_exp2f(t) - 1.f;
+}
+__device__ __forceinline__ double expm1_log2(double t) { return ::expm1(t * kLn2); }
+
+// The proxdiv epilogue of one element: writes the new potential (and lse_out),
+// adds the residual or mass partial and returns the weight w of the next
+// product; x.uo becomes the new potential.
+template <typename T>
+__device__ __forceinline__ T epi_core(int64_t e, T S2, EpiIn<T>& x, const EpiK<T>& K, const EpiArgs<T>& ep,
+                                      ResAcc<T>& ra) {
   const T Sraw = S2 * T(kLn2);
-  const T S = Sraw + T(c->zeta);              // z K(.): log z of a total-mass penalty, else 0
-  const T ld = x.ld;
+  const T S = Sraw + K.zeta;                  // z K(.): log z of a total-mass penalty, else 0
+  const T ld2 = x.ld * T(kLog2e);
+  const T sd2 = S2 + K.zeta * T(kLog2e) + ld2;
   const T uo = x.uo;
-  const T un = proxdiv_pot<T>(ep.F, x.lp, S, eps);
+  const T un = proxdiv_pot<T>(ep.F, x.lp, S, K.k);
   // a vanishing product (K b = 0 here, possible with exact zeros of K): the
   // row of the plan is zero whatever the potential, so the point carries no
   // marginal mass and enters the next product as -inf
   const bool vanish = Sraw == Num<T>::ninf();
   ep.pot[e] = un;
-  if (ep.wnext) ep.wnext[e] = vanish ? Num<T>::ninf() : (un / eps_w + ld) * T(kLog2e);
+  x.uo = un;
+  const T w = vanish ? Num<T>::ninf() : epi_weight<T>(un, K.kw, K.kwl, ld2);
   if (ep.lse_out) ep.lse_out[e] = S;
-  if (vanish) return;
+  if (vanish) return w;
   if (ep.part) {
     if (un == Num<T>::ninf()) {
       if (uo != Num<T>::ninf()) {
-        ra.add((S + uo / eps + ld) * T(kLog2e), T(0), T(1));
+        ra.add(epi_scale<T>(uo, K.ke, K.kel, sd2), T(0), T(1));
         ra.du = Num<T>::pinf();           // a potential that jumped to -inf
       }
     } else {
-      const T d = Num<T>::expm1((uo - un) / eps);
-      ra.add((S + un / eps + ld) * T(kLog2e), T(1), Num<T>::fmax(d, -d));
       const T a = uo - un;
+      const T d = expm1_log2(Num<T>::fmax(a, -a) < Num<T>::pinf() ? epi_scale<T>(a, K.ke, K.kel, T(0)) : a);
+      ra.add(epi_scale<T>(un, K.ke, K.kel, sd2), T(1), Num<T>::fmax(d, -d));
       ra.du = Num<T>::fmax(ra.du, uo == Num<T>::ninf() ? Num<T>::pinf() : Num<T>::fmax(a, -a));
     }
   } else if (ep.mass_m) {
     // mass of the plan without z: the (m, den) pair of ra carries it
-    ra.add((Sraw + un / eps + ld) * T(kLog2e), T(1), T(0));
+    ra.add(epi_scale<T>(un, K.ke, K.kel, S2 + ld2), T(1), T(0));
   }
+  return w;
 }
 
 template <typename T>
-__device__ __forceinline__ void epi_elem(int64_t e, T S2, const Ctrl* __restrict__ c, int side,
-                                         const EpiArgs<T>& ep, ResAcc<T>& ra) {
-  epi_apply<T>(e, S2, epi_load<T>(e, ep), c, side, ep, ra);
+__device__ __forceinline__ EpiK<T> epi_consts_of(const Ctrl* __restrict__ c, int side, const EpiArgs<T>& ep) {
+  EpiK<T> k{};
+  if (ep.mode == EPI_RAW) return k;
+  // (w feeds the next half-step, at its eps)
+  const int p = par_of(side), h = half_of(side);
+  return epi_consts<T>(c->eps[p], c->le[p], c->le[p ^ h], c->coef[p][h], c->zeta);
+}
+
+template <typename T>
+__device__ __forceinline__ void epi_apply(int64_t e, T S2, const EpiIn<T>& x, const EpiK<T>& K, const EpiArgs<T>& ep,
+                                          ResAcc<T>& ra) {
+  if (ep.mode == EPI_RAW) {
+    ep.out[e] = S2;
+    return;
+  }
+  EpiIn<T> xi = x;
+  const T w = epi_core<T>(e, S2, xi, K, ep, ra);
+  if (ep.wnext) ep.wnext[e] = w;
+}
+
+template <typename T>
+__device__ __forceinline__ void epi_elem(int64_t e, T S2, const EpiK<T>& K, const EpiArgs<T>& ep, ResAcc<T>& ra) {
+  epi_apply<T>(e, S2, epi_load<T>(e, ep), K, ep, ra);
 }
 
 // Ragged batches, the in-solve mass balance: in the half-steps that run
@@ -126,13 +194,13 @@ __device__ __forceinline__ void bal_elem(int64_t e, T S2, const Ctrl* __restrict
 
 // log2-sum-exp (m, s) over a block in T precision (every thread calls it);
 // thread 0 writes the result
-template <typename T>
+template <typename T, int NT = kBlock>
 __device__ __forceinline__ void block_lse_reduce(T m, T s, T* out_m, T* out_s) {
-  __shared__ T sm[kBlock], ss[kBlock];
+  __shared__ T sm[NT], ss[NT];
   sm[threadIdx.x] = m;
   ss[threadIdx.x] = s;
   __syncthreads();
-  for (int off = kBlock / 2; off >= 1; off >>= 1) {
+  for (int off = NT / 2; off >= 1; off >>= 1) {
     if ((int)threadIdx.x < off) {
       Lse2<T> a;
       a.m = sm[threadIdx.x];
@@ -149,11 +217,11 @@ __device__ __forceinline__ void block_lse_reduce(T m, T s, T* out_m, T* out_s) {
   }
 }
 
-template <typename T>
+template <typename T, int NT = kBlock>
 __device__ __forceinline__ void epi_finish(const EpiArgs<T>& ep, const ResAcc<T>& ra, int part_index) {
   if (ep.mode == EPI_RAW) return;
-  if (ep.part) block_res_reduce<T>(ra.m, ra.den, ra.num, ra.du, ep.part + part_index);
-  else if (ep.mass_m) block_lse_reduce<T>(ra.m, ra.den, ep.mass_m + part_index, ep.mass_s + part_index);
+  if (ep.part) block_res_reduce<T, NT>(ra.m, ra.den, ra.num, ra.du, ep.part + part_index);
+  else if (ep.mass_m) block_lse_reduce<T, NT>(ra.m, ra.den, ep.mass_m + part_index, ep.mass_s + part_index);
 }
 
 // ---------------------------------------------------------------------------
@@ -168,8 +236,9 @@ __device__ __forceinline__ void epi_finish(const EpiArgs<T>& ep, const ResAcc<T>
 // loads of the partials
 struct CtrlSnap {
   int64_t l, max_iter;
-  int stage, n_stages, sn;
-  double tol, eps_next;
+  int stage, n_stages;
+  double tol;
+  CtrlSlot next;
 };
 
 __device__ __forceinline__ CtrlSnap ctrl_snap(const Ctrl* c, int par) {
@@ -179,10 +248,7 @@ __device__ __forceinline__ CtrlSnap ctrl_snap(const Ctrl* c, int par) {
   s.stage = c->stage[par];
   s.n_stages = c->n_stages;
   s.tol = c->tol;
-  int64_t sn = c->iters_per_stage > 0 ? (s.l + 1) / c->iters_per_stage : s.n_stages;
-  if (sn > s.n_stages) sn = s.n_stages;
-  s.sn = (int)sn;
-  s.eps_next = c->eps_tab[sn];
+  s.next = slot_values(c, stage_at(c, s.l + 1), stage_at(c, s.l + 2), par);
   return s;
 }
 
@@ -196,8 +262,7 @@ static __device__ void control_finish(Ctrl* c, const CtrlSnap& s, double r, doub
   c->res = r;
   c->du = du;
   c->iter = s.l + 1;
-  c->stage[par ^ 1] = s.sn;
-  c->eps[par ^ 1] = s.eps_next;
+  set_slot(c, par ^ 1, s.next);
   const bool final_stage = s.stage >= s.n_stages;
   int status = 0;
   bool stop = false;
@@ -222,11 +287,12 @@ static __device__ void control_finish(Ctrl* c, const CtrlSnap& s, double r, doub
 __device__ __forceinline__ void control_skip(Ctrl* c, int par) { c->skip[par ^ 1] = 1; }
 
 // this thread's share of the residual partials of one problem
+template <int NT = kBlock>
 __device__ __forceinline__ void ctl_load(const ResPart* __restrict__ part, int nparts, float& m, float& den,
                                          float& num, float& du) {
   m = -__builtin_inff();
   den = num = du = 0.f;
-  for (int k = threadIdx.x; k < nparts; k += kBlock) {
+  for (int k = threadIdx.x; k < nparts; k += NT) {
     res_merge<float>(m, den, num, part[k].m, part[k].den, part[k].num);
     du = fmaxf(du, part[k].du);
   }
@@ -234,14 +300,74 @@ __device__ __forceinline__ void ctl_load(const ResPart* __restrict__ part, int n
 
 // block reduction of the shares and the control step (every thread of the
 // block calls it)
+template <int NT = kBlock>
 __device__ __forceinline__ void ctl_reduce_finish(Ctrl* c, const CtrlSnap& snap, float m, float den, float num,
                                                   float du, double* __restrict__ hist, int par) {
   __shared__ ResPart tot;
   __syncthreads();   // the block's own reductions before this one are complete
-  block_res_reduce<float>(m, den, num, du, &tot);
+  block_res_reduce<float, NT>(m, den, num, du, &tot);
   __syncthreads();
   if (threadIdx.x == 0)
     control_finish(c, snap, res_ratio(double(tot.num), double(tot.den)), double(tot.du), hist, par);
+}
+
+// Control step of iteration parity par by one block of NT threads.  One
+// problem (nfields 0): the partials and the control fields are loaded before
+// the skip flag is tested.  Several: the partials form nfields equal ranges,
+// and r is the largest per-field residual; the threads of a wave share the
+// fields, L lanes (a power of two) to a field.
+template <int NT = kBlock>
+__device__ __forceinline__ void control_block(Ctrl* c, const ResPart* __restrict__ part, int nparts,
+                                              double* __restrict__ hist, int nfields, int par) {
+  const CtrlSnap snap = ctrl_snap(c, par);
+  if (nfields == 0) {
+    float m, den, num, du;
+    ctl_load<NT>(part, nparts, m, den, num, du);
+    asm volatile("" ::"v"(m), "v"(den), "v"(num), "v"(du));
+    if (c->skip[par]) {
+      if (threadIdx.x == 0) control_skip(c, par);
+      return;
+    }
+    ctl_reduce_finish<NT>(c, snap, m, den, num, du, hist, par);
+    return;
+  }
+  if (c->skip[par]) {
+    if (threadIdx.x == 0) control_skip(c, par);
+    return;
+  }
+  __shared__ float smax[NT], sdu[NT];
+  float rmax = -1.0f, du = 0.f;
+  const int per = nparts / nfields;
+  int L = 1;
+  while (L < 64 && L < per && L * nfields < NT) L *= 2;
+  const int sub = threadIdx.x & (L - 1);
+  // (every lane runs every round, for the shuffles; lanes past the last field repeat it)
+  for (int f0 = 0; f0 < nfields; f0 += NT / L) {
+    const int f = f0 + (int)threadIdx.x / L < nfields ? f0 + (int)threadIdx.x / L : nfields - 1;
+    float m = -__builtin_inff(), den = 0.f, num = 0.f;
+    for (int k = f * per + sub; k < (f + 1) * per; k += L) {
+      res_merge<float>(m, den, num, part[k].m, part[k].den, part[k].num);
+      du = fmaxf(du, part[k].du);
+    }
+    for (int o = 1; o < L; o <<= 1) {
+      const float m2 = __shfl_xor(m, o), d2 = __shfl_xor(den, o), n2 = __shfl_xor(num, o);
+      res_merge<float>(m, den, num, m2, d2, n2);
+    }
+    const float rf = float(res_ratio(double(num), double(den)));
+    rmax = (rf != rf || rmax != rmax) ? rf : (rf > rmax ? rf : rmax);
+  }
+  smax[threadIdx.x] = rmax;
+  sdu[threadIdx.x] = du;
+  __syncthreads();
+  for (int off = NT / 2; off >= 1; off >>= 1) {
+    if ((int)threadIdx.x < off) {
+      const float a = smax[threadIdx.x], b = smax[threadIdx.x + off];
+      smax[threadIdx.x] = (a != a || b != b) ? (a != a ? a : b) : (a > b ? a : b);
+      sdu[threadIdx.x] = fmaxf(sdu[threadIdx.x], sdu[threadIdx.x + off]);
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) control_finish(c, snap, double(smax[0]), double(sdu[0]), hist, par);
 }
 
 }  // namespace uot

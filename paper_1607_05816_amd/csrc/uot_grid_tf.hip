@@ -126,6 +126,7 @@ __global__ __launch_bounds__(kBlock) void k_grid_tf(const float* __restrict__ in
   // opb > 1 only when one chunk holds all of a wave's tap tiles (the host
   // picks opb so), so the taps stay in registers across the output tiles
   __shared__ float smM[2][4][4][64], smS[2][4][4][64];
+  const EpiK<float> K = epi_consts_of<float>(c, side, ep);
   ResAcc<float> ra;
   ra.init();
   for (int o = 0; o < nob; ++o) {
@@ -221,7 +222,7 @@ __global__ __launch_bounds__(kBlock) void k_grid_tf(const float* __restrict__ in
     tot.s = smS[pb][0][wv][lane];
 #pragma unroll
     for (int k = 1; k < 4; ++k) tot.merge(smM[pb][k][wv][lane], smS[pb][k][wv][lane]);
-    if (valid) epi_apply<float>(eo, tot.result(), xin, c, side, ep, ra);
+    if (valid) epi_apply<float>(eo, tot.result(), xin, K, ep, ra);
     eo = eo_next;
     xin = xin_next;
   }

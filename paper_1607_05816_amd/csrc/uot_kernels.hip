@@ -16,6 +16,7 @@
 #include <algorithm>
 #include <cstdlib>
 
+#include "uot_bary.h"
 #include "uot_device.h"
 #include "uot_epilogue.h"
 #include "uot_launch.h"
@@ -49,10 +50,14 @@ __global__ void k_init_pot(const T* __restrict__ v0, const T* __restrict__ logd,
                            int which_eps) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
-  const T eps = T(c->eps[which_eps & 1]);
   T p = v0 ? v0[i] : T(0);
   if (pot) pot[i] = p;
-  if (w) w[i] = (p == Num<T>::pinf()) ? Num<T>::ninf() : (p / eps + logd[i % size]) * T(kLog2e);
+  if (w) {
+    // (the arithmetic of the epilogues, so a solve resumed from its v repeats it)
+    T k, kl;
+    epi_parts<T>(c->le[which_eps & 1], k, kl);
+    w[i] = (p == Num<T>::pinf()) ? Num<T>::ninf() : epi_weight<T>(p, k, kl, logd[i % size] * T(kLog2e));
+  }
 }
 
 // g tables of one grid axis for every eps stage, tab[s][k] = log2 of the 1-D
@@ -163,12 +168,13 @@ __global__ __launch_bounds__(kBlock) void k_grid_strided(const T* __restrict__ i
     }
   }
   merge_waves<T, RI>(acc);
+  const EpiK<T> K = epi_consts_of<T>(c, side, ep);
   ResAcc<T> ra;
   ra.init();
   if (wv == 0 && valid_b) {
 #pragma unroll
     for (int r = 0; r < RI; ++r)
-      if (i0 + r < n) epi_elem<T>((a * n + i0 + r) * B + b, acc[r].result(), c, side, ep, ra);
+      if (i0 + r < n) epi_elem<T>((a * n + i0 + r) * B + b, acc[r].result(), K, ep, ra);
   }
   epi_finish<T>(ep, ra, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
 }
@@ -290,13 +296,14 @@ __global__ __launch_bounds__(kBlock) void k_grid_contig(const T* __restrict__ in
     }
     return;
   }
+  const EpiK<T> K = epi_consts_of<T>(c, side, ep);
   ResAcc<T> ra;
   ra.init();
   if (wv == 0 && valid_a) {
 #pragma unroll
     for (int r = 0; r < RI; ++r) {
       const int i = (blockIdx.x * RI + r) * 64 + lane;
-      if (i < n) epi_elem<T>(a * n + i, acc[r].result(), c, side, ep, ra);
+      if (i < n) epi_elem<T>(a * n + i, acc[r].result(), K, ep, ra);
     }
   }
   epi_finish<T>(ep, ra, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
@@ -979,10 +986,11 @@ __global__ __launch_bounds__(kBlock) void k_dense_epi(const T* __restrict__ pm, 
   if (skip_side(c, side)) return;
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   const bool valid = i < Nr;
+  const EpiK<T> K = epi_consts_of<T>(c, side, ep);
   ResAcc<T> ra;
   ra.init();
   // the column splits of k_dense_lse (partial k of row i at k Nr + i)
-  if (valid) epi_elem<T>(i, merge_parts<T>(pm, ps, Nr, i, nsplit), c, side, ep, ra);
+  if (valid) epi_elem<T>(i, merge_parts<T>(pm, ps, Nr, i, nsplit), K, ep, ra);
   epi_finish<T>(ep, ra, blockIdx.x);
 }
 
@@ -990,63 +998,12 @@ __global__ __launch_bounds__(kBlock) void k_dense_epi(const T* __restrict__ pm, 
 // control kernel (one block), between the X and the Y half-step: reduce the
 // residual partials, count the iteration, pick the next eps, set stop flags.
 // ---------------------------------------------------------------------------
-// control step (one block of 256 threads): reduce the residual partials,
-// count the iteration, pick the next eps, set the stop flag.  (Folding this
-// step into the last block of the final pass needs a device-scope fence in
-// every block, which on a multi-XCD MI355X costs more than the launch.)
-__device__ void control_step(Ctrl* __restrict__ c, const ResPart* __restrict__ part, int nparts,
-                             double* __restrict__ hist, int nfields, int par) {
-  // nfields > 0: the partials form nfields equal contiguous ranges (one per
-  // field) and r is the largest per-field residual
-  __shared__ float smax[kBlock], sdu[kBlock];
-  const CtrlSnap snap = ctrl_snap(c, par);
-  float rmax = -1.0f, du = 0.f;
-  const int per = nparts / nfields;
-  for (int f = threadIdx.x; f < nfields; f += kBlock) {
-    float m = -__builtin_inff(), den = 0.f, num = 0.f;
-    for (int k = f * per; k < (f + 1) * per; ++k) {
-      res_merge<float>(m, den, num, part[k].m, part[k].den, part[k].num);
-      du = fmaxf(du, part[k].du);
-    }
-    const float rf = float(res_ratio(double(num), double(den)));
-    rmax = (rf != rf || rmax != rmax) ? rf : (rf > rmax ? rf : rmax);
-  }
-  smax[threadIdx.x] = rmax;
-  sdu[threadIdx.x] = du;
-  __syncthreads();
-  for (int off = kBlock / 2; off >= 1; off >>= 1) {
-    if ((int)threadIdx.x < off) {
-      const float a = smax[threadIdx.x], b = smax[threadIdx.x + off];
-      smax[threadIdx.x] = (a != a || b != b) ? (a != a ? a : b) : (a > b ? a : b);
-      sdu[threadIdx.x] = fmaxf(sdu[threadIdx.x], sdu[threadIdx.x + off]);
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) control_finish(c, snap, double(smax[0]), double(sdu[0]), hist, par);
-}
-
-// control step of iteration parity par as its own launch.  Single problem:
-// the partials and the control fields are loaded before the skip flag is
-// tested, then reduced with wave exchanges.
+// (Folding this step into the last block of the final pass needs a
+// device-scope fence in every block, which on a multi-XCD MI355X costs more
+// than the launch.)
 __global__ __launch_bounds__(kBlock) void k_control(Ctrl* __restrict__ c, const ResPart* __restrict__ part,
                                                      int nparts, double* __restrict__ hist, int nfields, int par) {
-  if (nfields > 0) {
-    if (c->skip[par]) {
-      if (threadIdx.x == 0) control_skip(c, par);
-      return;
-    }
-    control_step(c, part, nparts, hist, nfields, par);
-    return;
-  }
-  const CtrlSnap snap = ctrl_snap(c, par);
-  float m, den, num, du;
-  ctl_load(part, nparts, m, den, num, du);
-  asm volatile("" ::"v"(m), "v"(den), "v"(num), "v"(du));
-  if (c->skip[par]) {
-    if (threadIdx.x == 0) control_skip(c, par);
-    return;
-  }
-  ctl_reduce_finish(c, snap, m, den, num, du, hist, par);
+  control_block<kBlock>(c, part, nparts, hist, nfields, par);
 }
 
 // plain reduction of residual partials into out[0] (single half-step entry)
@@ -1123,10 +1080,7 @@ template void launch_map_finish<double>(double*, const double*, const double*, i
 __global__ void k_ctrl_post(Ctrl* __restrict__ c) {
   if (threadIdx.x != 0 || blockIdx.x != 0) return;
   const int64_t l = c->iter > 0 ? c->iter - 1 : 0;
-  int64_t sn = c->iters_per_stage > 0 ? l / c->iters_per_stage : c->n_stages;
-  if (sn > c->n_stages) sn = c->n_stages;
-  c->stage[0] = (int)sn;
-  c->eps[0] = c->eps_tab[sn];
+  set_slot(c, 0, slot_values(c, stage_at(c, l), stage_at(c, l + 1), -1));
   c->skip[0] = 0;
 }
 
@@ -1168,48 +1122,7 @@ __global__ void k_ctrl_init(Ctrl* __restrict__ c, Ctrl init) {
 // Y Gibbs product: T2 (n x size, log2 units) ->  log h (natural), and
 //   v_k = eps log proxdiv_{F2(.|h)}(e^{T_k}),  w_k = (v_k/eps_next + log dy) log2(e)
 // ---------------------------------------------------------------------------
-// Table estimatebary (iii) lam TV / (iv) RG[b1, b2]: log h is a root of
-//   TV: A0 + sum_{k: s_k>0} alpha_k clamp((x - log s_k) eps/lam, -1, 1)   (A0: weight of s_k = 0)
-//   RG: sum_k alpha_k [b2 min(x + log b2 - log s_k, 0) + b1 max(x + log b1 - log s_k, 0)]
-// in x = log h; both are non-decreasing and linear between their breakpoints
-// (log s_k -+ lam/eps, log s_k - log b_i).  The smallest root is taken: the
-// first breakpoint where the function is >= 0, linear interpolation from the
-// breakpoint before it.  h = 0 (TV: A0 >= weight of the others; RG: some
-// s_k = 0).  t2: log2 s_k at stride `stride`.
-
-// breakpoint w (0, 1) of input k, natural log t: TV t -+ d, RG t - log b2 / t - log b1
-template <typename T>
-__device__ __forceinline__ T bary_break(bool tv, T t, int w, T d, T lb1, T lb2) {
-  return tv ? (w == 0 ? t - d : t + d) : (w == 0 ? t - lb2 : t - lb1);
-}
-
-// TV / RG barycentre combine with L lanes per cell (L a power of two, 2..64):
-// each lane evaluates f at its share of the cell's breakpoints, segmented
-// shuffle reductions over the L lanes find the smallest breakpoint with
-// f >= 0 and the largest one below it, and f is linear in between.  Spreading
-// the breakpoints over lanes replaces one long dependent loop per cell, which
-// left a launch of a few blocks waiting on memory.
-template <typename T>
-__device__ __forceinline__ T bary_fa(const T* __restrict__ t2, int64_t stride, int n, const BaryW& la, bool tv, T a0,
-                                     T d, T lb1, T lb2, T b1, T b2, bool has_lo, T x) {
-  T acc = tv ? a0 : T(0);
-  for (int k = 0; k < n; ++k) {
-    const T t = t2[k * stride] * T(kLn2);
-    if (t == Num<T>::ninf()) continue;
-    const T al = T(la.a[k]);
-    if (tv) {
-      const T y = (x - t) / d;
-      acc += al * (y < T(-1) ? T(-1) : (y > T(1) ? T(1) : y));
-    } else {
-      const T up = x + lb2 - t, dn = x + lb1 - t;
-      T term = b2 * (up < T(0) ? up : T(0));
-      if (has_lo) term += b1 * (dn > T(0) ? dn : T(0));
-      acc += al * term;
-    }
-  }
-  return acc;
-}
-
+// (the per-cell forms: uot_bary.h)
 template <typename T, int L>
 __global__ __launch_bounds__(kBlock) void k_bary_root(const T* __restrict__ T2, int nm, int64_t size, BaryW la,
                                                        DivDev F2, const T* __restrict__ logdy, T* __restrict__ v,
@@ -1221,131 +1134,43 @@ __global__ __launch_bounds__(kBlock) void k_bary_root(const T* __restrict__ T2, 
   const bool valid = j < size;
   const T* __restrict__ t2 = T2 + (valid ? j : size - 1);   // every lane takes part in the shuffles
   const T eps = T(eps_of(c, side));
-  const T eps_w = T(eps_next_of(c, side));
-  const bool tv = F2.kind == 2;
-  const bool lo = F2.has_lo != 0;
-  T a0 = T(0), a1 = T(0), tmax = Num<T>::ninf(), tmin = Num<T>::pinf();
-  for (int k = 0; k < nm; ++k) {
-    const T t = t2[k * size] * T(kLn2);
-    const T al = T(la.a[k]);
-    if (t == Num<T>::ninf()) {
-      a0 += al;
-    } else {
-      a1 += al;
-      tmax = t > tmax ? t : tmax;
-      tmin = t < tmin ? t : tmin;
-    }
-  }
-  // the cases with a closed answer: no mass (-inf), or RG with every input in
-  // one band (the left end of the zero interval, exactly)
-  bool closed = false;
-  T logh = T(0);
-  if (tv ? (a0 >= a1) : (a0 > T(0))) {
-    closed = true;
-    logh = Num<T>::ninf();
-  } else if (!tv) {
-    const T left = tmax - T(F2.log_beta);
-    if (!lo || left <= tmin - T(F2.log_alpha)) {
-      closed = true;
-      logh = left;
-    }
-  }
-  const T d = tv ? T(F2.lam) / eps : T(0);
-  const T lb1 = lo ? T(F2.log_alpha) : T(0), lb2 = T(F2.log_beta);
-  const T b1 = lo ? T(::exp(F2.log_alpha)) : T(0), b2 = T(::exp(F2.log_beta));
-  const int per = tv ? 2 : (lo ? 2 : 1);
-  const int nbp = nm * per;
-  // smallest breakpoint with f >= 0 (and f there)
-  T bhi = Num<T>::pinf(), fhi = T(0);
-  for (int q = sub; q < nbp; q += L) {
-    const int k = q / per, wq = q % per;
-    const T t = t2[k * size] * T(kLn2);
-    if (t == Num<T>::ninf()) continue;
-    const T b = bary_break<T>(tv, t, wq, d, lb1, lb2);
-    const T fb = bary_fa<T>(t2, size, nm, la, tv, a0, d, lb1, lb2, b1, b2, lo, b);
-    if (fb >= T(0) && b < bhi) {
-      bhi = b;
-      fhi = fb;
-    }
-  }
-#pragma unroll
-  for (int o = L / 2; o >= 1; o >>= 1) {
-    const T ob = __shfl_xor(bhi, o), of = __shfl_xor(fhi, o);
-    if (ob < bhi || (ob == bhi && of < fhi)) {
-      bhi = ob;
-      fhi = of;
-    }
-  }
-  // largest breakpoint below it
-  T blo = Num<T>::ninf();
-  for (int q = sub; q < nbp; q += L) {
-    const int k = q / per, wq = q % per;
-    const T t = t2[k * size] * T(kLn2);
-    if (t == Num<T>::ninf()) continue;
-    const T b = bary_break<T>(tv, t, wq, d, lb1, lb2);
-    if (b < bhi && b > blo) blo = b;
-  }
-#pragma unroll
-  for (int o = L / 2; o >= 1; o >>= 1) {
-    const T ob = __shfl_xor(blo, o);
-    blo = ob > blo ? ob : blo;
-  }
-  if (!closed) {
-    if (blo == Num<T>::ninf()) {
-      logh = bhi;
-    } else {
-      const T flo = bary_fa<T>(t2, size, nm, la, tv, a0, d, lb1, lb2, b1, b2, lo, blo);
-      logh = blo + (T(0) - flo) * (bhi - blo) / (fhi - flo);
-    }
-  }
+  T kw, kwl;
+  epi_parts<T>(le_next_of(c, side), kw, kwl);
+  ProxK<T> K;
+  K.init(F2, eps_of(c, side));
+  const T logh = bary_root<T>(t2, size, nm, la, F2, eps, sub, L);
   if (!valid) return;
   if (sub == 0 && logh_out) logh_out[j] = logh;
   const T ld = logdy[j];
   for (int k = sub; k < nm; k += L) {
     const T S = T2[k * size + j] * T(kLn2);
-    const T vn = proxdiv_pot<T>(F2, logh, S, eps);
+    const T vn = proxdiv_pot<T>(F2, logh, S, K);
     v[k * size + j] = vn;
-    w[k * size + j] = (S == Num<T>::ninf()) ? Num<T>::ninf() : (vn / eps_w + ld) * T(kLog2e);
+    w[k * size + j] = (S == Num<T>::ninf()) ? Num<T>::ninf() : epi_weight<T>(vn, kw, kwl, ld * T(kLog2e));
   }
 }
 
 template <typename T>
 __global__ __launch_bounds__(kBlock) void k_bary_combine(const T* __restrict__ T2, int nm, int64_t size,
-                                                          BaryW log_alpha, double log_sum_alpha,
-                                                          DivDev F2, const T* __restrict__ logdy,
+                                                          BaryW la, DivDev F2, const T* __restrict__ logdy,
                                                           T* __restrict__ v, T* __restrict__ w, T* __restrict__ logh_out,
                                                           const Ctrl* __restrict__ c, int side) {
   if (skip_side(c, side)) return;
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= size) return;
   const T eps = T(eps_of(c, side));
-  const T eps_w = T(eps_next_of(c, side));
-  T logh;   // (TV and RG barycentres run in k_bary_root)
-  if (F2.kind == 0) {
-    double acc = 0.0, asum = 0.0;
-    for (int k = 0; k < nm; ++k) {
-      const double al = ::exp(log_alpha.v[k]);
-      acc += al * double(T2[k * size + j]) * kLn2;
-      asum += al;
-    }
-    logh = T(acc / asum);
-  } else {
-    const T gam = eps / (eps + T(F2.lam));           // eps/(eps+lam)
-    Lse2<T> a;
-    a.init();
-    for (int k = 0; k < nm; ++k) {
-      T t[1] = {T(log_alpha.v[k] * kLog2e) + gam * T2[k * size + j]};
-      a.template add<1>(t);
-    }
-    logh = (a.result() * T(kLn2) - T(log_sum_alpha)) / gam;
-  }
+  T kw, kwl;
+  epi_parts<T>(le_next_of(c, side), kw, kwl);
+  ProxK<T> K;
+  K.init(F2, eps_of(c, side));
+  const T logh = bary_mean<T>(T2 + j, size, nm, la, F2, eps);   // (TV and RG: k_bary_root)
   if (logh_out) logh_out[j] = logh;
   const T ld = logdy[j];
   for (int k = 0; k < nm; ++k) {
     const T S = T2[k * size + j] * T(kLn2);
-    const T vn = proxdiv_pot<T>(F2, logh, S, eps);
+    const T vn = proxdiv_pot<T>(F2, logh, S, K);
     v[k * size + j] = vn;
-    w[k * size + j] = (S == Num<T>::ninf()) ? Num<T>::ninf() : (vn / eps_w + ld) * T(kLog2e);
+    w[k * size + j] = (S == Num<T>::ninf()) ? Num<T>::ninf() : epi_weight<T>(vn, kw, kwl, ld * T(kLog2e));
   }
 }
 
@@ -1364,16 +1189,18 @@ __global__ __launch_bounds__(kBlock) void k_growth_combine(const T* __restrict__
   if (skip_side(c, side)) return;
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= size) return;
-  const T eps = T(eps_of(c, side));
-  const T eps_w = T(eps_next_of(c, side));
+  T kw, kwl;
+  epi_parts<T>(le_next_of(c, side), kw, kwl);
+  ProxK<T> K;
+  K.init(F, eps_of(c, side));
   Lse2<T> a;
   a.init();
   for (int k = 0; k < nm; ++k) {
     T t[1] = {T2[k * size + j]};
     a.template add<1>(t);
   }
-  const T vn = proxdiv_pot<T>(F, logq[j], a.result() * T(kLn2), eps);
-  const T wn = (vn / eps_w + logdy[j]) * T(kLog2e);
+  const T vn = proxdiv_pot<T>(F, logq[j], a.result() * T(kLn2), K);
+  const T wn = epi_weight<T>(vn, kw, kwl, logdy[j] * T(kLog2e));
   for (int k = 0; k < nm; ++k) {
     v[k * size + j] = vn;
     w[k * size + j] = (T2[k * size + j] == Num<T>::ninf()) ? Num<T>::ninf() : wn;
@@ -1500,42 +1327,6 @@ __global__ __launch_bounds__(kBlock) void k_sum_exp2(const T* __restrict__ a, co
     __syncthreads();
   }
   if (threadIdx.x == 0) part[blockIdx.x] = sm[0];
-}
-
-// dense transport-cost moment: for row i, log2 sum_j C_ij 2^{w_j - sc C_ij}
-// (single block column loop; one thread per row; used once per objective)
-template <typename T, int DIM>
-__global__ __launch_bounds__(kBlock) void k_dense_cost(const T* __restrict__ xr, int64_t Nr,
-                                                        const T* __restrict__ yc, const T* __restrict__ w,
-                                                        int64_t Mc, double eps, T* __restrict__ out, CostArgs cost) {
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  if (i >= Nr) return;
-  const double sc = kLog2e / eps;
-  double xi[3] = {0, 0, 0};
-  for (int d = 0; d < DIM; ++d) xi[d] = double(xr[d * Nr + i]);
-  double m = -__builtin_inf(), s = 0.0;
-  for (int64_t j = 0; j < Mc; ++j) {
-    double cst = 0.0;
-    for (int d = 0; d < DIM; ++d) {
-      const double dd = xi[d] - double(yc[d * Mc + j]);
-      cst += dd * dd;
-    }
-    if (cost.kind == 1) {
-      // WF: c = -2 log cos((pi/2) d / cut); no mass beyond the cut
-      if (cst >= cost.cut * cost.cut) continue;
-      cst = -2.0 * ::log(::cos(0.5 * M_PI * ::sqrt(cst) / cost.cut));
-    }
-    const double t = double(w[j]) - sc * cst;
-    if (t == -__builtin_inf() || cst == 0.0) continue;
-    const double tt = t + ::log2(cst);
-    if (tt > m) {
-      s = s * ::exp2(m - tt) + 1.0;
-      m = tt;
-    } else {
-      s += ::exp2(tt - m);
-    }
-  }
-  out[i] = T(m + ::log2(s));
 }
 
 // grid cost table: tab[k] = g_s[k] + log2(C1(k)) at the current X stage (-inf at 0 offset)
@@ -1875,13 +1666,14 @@ __global__ __launch_bounds__(kBlock) void k_wf_epi(const T* __restrict__ pm, con
                                                     const Ctrl* __restrict__ c, EpiArgs<T> ep) {
   if (skip_side(c, side)) return;
   const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  const EpiK<T> K = epi_consts_of<T>(c, side, ep);
   ResAcc<T> ra;
   ra.init();
   if (i < Nr) {
     // the units of the row's wave (unit k at slot k nrw + rw, row i at lane
     // i % 64); a row with no unit, or no term within the cut, gets -inf
     const int64_t rw = i / 64, nrw = (Nr + 63) / 64;
-    epi_elem<T>(i, merge_parts<T>(pm, ps, 64 * nrw, rw * 64 + i % 64, ucnt[rw]), c, side, ep, ra);
+    epi_elem<T>(i, merge_parts<T>(pm, ps, 64 * nrw, rw * 64 + i % 64, ucnt[rw]), K, ep, ra);
   }
   epi_finish<T>(ep, ra, blockIdx.x);
 }
@@ -1996,8 +1788,7 @@ void launch_ctrl_init(Ctrl* c, const Ctrl& init, hipStream_t s) {
 }
 
 template <typename T>
-void launch_bary_combine(const T* T2, int nm, int64_t size, const BaryW& log_alpha, double log_sum_alpha,
-                         const DivDev& F2, const T* logdy, T* v, T* w, T* logh, const Ctrl* c, int side,
+void launch_bary_combine(const T* T2, int nm, int64_t size, const BaryW& la, const DivDev& F2, const T* logdy, T* v, T* w, T* logh, const Ctrl* c, int side,
                          hipStream_t s) {
   if (F2.kind == 2 || F2.kind == 3) {
     const int nbp = nm * ((F2.kind == 2 || F2.has_lo) ? 2 : 1);
@@ -2005,7 +1796,7 @@ void launch_bary_combine(const T* T2, int nm, int64_t size, const BaryW& log_alp
     while (L < nbp && L < 64) L *= 2;
     const unsigned blocks = ceil_div(size * L, kBlock);
 #define UOT_BR(LL)                                                                                               \
-  hipLaunchKernelGGL((k_bary_root<T, LL>), dim3(blocks), dim3(kBlock), 0, s, T2, nm, size, log_alpha, F2, logdy, v, w, \
+  hipLaunchKernelGGL((k_bary_root<T, LL>), dim3(blocks), dim3(kBlock), 0, s, T2, nm, size, la, F2, logdy, v, w, \
                      logh, c, side)
     switch (L) {
       case 2: UOT_BR(2); break;
@@ -2018,8 +1809,7 @@ void launch_bary_combine(const T* T2, int nm, int64_t size, const BaryW& log_alp
 #undef UOT_BR
     return;
   }
-  hipLaunchKernelGGL(k_bary_combine<T>, dim3(ceil_div(size, kBlock)), dim3(kBlock), 0, s, T2, nm, size, log_alpha,
-                     log_sum_alpha, F2, logdy, v, w, logh, c, side);
+  hipLaunchKernelGGL(k_bary_combine<T>, dim3(ceil_div(size, kBlock)), dim3(kBlock), 0, s, T2, nm, size, la, F2, logdy, v, w, logh, c, side);
 }
 
 template <typename T>
@@ -2035,16 +1825,6 @@ int launch_sum_exp2(const T* a, const T* b, int64_t n, double* part, hipStream_t
   const unsigned nb = ceil_div(n, kBlock);
   hipLaunchKernelGGL(k_sum_exp2<T>, dim3(nb), dim3(kBlock), 0, s, a, b, n, part);
   return (int)nb;
-}
-
-template <typename T>
-void launch_dense_cost(int dim, const T* xr, int64_t Nr, const T* yc, const T* w, int64_t Mc, double eps, T* out,
-                       const CostArgs& cost, hipStream_t s) {
-  dim3 grid(ceil_div(Nr, kBlock));
-  if (dim == 1) hipLaunchKernelGGL((k_dense_cost<T, 1>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, eps, out, cost);
-  else if (dim == 2)
-    hipLaunchKernelGGL((k_dense_cost<T, 2>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, eps, out, cost);
-  else hipLaunchKernelGGL((k_dense_cost<T, 3>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, eps, out, cost);
 }
 
 #define UOT_INSTANTIATE(T)                                                                                         \
@@ -2071,13 +1851,11 @@ void launch_dense_cost(int dim, const T* xr, int64_t Nr, const T* yc, const T* w
                                  const EpiArgs<T>&, hipStream_t);                                                 \
   template void launch_dense_epi<T>(const T*, const T*, int, int64_t, int, const Ctrl*, const EpiArgs<T>&,       \
                                     hipStream_t);                                                                 \
-  template void launch_bary_combine<T>(const T*, int, int64_t, const BaryW&, double, const DivDev&, const T*,    \
+  template void launch_bary_combine<T>(const T*, int, int64_t, const BaryW&, const DivDev&, const T*,    \
                                        T*, T*, T*, const Ctrl*, int, hipStream_t);                               \
   template int launch_obj_side<T>(const T*, const T*, const T*, const T*, int64_t, double, const DivDev&, T*,    \
                                   double*, hipStream_t);                                                          \
-  template int launch_sum_exp2<T>(const T*, const T*, int64_t, double*, hipStream_t);                            \
-  template void launch_dense_cost<T>(int, const T*, int64_t, const T*, const T*, int64_t, double, T*,             \
-                                     const CostArgs&, hipStream_t);
+  template int launch_sum_exp2<T>(const T*, const T*, int64_t, double*, hipStream_t);
 
 UOT_INSTANTIATE(float)
 UOT_INSTANTIATE(double)
@@ -2147,6 +1925,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_lse(const BItem* __restrict__ 
   __shared__ V4 tile[kBlock];
   __shared__ int item_sh;
   const T sc = T(kLog2e / eps_of(c, side));
+  const EpiK<T> K = epi_consts_of<T>(c, side, ep);
   const int n_items = *count;
   const int32_t* __restrict__ skip = half_of(side) == 0 ? bc->stop : bc->yskip;
   while (true) {
@@ -2218,7 +1997,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_lse(const BItem* __restrict__ 
       if (vr[r]) {
         const int64_t e = rb + I.row0 + r * kBlock + threadIdx.x;
         const T S2 = acc[r].result();
-        epi_elem<T>(e, S2, c, side, ep, ra);
+        epi_elem<T>(e, S2, K, ep, ra);
         if (bal) bal_elem<T>(e, S2, c, side, ep, mb);
       }
     epi_finish<T>(ep, ra, I.part);
@@ -2329,10 +2108,7 @@ __global__ __launch_bounds__(kCompactBlock) void k_batch_compact(Ctrl* __restric
       c->active[l & 1] = B - nstop;
       c->built[par ^ 1] = rebuild ? nstop : built;
       c->iter = l + 1;
-      int64_t sn = c->iters_per_stage > 0 ? (l + 1) / c->iters_per_stage : c->n_stages;
-      if (sn > c->n_stages) sn = c->n_stages;
-      c->stage[par ^ 1] = (int)sn;
-      c->eps[par ^ 1] = c->eps_tab[sn];
+      set_slot(c, par ^ 1, slot_values(c, stage_at(c, l + 1), stage_at(c, l + 2), par));
     }
   }
   if (!rebuild) return;

@@ -41,7 +41,7 @@ template <typename T> struct EpiArgs {
   const ResPart* host_parts;
   double* host_hist;
   int host_nparts;
-  int host_pad;
+  int host_fields;   // (line passes) 0: one problem, else the partials form this many equal ranges
   // total-mass penalty (Y side): per-block log2-sum-exp partials (m, s) of
   // T + v/eps + log d, the log mass of the plan without the factor z
   T* mass_m;
@@ -189,25 +189,71 @@ void launch_mass_update(Ctrl* c, const T* mass_m, const T* mass_s, int nparts, c
                         hipStream_t s);
 constexpr int kMaxBary = 64;
 struct BaryW {
-  double v[kMaxBary];   // log alpha_k
+  double v[kMaxBary];   // log alpha_k (pointwise estimate)
   double a[kMaxBary];   // alpha_k
 };
 template <typename T>
-void launch_bary_combine(const T* T2, int nm, int64_t size, const BaryW& log_alpha, double log_sum_alpha,
-                         const DivDev& F2, const T* logdy, T* v, T* w, T* logh, const Ctrl* c, int side,
+void launch_bary_combine(const T* T2, int nm, int64_t size, const BaryW& la, const DivDev& F2, const T* logdy, T* v, T* w, T* logh, const Ctrl* c, int side,
                          hipStream_t s);
 template <typename T>
 int launch_obj_side(const T* pot, const T* S, const T* p, const T* d, int64_t n, double eps, const DivDev& F,
                     T* pi_out, double* part, hipStream_t s);
 template <typename T> int launch_sum_exp2(const T* a, const T* b, int64_t n, double* part, hipStream_t s);
+// FP64 objective (uot_objective.hip).  Grids: log2 weights pot le + log2 d
+// (pot null: 0), plus log2 of coordinate `axis` of the cell centre (-1: none,
+// -2: of its squared norm); a side's four sums from its product S; sums of
+// 2^{a + b} (per block of 256 elements)
+struct GridCells {
+  int dim;
+  int64_t n[3];
+  double h[3];
+};
 template <typename T>
-void launch_dense_cost(int dim, const T* xr, int64_t Nr, const T* yc, const T* w, int64_t Mc, double eps, T* out,
-                       const CostArgs& cost, hipStream_t s);
+void launch_obj_weight(const T* pot, const T* d, int64_t n, double le, const GridCells& g, int axis, double* out,
+                       hipStream_t s);
+template <typename T>
+void launch_obj_side64(const T* pot, const double* S, const T* p, const T* d, int64_t n, double eps, const DivDev& F,
+                       T* pi_out, double* part, hipStream_t s);
+void launch_obj_sum(const double* a, const double* b, int64_t n, double* part, hipStream_t s);
+// point clouds, one side: six sums per block of 256 rows (the side's four; with
+// `full` the transport cost and the mass of K); part: nsplit x (4 or 2) x Nr
+template <typename T>
+void launch_obj_points(bool full, int dim, const T* xr, int64_t Nr, const T* yc, const T* pot_c, const T* dc, int64_t Mc,
+                       int nsplit, double eps, const CostArgs& cost, const T* pot_r, const T* p, const T* dr,
+                       const DivDev& F, T* pi_out, double* part, double* out, hipStream_t s);
 
 void launch_probe(int which, float* out, int blocks, int iters, hipStream_t s);
 int grid_tf_parts(int n, int64_t A, int64_t B, bool strided);
 void launch_grid_tf(const float* in, int64_t A, int n, int64_t B, bool strided, bool half, double h, int side,
                     const Ctrl* c, const EpiArgs<float>& ep, hipStream_t s);
+// line passes (uot_grid_line.hip).  line_applies: they take an axis of c = h^2
+// log2(e) / eps; c_max below: the largest c of the schedule.  line_blocks: the
+// blocks over `groups` groups of `per` lines of n cells, at most max_blocks
+// where lines of 16 cells or more allow it
+bool line_applies(bool f64, double c);
+int64_t line_blocks(int n, int64_t groups, int64_t per, int max_blocks);
+// one pass over A x n x B cells with the epilogue ep
+template <typename T>
+void launch_line(const T* in, int64_t A, int n, int64_t B, double h, double c_max, int max_blocks, int side,
+                 const Ctrl* c, const EpiArgs<T>& ep, hipStream_t s);
+// F fields of R contiguous lines: pass, epilogue *ep, the next half-step's
+// pass (ep null: one raw pass), output transposed per field
+template <typename T>
+void launch_line_pair(const T* in, int64_t F, int64_t R, int n, double h, double c_max, int max_blocks, int side,
+                      const Ctrl* c, const EpiArgs<T>* ep, T* out, hipStream_t s);
+// ... with the barycentre combine over the F fields as the epilogue
+bool line_bary_fits(int64_t F, int n);
+template <typename T>
+void launch_line_bary(const T* in, int64_t F, int64_t R, int n, double h, double c_max, int side, const Ctrl* c,
+                      const EpiArgs<T>& ep, T* out, const BaryW& bw, hipStream_t s);
+// the last two axes of F fields of n0 x n1 x n2 cells, a plane per block
+bool line_plane_fits(int64_t n1, int64_t n2);
+template <typename T>
+void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1, double h2, double c1_max,
+                       double c2_max, int side, const Ctrl* c, const EpiArgs<T>* ep, T* out, hipStream_t s);
+// dst[f][b][a] = src[f][a][b], or its log (log 1: -inf where src <= 0; 2: log src)
+template <typename T>
+void launch_transpose(const T* src, T* dst, int64_t F, int64_t Na, int64_t Nb, int log, hipStream_t s);
 // direct batch product over *count items of the list (256 R rows per item),
 // pulled from *cursor (zero at launch)
 template <typename T>
