@@ -164,6 +164,7 @@ struct Plan {
   CostArgs cost{0, 0, 0.0};                  // squared Euclidean or WF with a cut locus
   bool line = false;                         // grids: line passes (uot_grid_line.hip)
   bool pair = false;                         // ... paired over the half-steps of a solve
+  bool loop = false;                         // 1-D grids: whole iterations in one block
   int np_pair_y = 0;                         // ... blocks of the paired Y epilogue
   double c_max[3] = {0, 0, 0};               // ... their c = h^2 log2(e) / eps at the schedule's smallest eps
   int parts_room = 1;                        // residual partials the workspace holds
@@ -341,12 +342,15 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
     // the line passes take every axis or none (squared Euclidean cost, the
     // default choice or grid_kernel 2): what they leave to the older passes
     // is kernels of a few cells (c above their limit), the WF cost, the
-    // direct and FP16 forms asked for by name, and 1-D grids
-    P.line = (grid_kernel == 0 || grid_kernel == 2) && g.cost == UOT_COST_SQEUCLID && g.dim >= 2 && eps_min > 0;
+    // direct and FP16 forms asked for by name, and long 1-D grids
+    P.line = (grid_kernel == 0 || grid_kernel == 2) && g.cost == UOT_COST_SQEUCLID && eps_min > 0;
     for (int k = 0; k < g.dim; ++k) {
       P.c_max[k] = eps_min > 0 ? g.h[k] * g.h[k] * kLog2e / eps_min : INFINITY;
       P.line = P.line && line_applies(dtype == UOT_F64, P.c_max[k]);
     }
+    // (1-D: one block, for a whole solve of a short line)
+    P.loop = P.line && g.dim == 1 && nb == 1 && g.n[0] <= line_loop_max(dtype == UOT_F64);
+    P.line = P.line && g.dim >= 2;
   } else {
     return fail(UOT_E_INVALID, "unknown geometry kind");
   }
@@ -830,8 +834,8 @@ struct GraphCache {
   }
 };
 
-// drive iterations until the device sets stop; `iteration(par)` enqueues one
-// iteration of parity par.  With a second phase (`iteration2`, non-null
+// drive iterations until the device sets stop; `iteration(k)` enqueues iteration
+// k of a chunk (parity k & 1).  With a second phase (`iteration2`, non-null
 // `final_tol`), a stop with status 0 ends phase one (whose control block
 // tolerance was looser): the solve resumes at `final_tol` with iteration2.
 template <typename F, typename F2 = std::remove_reference_t<F>>
@@ -851,7 +855,7 @@ int run_loop(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration, uot
   auto capture = [&](auto& it) -> int {
     if (!pr->use_graph || timing) return UOT_OK;
     HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < chunk; ++k) it(k & 1);
+    for (int k = 0; k < chunk; ++k) it(k);
     HIP_TRY(hipStreamEndCapture(s, &graph));
     HIP_TRY(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
     return UOT_OK;
@@ -878,8 +882,8 @@ int run_loop(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration, uot
       if (hipGraphLaunch(exec, s) != hipSuccess) { rc = fail(UOT_E_HIP, "hipGraphLaunch failed"); break; }
     } else {
       for (int k = 0; k < chunk; ++k) {
-        if (second) (*iteration2)(k & 1);
-        else iteration(k & 1);
+        if (second) (*iteration2)(k);
+        else iteration(k);
       }
     }
     launched += chunk;
@@ -948,7 +952,7 @@ int run_async(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration) {
   hipGraphExec_t exec = nullptr;
   if (pr->use_graph) {
     HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
-    for (int k = 0; k < chunk; ++k) iteration(k & 1);
+    for (int k = 0; k < chunk; ++k) iteration(k);
     HIP_TRY(hipStreamEndCapture(s, &graph));
     if (hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) {
       (void)hipGraphDestroy(graph);
@@ -963,7 +967,7 @@ int run_async(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration) {
     if (exec) {
       HIP_TRY(hipGraphLaunch(exec, s));
     } else {
-      for (int j = 0; j < chunk; ++j) iteration(j & 1);
+      for (int j = 0; j < chunk; ++j) iteration(j);
     }
   }
   HIP_TRY(hipEventRecord(ctx->ev_t1, s));
@@ -1162,7 +1166,19 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
   }
   if (P.pair) pair_start<T>(P, B, s);
   auto iteration_with = [&](const Plan& PP) {
-    return [&, pp = &PP](int par) {
+    return [&, pp = &PP](int k) {
+      const int par = k & 1;
+      if (pp->loop && !mass) {
+        // (one launch for the chunk)
+        if (k == 0)
+          timed(0, [&] {
+            launch_line_loop<T>((int)pp->n[0], pp->h[0], pp->c_max[0], B.ctrl,
+                                prox_epi<T>(uo, nullptr, B.logp, B.logdx, nullptr, B.parts, P.N, pbs.F1),
+                                prox_epi<T>(vo, nullptr, B.logq, B.logdy, nullptr, nullptr, P.M, pbs.F2), pr->res_hist,
+                                even_chunk(pr->check_every), s);
+          });
+        return;
+      }
       if (pp->pair) {
         pair_x<T>(*pp, B, par, prox_epi<T>(uo, nullptr, B.logp, B.logdx, nullptr, B.parts, P.N, pbs.F1), s);
         EpiArgs<T> ep = prox_epi<T>(vo, nullptr, B.logq, B.logdy, nullptr, nullptr, P.M, pbs.F2);
@@ -1214,6 +1230,10 @@ int half_step_t(uot_ctx* ctx, const uot_problem* pb, double eps, int side, const
   Plan P;
   int rc = make_plan(P, pb->dtype, pb->geom, 1, 1, 0, eps);
   if (rc) return rc;
+  if (P.loop) {   // one line: one block
+    P.line = true;
+    P.nparts_x = P.nparts_y = 1;
+  }
   if ((rc = check_ws(P, ws, wsb))) return rc;
   if (!pot_in || !pot_io) return fail(UOT_E_INVALID, "pot_in and pot_io are required");
   if (!(eps > 0)) return fail(UOT_E_INVALID, "eps must be > 0");
@@ -1328,7 +1348,8 @@ int objective_t(uot_ctx* ctx, const uot_problem* pb, double eps, const T* u, con
         int64_t A = 1, Bn = 1;
         for (int j = 0; j < k; ++j) A *= P.n[j];
         for (int j = k + 1; j < P.dim; ++j) Bn *= P.n[j];
-        launch_line<double>(src, A, (int)P.n[k], Bn, P.h[k], P.h[k] * P.h[k] * le, 1 << 30, 0, B.ctrl, raw, s);
+        launch_line<double>(src, A, (int)P.n[k], Bn, P.h[k], P.h[k] * P.h[k] * le, 1 << 30, 0, B.ctrl, raw, s,
+                            sizeof(T) == 4);   // (the kernel of a solve on FP32 data)
         src = raw.out;
       }
     };
@@ -1461,7 +1482,8 @@ int bary_t(uot_ctx* ctx, const uot_bary_problem* pb, const uot_params* pr, T* u,
   host.hist = pr->res_hist;
   if (pair) pair_start<T>(P, B, s);
   auto iteration_with = [&](const Plan& PP) {
-    return [&, pp = &PP](int par) {
+    return [&, pp = &PP](int k) {
+      const int par = k & 1;
       if (pair) {
         pair_x<T>(*pp, B, par, prox_epi<T>(B.t3, nullptr, B.logp, B.logdx, nullptr, B.parts, size, pb->F1), s);
         const EpiArgs<T> ep = with_host<T>(prox_epi<T>(v, nullptr, nullptr, B.logdy, logh, nullptr, size, pb->F2), host);
@@ -1503,6 +1525,7 @@ int map_t(uot_ctx* ctx, const uot_problem* pb, double eps, const T* v, T* Tout, 
   Plan P;
   int rc = make_plan(P, pb->dtype, pb->geom, 1, 1, 0, eps);
   if (rc) return rc;
+  P.line = P.line || P.loop;
   if ((rc = check_ws(P, ws, wsb))) return rc;
   if (!v || !Tout) return fail(UOT_E_INVALID, "v and T are required");
   if (!(eps > 0 && std::isfinite(eps))) return fail(UOT_E_INVALID, "eps must be finite and > 0");
@@ -1617,7 +1640,8 @@ int flow_t(uot_ctx* ctx, const uot_flow_problem* fp, const FlowDivs& fd, const u
   pb.F2 = fd.F2;
   const DivDev Fg = to_dev(fd.F2);
   const bool growth = fp->kind == UOT_FLOW_GROWTH;
-  auto iteration = [&](int par) {
+  auto iteration = [&](int k) {
+    const int par = k & 1;
     if (S == 1) {
       half_step<T>(P, pb, 0 | par << 1, B, u, nullptr, true, s);
       timed(2, [&] { launch_control(B.ctrl, B.parts, P.nparts_x, pr->res_hist, s, 0, par); });

@@ -277,11 +277,13 @@ template <typename T> __device__ __forceinline__ T* line_lds() {
 // ---------------------------------------------------------------------------
 // One pass along the axis of cells (a, i, b), element a n B + i B + b, with the
 // epilogue ep (raw output or proxdiv); a block takes L = 2^lsh lines: L
-// consecutive b of one a (B > 1), or L consecutive a (B == 1).
+// consecutive b of one a (B > 1), or L consecutive a (B == 1).  c32: c rounded to
+// FP32, as the passes on FP32 data round it.
 // ---------------------------------------------------------------------------
 template <typename T, int TS, int NT, int EPT>
 __global__ __launch_bounds__(NT) void k_line(const T* __restrict__ in, int64_t A, int64_t B, int lsh, LineShape S,
-                                             double h2, int side, const Ctrl* __restrict__ c, EpiArgs<T> ep) {
+                                             double h2, int side, const Ctrl* __restrict__ c, EpiArgs<T> ep,
+                                             int c32) {
   using Op = LineOp<T, TS>;
   T* const buf = line_lds<T>();
   T* const pm = buf + S.nl * S.ldl;
@@ -329,7 +331,7 @@ __global__ __launch_bounds__(NT) void k_line(const T* __restrict__ in, int64_t A
   for (int k = 0; k < EPT; ++k) xe[k] = epi_load<T>(el[k], ep);
   __builtin_amdgcn_sched_barrier(0);
   Op op;
-  op.init(T(h2 * le));
+  op.init(c32 ? T(float(h2 * le)) : T(h2 * le));
   const EpiK<T> K = epi_consts_of<T>(c, side, ep);
   __builtin_amdgcn_sched_barrier(0);
   // (keeps the loads ahead of the branch)
@@ -645,6 +647,120 @@ __global__ __launch_bounds__(NT) void k_plane_pair(const T* __restrict__ in, int
   if constexpr (FULL) epi_finish<T, NT>(ep, ra, (int)grp);
 }
 
+// ---------------------------------------------------------------------------
+// Whole iterations of one problem on a 1-D grid, in one block: both half-steps
+// run along the only axis, so the weights stay in LDS and the potentials in
+// registers, and `chunk` iterations are one launch.  The block's first wave
+// also takes the control step's decision.  exy[0], exy[1]: the X and Y
+// epilogues (potentials, log densities, log weights, penalties).
+// It is bound by the latency of a pass (two per iteration): about 2000 cycles
+// in FP32 at 256 cells, one 16-column group whose segments go over 8 waves.
+// ---------------------------------------------------------------------------
+template <typename T, int TS, int NT, int EPT>
+__global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape S, double h2, Ctrl* c, EpiArgs<T> ex,
+                                                                      EpiArgs<T> ey, double* __restrict__ hist,
+                                                                      int chunk) {
+  using Op = LineOp<T, TS>;
+  if (c->stop) return;
+  __shared__ ResPart tot;
+  __shared__ int stopped;   // 0 running, else 1 + the index of the status below
+  T* const buf = line_lds<T>();
+  T* const pm = buf + S.ldl;
+  T* const ps = pm + S.ksn * S.ldp;
+  const int n = S.n;
+  EpiIn<T> xe[EPT], ye[EPT];
+  T w[EPT];
+  bool ok[EPT];
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int i = threadIdx.x + k * NT;
+    ok[k] = i < n;
+    xe[k] = epi_load<T>(ok[k] ? i : 0, ex);
+    ye[k] = epi_load<T>(ok[k] ? i : 0, ey);
+  }
+  int64_t l = c->iter;
+  const int64_t max_iter = c->max_iter;
+  const int n_stages = c->n_stages;
+  const double tol = c->tol;
+  int sn = stage_at(c, l);
+  double eps = c->eps_tab[sn], le = kLog2e / eps;
+  EpiK<T> KX = epi_consts<T>(eps, le, le, ctrl_coef(c, 0, eps), 0.0), KY;
+  Op op;
+  op.init(T(h2 * le));
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int i = threadIdx.x + k * NT;
+    w[k] = ye[k].uo == Num<T>::pinf() ? Num<T>::ninf()
+                                      : epi_weight<T>(ye[k].uo, KX.ke, KX.kel, ye[k].ld * T(kLog2e));
+    if (ok[k]) buf[i] = Op::shifted(w[k], i, op.c);
+  }
+  line_pad<T, TS, NT>(S, buf);
+  if (threadIdx.x == 0) stopped = 0;
+  double r = 0.0, du = 0.0;
+  for (int it = 0; it < chunk; ++it) {
+    __syncthreads();
+    line_pass<T, TS, NT>(op, S, buf, pm, ps);
+    const int sn1 = stage_at(c, l + 1);
+    const double eps1 = sn1 == sn ? eps : c->eps_tab[sn1], le1 = sn1 == sn ? le : kLog2e / eps1;
+    if (it == 0 || sn1 != sn || KY.ke != KX.ke)
+      KY = epi_consts<T>(eps, le, le1, ctrl_coef(c, 1, eps), 0.0);
+    __syncthreads();
+    ResAcc<T> ra;
+    ra.init();
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      const int i = threadIdx.x + k * NT;
+      if (ok[k]) {
+        const T wu = epi_core<T>(i, line_result<T>(S, pm, ps, 0, i), xe[k], KX, ex, ra);
+        buf[i] = Op::shifted(wu, i, op.c);
+      }
+    }
+    block_res_reduce<T, NT>(ra.m, ra.den, ra.num, ra.du, &tot);   // (holds a barrier: the weights are in place)
+    if (threadIdx.x == 0) {
+      r = res_ratio(double(tot.num), double(tot.den));
+      du = double(tot.du);
+      if (hist) hist[l] = r;
+      // (the first residual compares with the initial u and is not used to stop)
+      if (r != r) stopped = 1;
+      else if (sn >= n_stages && r <= tol && l >= 1) stopped = 2;
+      else if (l + 1 >= max_iter) stopped = 3;
+    }
+    line_pass<T, TS, NT>(op, S, buf, pm, ps);
+    __syncthreads();
+    ++l;
+    if (sn1 != sn) op.init(T(h2 * le1));
+    ResAcc<T> none;
+    none.init();
+#pragma unroll
+    for (int k = 0; k < EPT; ++k) {
+      const int i = threadIdx.x + k * NT;
+      if (ok[k]) {
+        const T wv = epi_core<T>(i, line_result<T>(S, pm, ps, 0, i), ye[k], KY, ey, none);
+        buf[i] = Op::shifted(wv, i, op.c);
+      }
+    }
+    if (sn1 != sn) {
+      sn = sn1;
+      eps = eps1;
+      le = le1;
+      KX = epi_consts<T>(eps, le, le, ctrl_coef(c, 0, eps), 0.0);
+    }
+    if (stopped) break;
+  }
+  if (threadIdx.x == 0) {
+    c->iter = l;
+    c->res = r;
+    c->du = du;
+    const int p = (int)(l & 1);
+    set_slot(c, p, slot_values(c, stage_at(c, l), stage_at(c, l + 1), -1));
+    if (stopped) {
+      c->status = stopped == 1 ? -3 : stopped - 2;
+      c->stop = 1;
+      c->skip[p] = 1;
+    }
+  }
+}
+
 // dst[f][b][a] = src[f][a][b], or its log (log 1: densities, -inf where there is
 // none; 2: weights), a block per 16 x 16 tile; grid = (ceil(Nb / 16), ceil(Na / 16), fields)
 template <typename T>
@@ -766,7 +882,7 @@ static int line_threads(int tot, int64_t blocks) {
 
 template <typename T>
 void launch_line(const T* in, int64_t A, int n, int64_t B, double h, double c_max, int max_blocks, int side,
-                 const Ctrl* c, const EpiArgs<T>& ep, hipStream_t s) {
+                 const Ctrl* c, const EpiArgs<T>& ep, hipStream_t s, bool c32) {
   const int lsh = B > 1 ? line_lsh(n, A, B, max_blocks) : line_lsh(n, 1, A, max_blocks);
   const unsigned blocks = (unsigned)(B > 1 ? line_blocks(n, A, B, max_blocks) : line_blocks(n, 1, A, max_blocks));
   const int tot = n << lsh;
@@ -779,7 +895,7 @@ void launch_line(const T* in, int64_t A, int n, int64_t B, double h, double c_ma
   do {                                                                                                            \
     line_big_lds(k_line<T, TS, NT, EPT>, lds);                                                                    \
     hipLaunchKernelGGL((k_line<T, TS, NT, EPT>), dim3(blocks), dim3(NT), lds, s, in, A, B, lsh, S, h * h, side, c, \
-                       ep);                                                                                       \
+                       ep, c32 ? 1 : 0);                                                                                       \
   } while (0)
   UOT_LINE_TS(UOT_LN)
 #undef UOT_LN
@@ -873,6 +989,30 @@ void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1
 #undef UOT_LN
 }
 
+// Longest line the loop kernel is used for: one compute unit does what the
+// chip shares in the launches it replaces, whose latency hardly depends on n.
+// Measured (us per iteration, this kernel / the launches): FP32 64 cells 3.4 /
+// 11.9, 256 4.3 / 15.5, 512 7.2 / 21.2, 768 17.3 / 22.4, 1024 26.3 / 22.7; FP64
+// 64 5.3 / 15.5, 256 9.2 / 23.9, 512 22.2 / 31.2, 768 50.2 / 31.9.
+int line_loop_max(bool f64) { return f64 ? 512 : 768; }
+
+template <typename T>
+void launch_line_loop(int n, double h, double c_max, Ctrl* c, const EpiArgs<T>& ex, const EpiArgs<T>& ey, double* hist,
+                      int chunk, hipStream_t s) {
+  const int tot = n, nthr = line_threads(tot, 1);
+  LineShape S;
+  int ts;
+  line_shape(1, n, nthr, line_ts<T>(c_max), sizeof(T) == 4 ? 8 : 16, S, ts);
+  const size_t lds = line_lds_bytes<T>(S);
+#define UOT_LN(TS, NT, EPT)                                                                                         \
+  do {                                                                                                              \
+    if constexpr (NT != 256)                                                                                        \
+      hipLaunchKernelGGL((k_line_loop<T, TS, NT, EPT>), dim3(1), dim3(NT), lds, s, S, h * h, c, ex, ey, hist, chunk); \
+  } while (0)
+  UOT_LINE_TS(UOT_LN)
+#undef UOT_LN
+}
+
 template <typename T>
 void launch_transpose(const T* src, T* dst, int64_t F, int64_t Na, int64_t Nb, int log, hipStream_t s) {
   for (int64_t f = 0; f < F; f += 65535) {
@@ -884,13 +1024,15 @@ void launch_transpose(const T* src, T* dst, int64_t F, int64_t Na, int64_t Nb, i
 
 #define UOT_LINE_INST(T)                                                                                              \
   template void launch_line<T>(const T*, int64_t, int, int64_t, double, double, int, int, const Ctrl*,                \
-                               const EpiArgs<T>&, hipStream_t);                                                       \
+                               const EpiArgs<T>&, hipStream_t, bool);                                                 \
   template void launch_line_pair<T>(const T*, int64_t, int64_t, int, double, double, int, int, const Ctrl*,           \
                                     const EpiArgs<T>*, T*, hipStream_t);                                              \
   template void launch_line_bary<T>(const T*, int64_t, int64_t, int, double, double, int, const Ctrl*,                \
                                     const EpiArgs<T>&, T*, const BaryW&, hipStream_t);                        \
   template void launch_plane_pair<T>(const T*, int64_t, int, int, int, double, double, double, double, int,           \
                                      const Ctrl*, const EpiArgs<T>*, T*, hipStream_t);                                \
+  template void launch_line_loop<T>(int, double, double, Ctrl*, const EpiArgs<T>&, const EpiArgs<T>&, double*, int,    \
+                                    hipStream_t);                                                                     \
   template void launch_transpose<T>(const T*, T*, int64_t, int64_t, int64_t, int, hipStream_t);
 UOT_LINE_INST(float)
 UOT_LINE_INST(double)

@@ -232,10 +232,10 @@ void launch_grid_tf(const float* in, int64_t A, int n, int64_t B, bool strided, 
 // where lines of 16 cells or more allow it
 bool line_applies(bool f64, double c);
 int64_t line_blocks(int n, int64_t groups, int64_t per, int max_blocks);
-// one pass over A x n x B cells with the epilogue ep
+// one pass over A x n x B cells with the epilogue ep (c32: c rounded to FP32)
 template <typename T>
 void launch_line(const T* in, int64_t A, int n, int64_t B, double h, double c_max, int max_blocks, int side,
-                 const Ctrl* c, const EpiArgs<T>& ep, hipStream_t s);
+                 const Ctrl* c, const EpiArgs<T>& ep, hipStream_t s, bool c32 = false);
 // F fields of R contiguous lines: pass, epilogue *ep, the next half-step's
 // pass (ep null: one raw pass), output transposed per field
 template <typename T>
@@ -251,6 +251,11 @@ bool line_plane_fits(int64_t n1, int64_t n2);
 template <typename T>
 void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1, double h2, double c1_max,
                        double c2_max, int side, const Ctrl* c, const EpiArgs<T>* ep, T* out, hipStream_t s);
+// `chunk` iterations of a problem on one 1-D grid of n <= line_loop_max cells
+int line_loop_max(bool f64);
+template <typename T>
+void launch_line_loop(int n, double h, double c_max, Ctrl* c, const EpiArgs<T>& ex, const EpiArgs<T>& ey, double* hist,
+                      int chunk, hipStream_t s);
 // dst[f][b][a] = src[f][a][b], or its log (log 1: -inf where src <= 0; 2: log src)
 template <typename T>
 void launch_transpose(const T* src, T* dst, int64_t F, int64_t Na, int64_t Nb, int log, hipStream_t s);

@@ -84,11 +84,16 @@ template <int Q> __device__ __forceinline__ void block_sums(const double (&v)[Q]
   }
 }
 
+// log2 of a reference weight, rounded as a solve on T data rounds it (see
+// as_data)
+template <typename T> __device__ __forceinline__ double obj_logd(T d) {
+  return double(Num<T>::log(d) * T(kLog2e));
+}
 // log2 weight of a potential, pot / eps + log d; a potential of +inf (left by
 // a vanishing product) carries no mass
 template <typename T> __device__ __forceinline__ double obj_weight(const T* pot, const T* d, int64_t i, double le) {
   const double p = pot ? double(pot[i]) : 0.0;
-  return p == __builtin_inf() ? -__builtin_inf() : p * le + ::log2(double(d[i]));
+  return p == __builtin_inf() ? -__builtin_inf() : p * le + obj_logd<T>(d[i]);
 }
 
 }  // namespace
@@ -149,7 +154,7 @@ __global__ __launch_bounds__(kB) void k_obj_sum(const double* __restrict__ a, co
 template <typename T, int DIM, int COST, bool FULL>
 __global__ __launch_bounds__(kB) void k_obj_points(const T* __restrict__ xr, int64_t Nr, const T* __restrict__ yc,
                                                    const T* __restrict__ pot, const T* __restrict__ d, int64_t Mc,
-                                                   int64_t cps, double le, double a2, double cut2,
+                                                   int64_t cps, double le, double kc, double a2, double cut2,
                                                    double* __restrict__ part) {
   constexpr int C = 8, Q = FULL ? 4 : 2;
   __shared__ double ty[DIM][kB], tw[kB], tk[FULL ? kB : 1];
@@ -165,7 +170,7 @@ __global__ __launch_bounds__(kB) void k_obj_points(const T* __restrict__ xr, int
 #pragma unroll
     for (int k = 0; k < DIM; ++k) ty[k][threadIdx.x] = j < ce ? double(yc[k * Mc + j]) : 0.0;
     tw[threadIdx.x] = j < ce ? obj_weight<T>(pot, d, j, le) : -__builtin_inf();
-    if (FULL) tk[threadIdx.x] = j < ce ? ::log2(double(d[j])) : -__builtin_inf();
+    if (FULL) tk[threadIdx.x] = j < ce ? obj_logd<T>(d[j]) : -__builtin_inf();
     __syncthreads();
     const int cnt = ce - c0 < kB ? (int)(ce - c0) : kB;
     for (int jj = 0; jj < cnt; jj += C) {   // (columns past the end carry no weight)
@@ -185,10 +190,10 @@ __global__ __launch_bounds__(kB) void k_obj_points(const T* __restrict__ xr, int
           const bool in = d2 < cut2 && cv > 0.0;
           const double lc = in ? ::log2(cv) : 0.0;
           cst[k] = -2.0 * kLn2 * lc;
-          g = in ? 2.0 * kLn2 * le * lc : -__builtin_inf();
+          g = in ? kc * lc : -__builtin_inf();
         } else {
           cst[k] = d2;
-          g = -le * d2;
+          g = -kc * d2;
         }
         t[k] = tw[jj + k] + g;
         cm = __builtin_fmax(cm, t[k]);
@@ -253,6 +258,12 @@ __global__ __launch_bounds__(kB) void k_obj_points_finish(const double* __restri
   block_sums<6>(a, out + 6 * (int64_t)blockIdx.x);
 }
 
+// A constant of the kernel, rounded as the products of a solve on T data round
+// it (log reference weights likewise): the potentials belong to the kernel they
+// were computed with, and at another one, 2^-24 away in its exponents, the
+// plan's mass is off by about 1e-6, more than by anything else.
+template <typename T> static double as_data(double k) { return double(T(k)); }
+
 static unsigned obj_blocks(int64_t n) { return (unsigned)((n + kB - 1) / kB); }
 
 template <typename T>
@@ -274,9 +285,11 @@ static void obj_points_t(int dim, const T* xr, int64_t Nr, const T* yc, const T*
                          double le, const CostArgs& cost, double* part, hipStream_t s) {
   const int64_t cps = ((Mc + nsplit - 1) / nsplit + 7) / 8 * 8;
   const dim3 grid(obj_blocks(Nr), (unsigned)nsplit);
-  const double a2 = cost.kind == 1 ? 0.25 * M_PI * M_PI / (cost.cut * cost.cut) : 0.0, cut2 = cost.cut * cost.cut;
+  const double a2 = as_data<T>(cost.kind == 1 ? 0.25 * M_PI * M_PI / (cost.cut * cost.cut) : 0.0);
+  const double cut2 = as_data<T>(cost.cut * cost.cut);
+  const double kc = as_data<T>(cost.kind == 1 ? 2.0 * kLn2 * le : le);
 #define UOT_OP(D, C) \
-  hipLaunchKernelGGL((k_obj_points<T, D, C, FULL>), grid, dim3(kB), 0, s, xr, Nr, yc, pot, d, Mc, cps, le, a2, cut2, part)
+  hipLaunchKernelGGL((k_obj_points<T, D, C, FULL>), grid, dim3(kB), 0, s, xr, Nr, yc, pot, d, Mc, cps, le, kc, a2, cut2, part)
   if (cost.kind == 1) {
     if (dim == 1) UOT_OP(1, 1);
     else if (dim == 2) UOT_OP(2, 1);
