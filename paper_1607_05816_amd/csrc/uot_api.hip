@@ -565,7 +565,7 @@ void line_axis(const Plan& P, int axis, const T* w, int side, Ctrl* c, const Epi
 // (direct passes) or the tile-factored MFMA pass where the plan selects it
 template <typename T>
 void contig_pass(const Plan& P, int axis, const T* w, int64_t A, T* const* tabs, int side, Ctrl* c,
-                 const EpiArgs<T>& ep, hipStream_t s) {
+                 const EpiArgs<T>& ep, hipStream_t s, const CtlHost* host = nullptr) {
   if constexpr (std::is_same<T, float>::value) {
     if (use_tf(P, axis)) {
       timed(0, [&] { launch_grid_tf(w, A, (int)P.n[axis], 1, false, P.tf16_axis[axis], P.h[axis], side, c, ep, s); });
@@ -577,7 +577,8 @@ void contig_pass(const Plan& P, int axis, const T* w, int64_t A, T* const* tabs,
     T* pm = static_cast<T*>(P.split_pm);
     T* ps = static_cast<T*>(P.split_ps);
     timed(0, [&] {
-      launch_grid_contig_split<T>(w, A, (int)P.n[axis], tabs[axis], side, c, P.band[axis], P.split1d, pm, ps, s);
+      launch_grid_contig_split<T>(w, A, (int)P.n[axis], tabs[axis], side, c, P.band[axis], P.split1d, pm, ps,
+                                  host ? *host : CtlHost{}, s);
     });
     timed(1, [&] { launch_dense_epi<T>(pm, ps, P.split1d, A * P.n[axis], side, c, ep, s); });
     return;
@@ -596,15 +597,6 @@ void strided_pass(const Plan& P, int axis, const T* w, int64_t A, int64_t B, T* 
   }
   timed(1, [&] { launch_grid_strided<T>(w, A, (int)P.n[axis], B, tabs[axis], side, c, ep, s); });
 }
-
-// control step hosted by the first pass of a chain (see k_control)
-struct CtlHost {
-  Ctrl* c = nullptr;
-  const ResPart* parts = nullptr;
-  int nparts = 0;
-  double* hist = nullptr;
-  int nfields = 0;
-};
 
 template <typename T>
 void grid_chain(const Plan& P, const T* w, T* const* tabs, int side, Ctrl* c, const EpiArgs<T>& ep, T* tmp1,
@@ -633,7 +625,7 @@ void grid_chain(const Plan& P, const T* w, T* const* tabs, int side, Ctrl* c, co
     first.host_hist = host->hist;
   }
   if (P.dim == 1) {
-    contig_pass<T>(P, 0, w, nb, tabs, side, c, ep, s);
+    contig_pass<T>(P, 0, w, nb, tabs, side, c, ep, s, host);
   } else if (P.dim == 2) {
     contig_pass<T>(P, 1, w, nb * P.n[0], tabs, side, c, first, s);
     strided_pass<T>(P, 0, tmp1, nb, P.n[1], tabs, side, c, ep, s);
@@ -726,7 +718,8 @@ MfSkip mf_skip(Ctrl* c, bool count) {
 // dense point-cloud product for one side; returns the residual partial count
 template <typename T>
 void dense_half(const Plan& P, const uot_geom& g, int side, const T* w_cols, Bufs<T>& B, Ctrl* c,
-                const EpiArgs<T>& ep, hipStream_t s) {
+                const EpiArgs<T>& ep, hipStream_t s, const CtlHost* hosted = nullptr) {
+  const CtlHost host = hosted ? *hosted : CtlHost{};
   const int half = side & 1;
   const T* rows = static_cast<const T*>(half == 0 ? g.x : g.y);
   const T* cols = static_cast<const T*>(half == 0 ? g.y : g.x);
@@ -735,22 +728,23 @@ void dense_half(const Plan& P, const uot_geom& g, int side, const T* w_cols, Buf
   timed(0, [&] {
     if constexpr (std::is_same<T, float>::value) {
       if (P.dense_tf) {
-        launch_dense_tf(P.dim, rows, Nr, cols, w_cols, Mc, P.splits[half], P.cps[half], B.pm, B.ps, side, c, s);
+        launch_dense_tf(P.dim, rows, Nr, cols, w_cols, Mc, P.splits[half], P.cps[half], B.pm, B.ps, side, c, host,
+                        s);
         return;
       }
       if (P.dense_mf) {
         launch_dense_mf(P.dim, P.mf_groups, P.mf_split, rows, Nr, cols, w_cols, Mc, P.splits[half], P.cps[half], B.pm, B.ps,
-                        B.pw + half * P.np_pw, side, c, mf_skip(c, true), s);
+                        B.pw + half * P.np_pw, side, c, mf_skip(c, true), host, s);
         return;
       }
     }
     if (P.wfl) {
       launch_wf_lse<T>(P.dim, rows, Nr, cols, w_cols, Mc, P.cost.cut, B.wfl[half], P.wf_umax[half], B.wfpm, B.wfps,
-                       side, c, s);
+                       side, c, host, s);
       return;
     }
     launch_dense_lse<T>(P.dim, P.R[half], rows, Nr, cols, w_cols, Mc, P.splits[half], P.cps[half], B.pm, B.ps, side,
-                        c, P.cost, s);
+                        c, P.cost, host, s);
   });
   timed(1, [&] {
     if (P.wfl) launch_wf_epi<T>(B.wfpm, B.wfps, B.wfl[half], Nr, Mc, side, c, ep, s);
@@ -774,6 +768,13 @@ EpiArgs<T> prox_epi(T* pot, T* wnext, const T* logp, const T* logd, T* lse_out, 
   return ep;
 }
 
+// whether the first launch of a half-step (one problem) has no epilogue: a
+// product of point clouds, a slice of a long line, the first pass over 2 or 3 axes
+bool hosts_control(const Plan& P) {
+  if (P.geom == UOT_GEOM_POINTS) return true;
+  return !P.line && (P.dim >= 2 || (P.split1d > 1 && !P.loop && !use_tf(P, 0)));
+}
+
 // one half-step (X: side 0 reads wv, writes u / wu; Y: side 1 reads wu, writes
 // v / wv); bit 1 of side is the parity of the iteration
 template <typename T>
@@ -790,7 +791,7 @@ void half_step(const Plan& P, const uot_problem& pb, int side, Bufs<T>& B, T* po
       ep.mass_s = B.mass_s;
     }
     if (P.geom == UOT_GEOM_GRID) grid_chain<T>(P, B.wu, B.gtab, side, B.ctrl, ep, B.t1, B.t2, s, host);
-    else dense_half<T>(P, pb.geom, side, B.wu, B, B.ctrl, ep, s);
+    else dense_half<T>(P, pb.geom, side, B.wu, B, B.ctrl, ep, s, host);
   }
 }
 
@@ -1061,7 +1062,7 @@ int tune_dense_mf(uot_ctx* ctx, Plan& P, const uot_geom& g, Bufs<T>& B, hipStrea
         last_sp = P.splits[half];
         auto launch = [&] {
           launch_dense_mf(P.dim, P.mf_groups, P.mf_split, rows, Nr, cols, wc, Mc, P.splits[half], P.cps[half], B.pm,
-                          B.ps, pw, half, B.ctrl, mf_skip(B.ctrl, false), s);
+                          B.ps, pw, half, B.ctrl, mf_skip(B.ctrl, false), CtlHost{}, s);
         };
         HIP_TRY(hipMemsetAsync(pw, 0xFF, sizeof(float) * P.np_pw, s));
         launch();
@@ -1152,11 +1153,11 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
   Plan P2 = P;
   for (int k = 0; k < 3; ++k) P2.tf16_axis[k] = false;
   const int nfields = nb > 1 ? nb : 0;
-  // a single problem on a grid of 2 or 3 axes: the first Y pass (no
-  // epilogue) hosts the control step; otherwise it is its own launch
+  // the first launch of the Y half-step hosts the control step where it has no
+  // epilogue (paired passes do for batches of fields too); otherwise the step is
+  // its own launch
   CtlHost host;
-  // (paired passes host it for batches of fields too)
-  const bool hosted = P.pair || (nfields == 0 && P.geom == UOT_GEOM_GRID && P.dim >= 2 && !P.line);
+  const bool hosted = P.pair || (nfields == 0 && hosts_control(P));
   if (hosted) {
     host.nfields = nfields;
     host.c = B.ctrl;
@@ -1640,22 +1641,28 @@ int flow_t(uot_ctx* ctx, const uot_flow_problem* fp, const FlowDivs& fd, const u
   pb.F2 = fd.F2;
   const DivDev Fg = to_dev(fd.F2);
   const bool growth = fp->kind == UOT_FLOW_GROWTH;
+  CtlHost host;
+  host.c = B.ctrl;
+  host.parts = B.parts;
+  host.nparts = P.nparts_x;
+  host.hist = pr->res_hist;
+  const CtlHost* const hosted = hosts_control(P) ? &host : nullptr;
   auto iteration = [&](int k) {
     const int par = k & 1;
     if (S == 1) {
       half_step<T>(P, pb, 0 | par << 1, B, u, nullptr, true, s);
-      timed(2, [&] { launch_control(B.ctrl, B.parts, P.nparts_x, pr->res_hist, s, 0, par); });
-      half_step<T>(P, pb, 1 | par << 1, B, v, nullptr, false, s);
+      if (!hosted) timed(2, [&] { launch_control(B.ctrl, B.parts, P.nparts_x, pr->res_hist, s, 0, par); });
+      half_step<T>(P, pb, 1 | par << 1, B, v, nullptr, false, s, hosted);
     } else {
       // several species: KL(. | p_k) on each first marginal, the joint growth
       // proxdiv on the sum of the second marginals
       EpiArgs<T> ep = prox_epi<T>(u, B.wu, B.logp, B.logdx, nullptr, B.parts, N, fd.F1);
       grid_chain<T>(P, B.wv, B.gtab, 0 | par << 1, B.ctrl, ep, B.t1, B.t2, s);
-      timed(2, [&] { launch_control(B.ctrl, B.parts, P.nparts_x, pr->res_hist, s, 0, par); });
+      if (!hosted) timed(2, [&] { launch_control(B.ctrl, B.parts, P.nparts_x, pr->res_hist, s, 0, par); });
       EpiArgs<T> raw{};
       raw.mode = EPI_RAW;
       raw.out = B.t3;
-      grid_chain<T>(P, B.wu, B.gtab, 1 | par << 1, B.ctrl, raw, B.t1, B.t2, s);
+      grid_chain<T>(P, B.wu, B.gtab, 1 | par << 1, B.ctrl, raw, B.t1, B.t2, s, hosted);
       launch_growth_combine<T>(B.t3, S, N, Fg, B.logq, B.logdy, v, B.wv, B.ctrl, 1 | par << 1, s);
     }
   };
@@ -1772,7 +1779,8 @@ int time_half_step_t(uot_ctx* ctx, const uot_problem* pb, int nb, double eps, co
     ks.push_back([&] {
       if constexpr (std::is_same<T, float>::value) {
         if (P.dense_tf) {
-          launch_dense_tf(P.dim, rows, P.N, cols, B.wv, P.M, P.splits[0], P.cps[0], B.pm, B.ps, 0, B.ctrl, s);
+          launch_dense_tf(P.dim, rows, P.N, cols, B.wv, P.M, P.splits[0], P.cps[0], B.pm, B.ps, 0, B.ctrl,
+                          CtlHost{}, s);
           return;
         }
         if (P.dense_mf) {
@@ -1780,17 +1788,17 @@ int time_half_step_t(uot_ctx* ctx, const uot_problem* pb, int nb, double eps, co
           sk.on = tile_skip_enabled() ? 1 : 0;
           sk.pairs = count_pairs ? &B.ctrl->pairs : nullptr;
           launch_dense_mf(P.dim, P.mf_groups, P.mf_split, rows, P.N, cols, B.wv, P.M, P.splits[0], P.cps[0], B.pm, B.ps,
-                          B.pw, 0, B.ctrl, sk, s);
+                          B.pw, 0, B.ctrl, sk, CtlHost{}, s);
           return;
         }
       }
       if (P.wfl) {
         launch_wf_lse<T>(P.dim, rows, P.N, cols, B.wv, P.M, P.cost.cut, B.wfl[0], P.wf_umax[0], B.wfpm, B.wfps, 0,
-                         B.ctrl, s);
+                         B.ctrl, CtlHost{}, s);
         return;
       }
       launch_dense_lse<T>(P.dim, P.R[0], rows, P.N, cols, B.wv, P.M, P.splits[0], P.cps[0], B.pm, B.ps, 0, B.ctrl,
-                          P.cost, s);
+                          P.cost, CtlHost{}, s);
     });
     ks.push_back([&] {
       if (P.wfl) launch_wf_epi<T>(B.wfpm, B.wfps, B.wfl[0], P.N, P.M, 0, B.ctrl, ep, s);

@@ -614,8 +614,10 @@ __global__ __launch_bounds__(kBlock, G == 4 ? 4 : 2) void k_dense_mf(const float
                                                       int64_t Mc, int64_t cols_per_split,
                                                       float* __restrict__ pm, float* __restrict__ ps,
                                                       float* __restrict__ pw, int side, const Ctrl* __restrict__ c,
-                                                      int skip_tiles, unsigned long long* __restrict__ pairs) {
+                                                      int skip_tiles, unsigned long long* __restrict__ pairs,
+                                                      CtlHost host) {
   using Op = typename MfOps<SPLIT>::Op;
+  if (control_hosted(host, side)) return;
   if (skip_side(c, side)) return;
   // column operands of a chunk of 512 columns and two padding tiles (read
   // by the discarded final products of the passes): FP32 [k][column], BF16
@@ -727,14 +729,15 @@ bool tile_skip_enabled() {
 
 void launch_dense_mf(int dim, int groups, bool split, const float* xr, int64_t Nr, const float* yc, const float* w,
                      int64_t Mc, int nsplit, int64_t cps, float* pm, float* ps, float* pw, int side, const Ctrl* c,
-                     const MfSkip& sk, hipStream_t s) {
+                     const MfSkip& sk, const CtlHost& host, hipStream_t s) {
   // tiles are left out only within a single column split: with several,
   // each split's bound is relative to its own maximum, whose tile is always
   // kept, so little goes and the tile records cost more than they save
   const int skip = sk.on && nsplit == 1 ? 1 : 0;
 #define UOT_MF(D, G, S)                                                                                        \
-  hipLaunchKernelGGL((k_dense_mf<D, G, S>), dim3((unsigned)((Nr + 64 * G - 1) / (64 * G)), (unsigned)nsplit), \
-                     dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, pw, side, c, skip, sk.pairs)
+  hipLaunchKernelGGL((k_dense_mf<D, G, S>), dim3((unsigned)((Nr + 64 * G - 1) / (64 * G)) + host.extra(), (unsigned)nsplit), \
+                     dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, pw, side, c, skip, sk.pairs,    \
+                     host.at((Nr + 64 * G - 1) / (64 * G)))
 #define UOT_MF_DIM(G, S)              \
   if (dim == 1) UOT_MF(1, G, S);      \
   else if (dim == 2) UOT_MF(2, G, S); \

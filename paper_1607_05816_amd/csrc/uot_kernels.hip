@@ -197,7 +197,9 @@ template <typename T, int RI, bool SPLIT>
 __global__ __launch_bounds__(kBlock) void k_grid_contig(const T* __restrict__ in, int n, int64_t A,
                                                          const T* __restrict__ gtab, int side,
                                                          const Ctrl* __restrict__ c, EpiArgs<T> ep, int band,
-                                                         T* __restrict__ pm, T* __restrict__ ps, int nsplit) {
+                                                         T* __restrict__ pm, T* __restrict__ ps, int nsplit,
+                                                         CtlHost host) {
+  if (SPLIT && control_hosted(host, side)) return;
   // block 0 of a launch that hosts the control step: partials loaded first
   const bool hosting = !SPLIT && ep.host_ctl != nullptr && blockIdx.x == 0 && blockIdx.y == 0 && blockIdx.z == 0;
   const int par = par_of(side);
@@ -343,7 +345,8 @@ __global__ __launch_bounds__(kBlock) void k_dense_lse(const T* __restrict__ xr, 
                                                        const T* __restrict__ yc, const T* __restrict__ w,
                                                        int64_t Mc, int64_t cols_per_split,
                                                        T* __restrict__ pm, T* __restrict__ ps, int side,
-                                                       const Ctrl* __restrict__ c, T a2, T cut2) {
+                                                       const Ctrl* __restrict__ c, T a2, T cut2, CtlHost host) {
+  if (control_hosted(host, side)) return;
   if (skip_side(c, side)) return;
   using V4 = typename Vec4<T>::type;
   __shared__ V4 tile[kBlock];
@@ -513,7 +516,8 @@ __global__ __launch_bounds__(kBlock) void k_dense_tf(const float* __restrict__ x
                                                       const float* __restrict__ yc, const float* __restrict__ w,
                                                       int64_t Mc, int64_t cols_per_split,
                                                       float* __restrict__ pm, float* __restrict__ ps, int side,
-                                                      const Ctrl* __restrict__ c) {
+                                                      const Ctrl* __restrict__ c, CtlHost host) {
+  if (control_hosted(host, side)) return;
   if (skip_side(c, side)) return;
   __shared__ float4 tile[kBlock];        // (y, w) of the chunk, for directly summed tile pairs
   __shared__ float4 fe[4][kBlock];       // (f_j, l_jI) for the row tile I of each wave
@@ -936,12 +940,15 @@ template void launch_scatter<float>(const float*, const int32_t*, int64_t, float
 template void launch_scatter<double>(const double*, const int32_t*, int64_t, double*, hipStream_t);
 
 void launch_dense_tf(int dim, const float* xr, int64_t Nr, const float* yc, const float* w, int64_t Mc, int nsplit,
-                     int64_t cps, float* pm, float* ps, int side, const Ctrl* c, hipStream_t s) {
-  dim3 grid(ceil_div(Nr, kBlock * 2), (unsigned)nsplit);
-  if (dim == 1) hipLaunchKernelGGL((k_dense_tf<1, 2>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, side, c);
+                     int64_t cps, float* pm, float* ps, int side, const Ctrl* c, const CtlHost& host, hipStream_t s) {
+  dim3 grid(ceil_div(Nr, kBlock * 2) + host.extra(), (unsigned)nsplit);
+  if (dim == 1) hipLaunchKernelGGL((k_dense_tf<1, 2>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, side, c,
+                       host.at(ceil_div(Nr, kBlock * 2)));
   else if (dim == 2)
-    hipLaunchKernelGGL((k_dense_tf<2, 2>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, side, c);
-  else hipLaunchKernelGGL((k_dense_tf<3, 2>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, side, c);
+    hipLaunchKernelGGL((k_dense_tf<2, 2>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, side, c,
+                       host.at(ceil_div(Nr, kBlock * 2)));
+  else hipLaunchKernelGGL((k_dense_tf<3, 2>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, side, c,
+                       host.at(ceil_div(Nr, kBlock * 2)));
 }
 
 // log2 of the sum of n partials (m, s) of one row (2^m s each, partial k at
@@ -1429,10 +1436,10 @@ void launch_grid_contig(const T* in, int64_t A, int n, const T* gtab, int side, 
   const int bd = (band < 1 || band > n) ? n : band;
   if (ri == 2)
     hipLaunchKernelGGL((k_grid_contig<T, 2, false>), dim3(gx, gy, gz), dim3(kBlock), lds, s, in, n, A, gtab, side, c,
-                       ep, bd, (T*)nullptr, (T*)nullptr, 1);
+                       ep, bd, (T*)nullptr, (T*)nullptr, 1, CtlHost{});
   else
     hipLaunchKernelGGL((k_grid_contig<T, 1, false>), dim3(gx, gy, gz), dim3(kBlock), lds, s, in, n, A, gtab, side, c,
-                       ep, bd, (T*)nullptr, (T*)nullptr, 1);
+                       ep, bd, (T*)nullptr, (T*)nullptr, 1, CtlHost{});
 }
 
 // tap slices for few long lines (A x ceil(n/64) blocks well below the chip's
@@ -1449,26 +1456,27 @@ int grid_contig_splits(int n, int64_t A, int band) {
 
 template <typename T>
 void launch_grid_contig_split(const T* in, int64_t A, int n, const T* gtab, int side, const Ctrl* c, int band,
-                              int nsplit, T* pm, T* ps, hipStream_t s) {
+                              int nsplit, T* pm, T* ps, const CtlHost& host, hipStream_t s) {
   const int bd = (band < 1 || band > n) ? n : band;
   const size_t lds = (size_t)(2 * n - 1) * sizeof(T);
   EpiArgs<T> none{};
-  hipLaunchKernelGGL((k_grid_contig<T, 1, true>), dim3(ceil_div(n, 64), (unsigned)A, (unsigned)nsplit), dim3(kBlock),
-                     lds, s, in, n, A, gtab, side, c, none, bd, pm, ps, nsplit);
+  hipLaunchKernelGGL((k_grid_contig<T, 1, true>), dim3(ceil_div(n, 64) + host.extra(), (unsigned)A, (unsigned)nsplit),
+                     dim3(kBlock), lds, s, in, n, A, gtab, side, c, none, bd, pm, ps, nsplit,
+                     host.at(ceil_div(n, 64)));
 }
 
 template <typename T, int DIM, int R>
 static void launch_dense_lse_t(const T* xr, int64_t Nr, const T* yc, const T* w, int64_t Mc, int nsplit,
                                int64_t cps, T* pm, T* ps, int side, const Ctrl* c, const CostArgs& cost,
-                               hipStream_t s) {
-  dim3 grid(ceil_div(Nr, kBlock * R), (unsigned)nsplit);
+                               const CtlHost& host, hipStream_t s) {
+  dim3 grid(ceil_div(Nr, kBlock * R) + host.extra(), (unsigned)nsplit);
   if (cost.kind == 1) {
     const T a2 = T(0.25 * M_PI * M_PI / (cost.cut * cost.cut)), cut2 = T(cost.cut * cost.cut);
     hipLaunchKernelGGL((k_dense_lse<T, DIM, R, 1>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, side,
-                       c, a2, cut2);
+                       c, a2, cut2, host.at(ceil_div(Nr, kBlock * R)));
   } else {
     hipLaunchKernelGGL((k_dense_lse<T, DIM, R, 0>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, cps, pm, ps, side,
-                       c, T(0), T(0));
+                       c, T(0), T(0), host.at(ceil_div(Nr, kBlock * R)));
   }
 }
 
@@ -1516,8 +1524,8 @@ void launch_chunk_boxes(const T* pts, int64_t n, int64_t per, int dim, T* out, h
 // one mask bit per (row wave, group) pair within the cut (k_wf_mask), and
 // the work units of every row wave: consecutive ranges [g0, g1) of its
 // groups that hold kWfUnitGroups groups within the cut, the last one
-// possibly fewer (k_wf_units).  Per half-step one wave per unit stages the
-// unit's columns in its own LDS and sums its row wave's 64 rows (one per
+// possibly fewer (k_wf_units).  Per half-step one block per unit stages the
+// unit's columns in LDS and sums its row wave's 64 rows (one per
 // lane) over them (k_wf_lse), and k_wf_epi merges each row's units in unit
 // order and applies the epilogue.  Unit k of row wave rw sits in slot
 // k nrw + rw (at most ceil(groups / kWfUnitGroups) units per row wave), so
@@ -1578,86 +1586,101 @@ __global__ __launch_bounds__(kBlock) void k_wf_units(const uint32_t* __restrict_
 __global__ void k_zero_int(int* p) { *p = 0; }
 
 
+// One unit per block, four of its groups (64 columns) per wave: bound by the
+// chain of a wave's pairs (some 60 instructions each: square root, cosine,
+// logarithm, exponential), of which there are few next to the chip.  With a unit per wave
+// (256 columns one after another) a product of 6000 x 5000 points, cut 0.1,
+// took 22.8 us on a quarter of the SIMDs; now 10.7 us.
 template <typename T, int DIM>
 __global__ __launch_bounds__(kBlock) void k_wf_lse(const T* __restrict__ xr, int64_t Nr, const T* __restrict__ yc,
                                                     const T* __restrict__ w, int64_t Mc,
                                                     const uint32_t* __restrict__ mask, const int2* __restrict__ units,
                                                     const int* __restrict__ ucnt, int nwd, T* __restrict__ pm,
                                                     T* __restrict__ ps, int side, const Ctrl* __restrict__ c, T a2,
-                                                    T cut2) {
+                                                    T cut2, CtlHost host) {
+  if (control_hosted(host, side)) return;
   using V4 = typename Vec4<T>::type;
-  // per wave: its unit's groups and their columns (x, y, z, w)
-  __shared__ int glist[kBlock / 64][kWfUnitGroups];
-  __shared__ V4 cols[kBlock / 64][kWfUnitGroups * 16];
-  if (skip_side(c, side)) return;
+  constexpr int kWaves = kBlock / 64, kGroups = kWfUnitGroups / kWaves;
+  static_assert(kGroups * 16 == 64, "a lane stages a column");
+  // per wave: its groups and their columns (x, y, z, w)
+  __shared__ int glist[kWfUnitGroups];
+  __shared__ V4 cols[kWaves][64];
+  __shared__ T red_m[kWaves][64], red_s[kWaves][64];
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  const int64_t nrw = (Nr + 63) / 64;
-  const int64_t slot = (int64_t)blockIdx.x * (kBlock / 64) + wv;
-  const int64_t rw = slot % nrw, k = slot / nrw;
-  // a wave past its row wave's units has no work, but takes part in the
-  // block's two barriers (wave-uniform)
-  const bool has = k < ucnt[rw];
-  int ng = 0;
-  if (has) {
-    const int2 un = units[slot];
-    for (int wd = un.x >> 5; wd <= (un.y - 1) >> 5; ++wd) {
-      uint32_t bits = mask[rw * nwd + wd];
-      while (bits) {
-        const int g = wd * 32 + __builtin_ctz(bits);
-        bits &= bits - 1;
-        if (g < un.x || g >= un.y) continue;
-        if (lane == 0) glist[wv][ng] = g;
-        ++ng;
-      }
-    }
-  }
-  __syncthreads();
-  // stage the unit's columns: every load in flight at once, then LDS
-  constexpr int NR = kWfUnitGroups * 16 / 64;
-  V4 rec[NR];
-#pragma unroll
-  for (int r = 0; r < NR; ++r) {
-    const int k = r * 64 + lane;
-    V4 q;
-    q.x = q.y = q.z = T(0);
-    q.w = Num<T>::ninf();
-    if (k < ng * 16) {
-      const int64_t col = (int64_t)glist[wv][k >> 4] * 16 + (k & 15);
-      if (col < Mc) {
-        q.x = yc[col];
-        if (DIM > 1) q.y = yc[Mc + col];
-        if (DIM > 2) q.z = yc[2 * Mc + col];
-        q.w = w[col];
-      }
-    }
-    rec[r] = q;
-  }
-#pragma unroll
-  for (int r = 0; r < NR; ++r)
-    if (r * 64 + lane < ng * 16) cols[wv][r * 64 + lane] = rec[r];
-  __syncthreads();
-  if (!has) return;
-  const T ewf = T(2.0 / eps_of(c, side));
+  const int64_t nrw = (Nr + 63) / 64, slot = blockIdx.x, rw = slot % nrw;
+  if (slot / nrw >= ucnt[rw] || skip_side(c, side)) return;
+  const int2 un = units[slot];
   const int64_t i = rw * 64 + lane < Nr ? rw * 64 + lane : Nr - 1;
   T xi[3] = {T(0), T(0), T(0)};
 #pragma unroll
   for (int d = 0; d < DIM; ++d) xi[d] = xr[d * Nr + i];
+  // the wave's groups: those of rank kGroups wv .. in the unit's mask words (lane: word)
+  const int wa = un.x >> 5, wb = (un.y - 1) >> 5;
+  int ng = 0;
+  for (int w0 = wa; w0 <= wb; w0 += 64) {
+    const int wd = w0 + lane;
+    uint32_t bits = wd <= wb ? mask[rw * nwd + wd] : 0u;
+    if (wd == wa) bits &= ~0u << (un.x & 31);
+    if (wd == wb) bits &= ~0u >> (31 - ((un.y - 1) & 31));
+    const int cnt = __builtin_popcount(bits);
+    int rank = cnt;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(rank, o);
+      rank += lane >= o ? u : 0;
+    }
+    const int total = __shfl(rank, 63);
+    rank += ng - cnt;
+    for (; bits; bits &= bits - 1, ++rank)
+      if (rank / kGroups == wv) glist[rank] = wd * 32 + __builtin_ctz(bits);
+    ng += total;
+  }
+  ng = __builtin_amdgcn_readfirstlane(ng - wv * kGroups);
+  ng = ng < 0 ? 0 : ng > kGroups ? kGroups : ng;
+  // (LDS entries of this wave alone)
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  V4 q;
+  q.x = q.y = q.z = T(0);
+  q.w = Num<T>::ninf();
+  if (lane < ng * 16) {
+    const int64_t col = (int64_t)glist[wv * kGroups + (lane >> 4)] * 16 + (lane & 15);
+    if (col < Mc) {
+      q.x = yc[col];
+      if (DIM > 1) q.y = yc[Mc + col];
+      if (DIM > 2) q.z = yc[2 * Mc + col];
+      q.w = w[col];
+    }
+  }
+  cols[wv][lane] = q;
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+  const T ewf = T(2.0 / eps_of(c, side));
   Lse2<T> acc;
   acc.init();
   for (int g = 0; g < ng; ++g) {
     T t[16];
 #pragma unroll
     for (int j = 0; j < 16; ++j) {
-      const V4 q = cols[wv][g * 16 + j];
-      T d2 = (xi[0] - q.x) * (xi[0] - q.x);
-      if (DIM > 1) d2 = Num<T>::fma(xi[1] - q.y, xi[1] - q.y, d2);
-      if (DIM > 2) d2 = Num<T>::fma(xi[2] - q.z, xi[2] - q.z, d2);
-      t[j] = q.w + wf_log2k<T>(d2, a2, cut2, ewf);
+      const V4 r = cols[wv][g * 16 + j];
+      T d2 = (xi[0] - r.x) * (xi[0] - r.x);
+      if (DIM > 1) d2 = Num<T>::fma(xi[1] - r.y, xi[1] - r.y, d2);
+      if (DIM > 2) d2 = Num<T>::fma(xi[2] - r.z, xi[2] - r.z, d2);
+      t[j] = r.w + wf_log2k<T>(d2, a2, cut2, ewf);
     }
     acc.template add<16>(t);
   }
-  pm[slot * 64 + lane] = acc.m;
-  ps[slot * 64 + lane] = acc.s;
+  red_m[wv][lane] = acc.m;
+  red_s[wv][lane] = acc.s;
+  __syncthreads();
+  if (wv == 0) {
+#pragma unroll
+    for (int k = 1; k < kWaves; ++k) acc.merge(red_m[k][lane], red_s[k][lane]);
+    pm[slot * 64 + lane] = acc.m;
+    ps[slot * 64 + lane] = acc.s;
+  }
 }
 
 template <typename T>
@@ -1694,17 +1717,18 @@ void launch_wf_lists(const T* rows, int64_t Nr, const T* cols, int64_t Mc, int d
 
 template <typename T>
 void launch_wf_lse(int dim, const T* xr, int64_t Nr, const T* yc, const T* w, int64_t Mc, double cut,
-                   const WfLists<T>& L, int umax, T* pm, T* ps, int side, const Ctrl* c, hipStream_t s) {
+                   const WfLists<T>& L, int umax, T* pm, T* ps, int side, const Ctrl* c, const CtlHost& host,
+                   hipStream_t s) {
   const int64_t nrw = (Nr + 63) / 64, ngr = (Mc + 15) / 16;
   const int nwd = (int)((ngr + 31) / 32);
   // the slots of the first umax units of every row wave (unit-major): the
   // rest are empty
   if (umax < 1) umax = 1;
-  const dim3 grid(ceil_div(nrw * umax, kBlock / 64));
+  const dim3 grid((unsigned)(nrw * umax) + host.extra());
   const T a2 = T(0.25 * M_PI * M_PI / (cut * cut)), cut2 = T(cut * cut);
 #define UOT_WF(D)                                                                                                 \
   hipLaunchKernelGGL((k_wf_lse<T, D>), grid, dim3(kBlock), 0, s, xr, Nr, yc, w, Mc, L.mask, L.units, L.ucnt, nwd, \
-                     pm, ps, side, c, a2, cut2)
+                     pm, ps, side, c, a2, cut2, host.at(nrw * umax))
   if (dim == 1) UOT_WF(1);
   else if (dim == 2) UOT_WF(2);
   else UOT_WF(3);
@@ -1720,8 +1744,9 @@ void launch_wf_epi(const T* pm, const T* ps, const WfLists<T>& L, int64_t Nr, in
 
 template <typename T>
 void launch_dense_lse(int dim, int R, const T* xr, int64_t Nr, const T* yc, const T* w, int64_t Mc, int nsplit,
-                      int64_t cps, T* pm, T* ps, int side, const Ctrl* c, const CostArgs& cost, hipStream_t s) {
-#define UOT_DL(D, RR) launch_dense_lse_t<T, D, RR>(xr, Nr, yc, w, Mc, nsplit, cps, pm, ps, side, c, cost, s)
+                      int64_t cps, T* pm, T* ps, int side, const Ctrl* c, const CostArgs& cost, const CtlHost& host,
+                      hipStream_t s) {
+#define UOT_DL(D, RR) launch_dense_lse_t<T, D, RR>(xr, Nr, yc, w, Mc, nsplit, cps, pm, ps, side, c, cost, host, s)
   if (R == 1) {
     if (dim == 1) UOT_DL(1, 1); else if (dim == 2) UOT_DL(2, 1); else UOT_DL(3, 1);
   } else if (R == 2) {
@@ -1839,14 +1864,14 @@ int launch_sum_exp2(const T* a, const T* b, int64_t n, double* part, hipStream_t
   template void launch_grid_contig<T>(const T*, int64_t, int, const T*, int, const Ctrl*, const EpiArgs<T>&,     \
                                       int, hipStream_t);                                                          \
   template void launch_grid_contig_split<T>(const T*, int64_t, int, const T*, int, const Ctrl*, int, int, T*, T*, \
-                                            hipStream_t);                                                         \
+                                            const CtlHost&, hipStream_t);                                         \
   template void launch_dense_lse<T>(int, int, const T*, int64_t, const T*, const T*, int64_t, int, int64_t, T*,  \
-                                    T*, int, const Ctrl*, const CostArgs&, hipStream_t);                          \
+                                    T*, int, const Ctrl*, const CostArgs&, const CtlHost&, hipStream_t);          \
   template void launch_chunk_boxes<T>(const T*, int64_t, int64_t, int, T*, hipStream_t);                        \
   template void launch_wf_lists<T>(const T*, int64_t, const T*, int64_t, int, double, const WfLists<T>&,          \
                                    hipStream_t);                                                                  \
   template void launch_wf_lse<T>(int, const T*, int64_t, const T*, const T*, int64_t, double, const WfLists<T>&, \
-                                 int, T*, T*, int, const Ctrl*, hipStream_t);                                     \
+                                 int, T*, T*, int, const Ctrl*, const CtlHost&, hipStream_t);                     \
   template void launch_wf_epi<T>(const T*, const T*, const WfLists<T>&, int64_t, int64_t, int, const Ctrl*,      \
                                  const EpiArgs<T>&, hipStream_t);                                                 \
   template void launch_dense_epi<T>(const T*, const T*, int, int64_t, int, const Ctrl*, const EpiArgs<T>&,       \

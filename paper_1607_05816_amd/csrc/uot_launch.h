@@ -55,6 +55,25 @@ template <typename T> struct EpiArgs {
   int64_t bal_iter;
 };
 
+// The control step of an iteration, run by one more block of a launch that has
+// no epilogue and comes before the Y epilogue (such a launch reads the slot of
+// the current iteration only); c null: none.
+struct CtlHost {
+  Ctrl* c = nullptr;
+  const ResPart* parts = nullptr;
+  int nparts = 0;
+  double* hist = nullptr;
+  int nfields = 0;
+  int block = -1;   // (set by the launch) the block, in x; a kernel argument, not
+                    // gridDim, whose load costs every short block of k_wf_lse 2 us
+  CtlHost at(int64_t b) const {
+    CtlHost h = *this;
+    h.block = c ? (int)b : -1;
+    return h;
+  }
+  unsigned extra() const { return c ? 1 : 0; }
+};
+
 // the in-solve mass balance of a ragged batch (KL on both marginals), taken
 // by the control step of iteration `iter`: per running problem the X and Y
 // mass partials give s = log(P/Q) / (theta1/lam1 + 1/lam2), and the X side's
@@ -90,10 +109,11 @@ void launch_grid_contig(const T* in, int64_t A, int n, const T* gtab, int side, 
 int grid_contig_splits(int n, int64_t A, int band);
 template <typename T>
 void launch_grid_contig_split(const T* in, int64_t A, int n, const T* gtab, int side, const Ctrl* c, int band,
-                              int nsplit, T* pm, T* ps, hipStream_t s);
+                              int nsplit, T* pm, T* ps, const CtlHost& host, hipStream_t s);
 template <typename T>
 void launch_dense_lse(int dim, int R, const T* xr, int64_t Nr, const T* yc, const T* w, int64_t Mc, int nsplit,
-                      int64_t cps, T* pm, T* ps, int side, const Ctrl* c, const CostArgs& cost, hipStream_t s);
+                      int64_t cps, T* pm, T* ps, int side, const Ctrl* c, const CostArgs& cost, const CtlHost& host,
+                      hipStream_t s);
 // boxes of consecutive chunks of `per` points (SoA, n points, dim <= 3):
 // out[6 b + 2 d], out[6 b + 2 d + 1] = min, max of coordinate d over chunk b
 template <typename T>
@@ -118,7 +138,8 @@ void launch_wf_lists(const T* rows, int64_t Nr, const T* cols, int64_t Mc, int d
 // partial log2-sum-exp of every unit (pm, ps: 64 per unit slot)
 template <typename T>
 void launch_wf_lse(int dim, const T* xr, int64_t Nr, const T* yc, const T* w, int64_t Mc, double cut,
-                   const WfLists<T>& L, int umax, T* pm, T* ps, int side, const Ctrl* c, hipStream_t s);
+                   const WfLists<T>& L, int umax, T* pm, T* ps, int side, const Ctrl* c, const CtlHost& host,
+                   hipStream_t s);
 // merge of each row's units in unit order, then the epilogue
 template <typename T>
 void launch_wf_epi(const T* pm, const T* ps, const WfLists<T>& L, int64_t Nr, int64_t Mc, int side, const Ctrl* c,
@@ -139,7 +160,7 @@ template <typename T> void launch_gather(const T* in, const int32_t* perm, int64
 template <typename T> void launch_scatter(const T* in, const int32_t* perm, int64_t n, T* out, hipStream_t s);
 // tile-factored dense product (FP32, R = 2), partials as launch_dense_lse
 void launch_dense_tf(int dim, const float* xr, int64_t Nr, const float* yc, const float* w, int64_t Mc, int nsplit,
-                     int64_t cps, float* pm, float* ps, int side, const Ctrl* c, hipStream_t s);
+                     int64_t cps, float* pm, float* ps, int side, const Ctrl* c, const CtlHost& host, hipStream_t s);
 // Morton order of each problem of a batch (problem b: points off[b] ..
 // off[b + 1] - 1, coordinate stride tot; nmax: the largest problem; box: 6
 // per problem); perm maps within each problem's range
@@ -172,7 +193,7 @@ void launch_batch_mf(int dim, int groups, int blocks, const BItem* items, const 
 // the product starts from and leaves for the next one
 void launch_dense_mf(int dim, int groups, bool split, const float* xr, int64_t Nr, const float* yc, const float* w,
                      int64_t Mc, int nsplit, int64_t cps, float* pm, float* ps, float* pw, int side, const Ctrl* c,
-                     const MfSkip& sk, hipStream_t s);
+                     const MfSkip& sk, const CtlHost& host, hipStream_t s);
 template <typename T>
 void launch_coord_weight(const T* w, T* out, int64_t M, int64_t stride, int64_t nk, double hk, const T* yk, int sign,
                          hipStream_t s);
