@@ -989,8 +989,9 @@ uot_problem sorted_points(const Plan& P, const uot_problem& pb, char* ws, hipStr
   T* box = at<T>(ws, P.o_box);
   const T* x = static_cast<const T*>(pb.geom.x);
   const T* y = static_cast<const T*>(pb.geom.y);
-  launch_spatial_order<T>(x, P.N, P.dim, box, code, px, s);
-  launch_spatial_order<T>(y, P.M, P.dim, box, code, py, s);
+  // (the sorted copies' room serves as scratch before they are written)
+  launch_spatial_order<T>(x, P.N, P.dim, box, code, reinterpret_cast<int32_t*>(xs), px, s);
+  launch_spatial_order<T>(y, P.M, P.dim, box, code, reinterpret_cast<int32_t*>(ys), py, s);
   launch_gather<T>(x, px, P.N, P.dim, xs, s);
   launch_gather<T>(y, py, P.M, P.dim, ys, s);
   uot_problem q = pb;

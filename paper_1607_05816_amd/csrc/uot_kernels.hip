@@ -237,6 +237,11 @@ __global__ __launch_bounds__(kBlock) void k_grid_contig(const T* __restrict__ in
   const int wlo = o0 - tb + 1 + (n - 1);
   const int wlen = (tb > ta) ? (o1 - o0) + (tb - ta) - 1 : 0;
   for (int k = threadIdx.x; k < wlen; k += kBlock) gl[k] = g[wlo + k];
+  // the taps of a slice too: read from memory chunk by chunk, each a round
+  // trip, they took most of the time of these short loops
+  T* wl = gl + wlen;
+  if (SPLIT)
+    for (int k = threadIdx.x; k < tb - ta; k += kBlock) wl[k] = line[ta + k];
   __syncthreads();
   int ii[RI];
 #pragma unroll
@@ -254,7 +259,7 @@ __global__ __launch_bounds__(kBlock) void k_grid_contig(const T* __restrict__ in
   for (; j + kChunk <= j1; j += kChunk) {
     T w[kChunk];
 #pragma unroll
-    for (int k = 0; k < kChunk; ++k) w[k] = line[j + k];
+    for (int k = 0; k < kChunk; ++k) w[k] = SPLIT ? wl[j - ta + k] : line[j + k];
 #pragma unroll
     for (int r = 0; r < RI; ++r) {
       T t[kChunk];
@@ -270,7 +275,7 @@ __global__ __launch_bounds__(kBlock) void k_grid_contig(const T* __restrict__ in
 #pragma unroll
     for (int k = 0; k < kChunk; ++k) {
       jc[k] = (j + k < j1) ? j + k : j1 - 1;
-      w[k] = line[jc[k]];
+      w[k] = SPLIT ? wl[jc[k] - ta] : line[jc[k]];
     }
 #pragma unroll
     for (int r = 0; r < RI; ++r) {
@@ -705,23 +710,30 @@ __global__ __launch_bounds__(kBlock) void k_dense_tf(const float* __restrict__ x
 
 // ---------------------------------------------------------------------------
 // spatial order of a point cloud (Z-order / Morton), for the tile-factored
-// dense product: box, codes, then the permutation by counting ranks
+// dense product: box, codes, then the permutation
 // ---------------------------------------------------------------------------
-// bx[d] = min, bx[3 + d] = max of coordinate d (one block)
+// bx[d] = min, bx[3 + d] = max of coordinate d (one block: bound by its
+// round trips, so 1024 threads with 8 loads each in flight)
+constexpr int kBoxThreads = 1024;
 template <typename T>
-__global__ __launch_bounds__(kBlock) void k_point_box(const T* __restrict__ x, int64_t n, int dim, T* __restrict__ bx) {
-  __shared__ T smin[kBlock], smax[kBlock];
+__global__ __launch_bounds__(kBoxThreads) void k_point_box(const T* __restrict__ x, int64_t n, int dim, T* __restrict__ bx) {
+  __shared__ T smin[kBoxThreads], smax[kBoxThreads];
   for (int d = 0; d < dim; ++d) {
     T lo = Num<T>::pinf(), hi = Num<T>::ninf();
-    for (int64_t i = threadIdx.x; i < n; i += kBlock) {
-      const T v = x[d * n + i];
-      lo = Num<T>::fmin(lo, v);
-      hi = Num<T>::fmax(hi, v);
+    for (int64_t i = threadIdx.x; i < n; i += 8 * kBoxThreads) {
+      T v[8];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) v[k] = x[d * n + (i + k * kBoxThreads < n ? i + k * kBoxThreads : i)];
+#pragma unroll
+      for (int k = 0; k < 8; ++k) {
+        lo = Num<T>::fmin(lo, v[k]);
+        hi = Num<T>::fmax(hi, v[k]);
+      }
     }
     smin[threadIdx.x] = lo;
     smax[threadIdx.x] = hi;
     __syncthreads();
-    for (int o = kBlock / 2; o >= 1; o >>= 1) {
+    for (int o = kBoxThreads / 2; o >= 1; o >>= 1) {
       if ((int)threadIdx.x < o) {
         smin[threadIdx.x] = Num<T>::fmin(smin[threadIdx.x], smin[threadIdx.x + o]);
         smax[threadIdx.x] = Num<T>::fmax(smax[threadIdx.x], smax[threadIdx.x + o]);
@@ -762,25 +774,62 @@ __global__ void k_morton(const T* __restrict__ x, int64_t n, int dim, const T* _
   code[i] = morton_code<T>(x + i, n, dim, bx);
 }
 
-// perm[rank_i] = i with rank_i = #{j : code_j < code_i, or code_j = code_i and j < i}
-// (a stable order; O(n^2) comparisons, once per solve, through LDS tiles)
-__global__ __launch_bounds__(kBlock) void k_rank(const uint32_t* __restrict__ code, int64_t n,
-                                                  int32_t* __restrict__ perm) {
-  __shared__ uint32_t sc[kBlock];
-  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
-  const uint32_t ci = i < n ? code[i] : 0u;
-  int64_t rank = 0;
-  for (int64_t j0 = 0; j0 < n; j0 += kBlock) {
-    __syncthreads();
-    sc[threadIdx.x] = (j0 + threadIdx.x < n) ? code[j0 + threadIdx.x] : 0xffffffffu;
-    __syncthreads();
-    const int cnt = (n - j0 < kBlock) ? (int)(n - j0) : kBlock;
-    for (int k = 0; k < cnt; ++k) {
-      const uint32_t cj = sc[k];
-      rank += (cj < ci || (cj == ci && j0 + k < i)) ? 1 : 0;
+// The permutation that sorts by (code, index): chunks of kSortChunk points are
+// sorted in LDS (bitonic; code and index as one key, so the order is stable),
+// codes in place and indices to idx; then every point's rank is its place in
+// its chunk plus, by bisection, what the other chunks hold below it.  Counting
+// every point against every other took 1430 us a cloud at 20000 points; these
+// two take 36 us.
+constexpr int kSortChunk = 2048;
+__global__ __launch_bounds__(1024) void k_sort_chunks(uint32_t* __restrict__ code, int64_t n,
+                                                       int32_t* __restrict__ idx) {
+  __shared__ uint64_t key[kSortChunk];
+  const int64_t o = (int64_t)blockIdx.x * kSortChunk;
+  const int cnt = (int)(n - o < kSortChunk ? n - o : kSortChunk);
+  for (int i = threadIdx.x; i < kSortChunk; i += 1024)
+    key[i] = i < cnt ? (uint64_t)code[o + i] << 32 | (uint32_t)i : ~0ull;
+  __syncthreads();
+  for (int k = 2; k <= kSortChunk; k <<= 1) {
+    for (int j = k >> 1; j > 0; j >>= 1) {
+      const int t = threadIdx.x, a = ((t & ~(j - 1)) << 1) | (t & (j - 1)), b = a + j;
+      const uint64_t ka = key[a], kb = key[b];
+      if ((ka > kb) == ((a & k) == 0)) {
+        key[a] = kb;
+        key[b] = ka;
+      }
+      __syncthreads();
     }
   }
-  if (i < n) perm[rank] = (int32_t)i;
+  for (int i = threadIdx.x; i < cnt; i += 1024) {
+    code[o + i] = (uint32_t)(key[i] >> 32);
+    idx[o + i] = (int32_t)(o + (int64_t)(uint32_t)key[i]);
+  }
+}
+__global__ __launch_bounds__(kBlock) void k_merge_rank(const uint32_t* __restrict__ code,
+                                                        const int32_t* __restrict__ idx, int64_t n,
+                                                        int32_t* __restrict__ perm) {
+  const int64_t i = (int64_t)blockIdx.x * kBlock + threadIdx.x;
+  if (i >= n) return;
+  const uint32_t ci = code[i];
+  const int64_t own = i / kSortChunk;
+  int64_t rank = i % kSortChunk;
+  for (int64_t c = 0; c * kSortChunk < n; ++c) {
+    if (c == own) continue;
+    // entries of the chunk below ci, or equal where the chunk comes first
+    const uint32_t* __restrict__ p = code + c * kSortChunk;
+    const int m = (int)(n - c * kSortChunk < kSortChunk ? n - c * kSortChunk : kSortChunk);
+    int lo = 0;
+#pragma unroll
+    for (int h = kSortChunk; h > 0; h >>= 1) {
+      const int t = lo + h;
+      if (t <= m) {
+        const uint32_t v = p[t - 1];
+        if (c < own ? v <= ci : v < ci) lo = t;
+      }
+    }
+    rank += lo;
+  }
+  perm[rank] = idx[i];
 }
 
 // out[r][k] = in[r][perm[k]] for rows r < nrow of length n
@@ -919,10 +968,12 @@ template void launch_spatial_order_batch<float>(const float*, int64_t, const int
                                                 uint32_t*, int32_t*, hipStream_t);
 
 template <typename T>
-void launch_spatial_order(const T* x, int64_t n, int dim, T* box, uint32_t* code, int32_t* perm, hipStream_t s) {
-  hipLaunchKernelGGL(k_point_box<T>, dim3(1), dim3(kBlock), 0, s, x, n, dim, box);
+void launch_spatial_order(const T* x, int64_t n, int dim, T* box, uint32_t* code, int32_t* idx, int32_t* perm,
+                          hipStream_t s) {
+  hipLaunchKernelGGL(k_point_box<T>, dim3(1), dim3(kBoxThreads), 0, s, x, n, dim, box);
   hipLaunchKernelGGL(k_morton<T>, dim3(ceil_div(n, kBlock)), dim3(kBlock), 0, s, x, n, dim, box, code);
-  hipLaunchKernelGGL(k_rank, dim3(ceil_div(n, kBlock)), dim3(kBlock), 0, s, code, n, perm);
+  hipLaunchKernelGGL(k_sort_chunks, dim3(ceil_div(n, kSortChunk)), dim3(1024), 0, s, code, n, idx);
+  hipLaunchKernelGGL(k_merge_rank, dim3(ceil_div(n, kBlock)), dim3(kBlock), 0, s, code, idx, n, perm);
 }
 template <typename T>
 void launch_gather(const T* in, const int32_t* perm, int64_t n, int nrow, T* out, hipStream_t s) {
@@ -932,8 +983,9 @@ template <typename T>
 void launch_scatter(const T* in, const int32_t* perm, int64_t n, T* out, hipStream_t s) {
   hipLaunchKernelGGL(k_scatter<T>, dim3(ceil_div(n, kBlock)), dim3(kBlock), 0, s, in, perm, n, out);
 }
-template void launch_spatial_order<float>(const float*, int64_t, int, float*, uint32_t*, int32_t*, hipStream_t);
-template void launch_spatial_order<double>(const double*, int64_t, int, double*, uint32_t*, int32_t*, hipStream_t);
+template void launch_spatial_order<float>(const float*, int64_t, int, float*, uint32_t*, int32_t*, int32_t*, hipStream_t);
+template void launch_spatial_order<double>(const double*, int64_t, int, double*, uint32_t*, int32_t*, int32_t*,
+                                           hipStream_t);
 template void launch_gather<float>(const float*, const int32_t*, int64_t, int, float*, hipStream_t);
 template void launch_gather<double>(const double*, const int32_t*, int64_t, int, double*, hipStream_t);
 template void launch_scatter<float>(const float*, const int32_t*, int64_t, float*, hipStream_t);
@@ -1451,14 +1503,30 @@ int grid_contig_splits(int n, int64_t A, int band) {
   const int taps = std::min(n, 2 * bd - 1);
   int64_t sp = (2048 + blocks1 - 1) / blocks1;
   const int64_t maxsp = std::max(1, taps / 256);
-  return (int)std::max<int64_t>(1, std::min(sp, maxsp));
+  sp = std::max<int64_t>(1, std::min(sp, maxsp));
+  // among up to that many slices, the ones whose blocks, dealt to 256 compute
+  // units, leave the busiest with the least: its blocks times their taps (and some
+  // 64 more for a block's set-up).  3000 cells in FP64: 11 slices are 517 blocks,
+  // three on five of the units, and took 16.1 us; 10 are two on most, 15.8 us (14.4
+  // with their taps in LDS).
+  int64_t best = sp, least = INT64_MAX;
+  for (int64_t k = sp; k >= std::max<int64_t>(1, sp / 2); --k) {
+    const int64_t cost = (blocks1 * k + 255) / 256 * ((taps + k - 1) / k + 64);
+    if (cost < least) {
+      least = cost;
+      best = k;
+    }
+  }
+  return (int)best;
 }
 
 template <typename T>
 void launch_grid_contig_split(const T* in, int64_t A, int n, const T* gtab, int side, const Ctrl* c, int band,
                               int nsplit, T* pm, T* ps, const CtlHost& host, hipStream_t s) {
   const int bd = (band < 1 || band > n) ? n : band;
-  const size_t lds = (size_t)(2 * n - 1) * sizeof(T);
+  // 64 outputs against a slice of their taps: the slice, and the g entries it meets
+  const int taps = std::min<int64_t>(n, 2 * (int64_t)bd + 62);
+  const size_t lds = (size_t)(2 * ((taps + nsplit - 1) / nsplit) + 64) * sizeof(T);
   EpiArgs<T> none{};
   hipLaunchKernelGGL((k_grid_contig<T, 1, true>), dim3(ceil_div(n, 64) + host.extra(), (unsigned)A, (unsigned)nsplit),
                      dim3(kBlock), lds, s, in, n, A, gtab, side, c, none, bd, pm, ps, nsplit,

@@ -153,9 +153,11 @@ void launch_ctrl_init(Ctrl* c, const Ctrl& init, hipStream_t s);
 void launch_ctrl_resume(Ctrl* c, double tol, hipStream_t s);
 // slot 0 valid again after a stopped solve (one more product at the last eps)
 // spatial (Morton) order of n points (dim x n, coordinate-major): box (6),
-// codes (n) and the permutation perm (n, sorted position -> original index)
+// codes and indices (scratch, n each) and the permutation perm (n, sorted
+// position -> original index)
 template <typename T>
-void launch_spatial_order(const T* x, int64_t n, int dim, T* box, uint32_t* code, int32_t* perm, hipStream_t s);
+void launch_spatial_order(const T* x, int64_t n, int dim, T* box, uint32_t* code, int32_t* idx, int32_t* perm,
+                          hipStream_t s);
 template <typename T> void launch_gather(const T* in, const int32_t* perm, int64_t n, int nrow, T* out, hipStream_t s);
 template <typename T> void launch_scatter(const T* in, const int32_t* perm, int64_t n, T* out, hipStream_t s);
 // tile-factored dense product (FP32, R = 2), partials as launch_dense_lse
