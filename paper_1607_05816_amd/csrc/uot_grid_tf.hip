@@ -290,3 +290,6 @@ void launch_grid_tf(const float* in, int64_t A, int n, int64_t B, bool strided, 
 }
 
 }  // namespace uot
+
+// (one translation unit with the line passes, the other form of a grid pass)
+#include "uot_grid_line.hip"

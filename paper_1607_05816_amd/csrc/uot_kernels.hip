@@ -2414,3 +2414,6 @@ template void launch_batch_lse<double>(int, int, int, const BItem*, const int*, 
                                        const BCtrl*, const Ctrl*, int, const EpiArgs<double>&, hipStream_t);
 
 }  // namespace uot
+
+// (one translation unit with the objective's kernels)
+#include "uot_objective.hip"
