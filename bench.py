@@ -350,7 +350,10 @@ def extensions(U, pr, ctx, dev, np, torch):
     return out
 
 
-PASS_NAMES = ["k_grid_tf<false, 4>", "k_grid_tf<true, 4>"]
+# the two passes of a half-step timed one by one: the line passes (a solve runs
+# them in pairs), and the FP16 form
+PASS_NAMES = ["k_line, last axis", "k_line, first axis + epilogue"]
+FP16_PASS_NAMES = ["k_grid_tf<false, 4>", "k_grid_tf<true, 4>"]
 
 # HBM bytes per launch (calibrated FETCH_SIZE read + WRITE_SIZE written) of the
 # two passes at both launch shapes, from the two counter runs of
@@ -412,15 +415,6 @@ def traffic(kernel, fields):
     return TRAFFIC_BYTES.get((kernel, fields))
 
 
-def exp2_executed_per_launch(lines, n, tpc=4):
-    """exp2 instructions one tile-factored pass executes, counted from the
-    kernel, per (line, 16-cell output tile): 16 column factors per tap tile,
-    16 (1 + tpc) per chunk of tpc tap tiles for the online combination, 64
-    for the Khat operands and 96 for merging the four waves."""
-    nt = n // 16
-    return float(lines) * nt * (nt * 16 + (nt // tpc) * 16 * (1 + tpc) + 64 + 96)
-
-
 def grid_roofline(U, probs, last, ctx, torch, np, nb_fields=256):
     """Roofline of the dominant kernel: the two Gibbs-product passes of one X
     half-step at the final eps (KL problem, converged v), each launched back
@@ -437,9 +431,7 @@ def grid_roofline(U, probs, last, ctx, torch, np, nb_fields=256):
     out = {"bound": "alu", "achieved": taps / (ms[k] * 1e-3) / 1e12, "peak": peak / 1e12, "unit": "Texp/s",
            "frac": taps / (ms[k] * 1e-3) / peak, "traffic": None, "kernel": PASS_NAMES[k], "kernel_avg_ms": ms[k],
            "work_per_launch": taps, "work_unit": "exp (one per tap: n1 n2 n)",
-           "exp2_executed_per_launch": exp2_executed_per_launch(N_GRID, N_GRID),
            "avg_ms_by_kernel": dict(zip(PASS_NAMES, ms)), "launch": "single 256x256 problem"}
-    out["executed_exp2_frac"] = out["exp2_executed_per_launch"] / (ms[k] * 1e-3) / peak
     tr = traffic(PASS_NAMES[k], 1)
     if tr is not None:
         out["traffic"] = float(sum(tr))
@@ -457,16 +449,14 @@ def grid_roofline(U, probs, last, ctx, torch, np, nb_fields=256):
     tb = taps * nb_fields
     out["batched"] = {"fields": nb_fields, "kernel": PASS_NAMES[kb], "kernel_avg_ms": msb[kb],
                       "achieved": tb / (msb[kb] * 1e-3) / 1e12, "frac": tb / (msb[kb] * 1e-3) / peak,
-                      "work_per_launch": tb, "avg_ms_by_kernel": dict(zip(PASS_NAMES, msb)),
-                      "exp2_executed_per_launch": exp2_executed_per_launch(nb_fields * N_GRID, N_GRID)}
-    out["batched"]["executed_exp2_frac"] = out["batched"]["exp2_executed_per_launch"] / (msb[kb] * 1e-3) / peak
+                      "work_per_launch": tb, "avg_ms_by_kernel": dict(zip(PASS_NAMES, msb))}
     # the same launches with FP16 MFMA operands (grid_kernel 3, ~1e-3 relative)
     msh = U.time_fields_half_step((N_GRID, N_GRID), h, p, pb.dx, pb.dy, U.KL(PENALTIES[0][1]), EPS, v, reps=20,
                                   ctx=ctx, grid_kernel=U.GRID_MFMA16)
     kh = int(np.argmax(msh))
-    out["batched_fp16"] = {"fields": nb_fields, "kernel": PASS_NAMES[kh] + " fp16", "kernel_avg_ms": msh[kh],
+    out["batched_fp16"] = {"fields": nb_fields, "kernel": FP16_PASS_NAMES[kh] + " fp16", "kernel_avg_ms": msh[kh],
                            "achieved": tb / (msh[kh] * 1e-3) / 1e12, "frac": tb / (msh[kh] * 1e-3) / peak,
-                           "avg_ms_by_kernel": dict(zip(PASS_NAMES, msh))}
+                           "avg_ms_by_kernel": dict(zip(FP16_PASS_NAMES, msh))}
     trb = traffic(PASS_NAMES[kb], nb_fields)
     out["batched"]["traffic"] = None if trb is None else float(sum(trb))
     del p, v
