@@ -74,10 +74,6 @@ __device__ __forceinline__ double exp2_f64(double x) {
   return __builtin_amdgcn_ldexp(r, (int)n);
 }
 
-// 2^x for x <= 0
-__device__ __forceinline__ float exp2_neg(float x) { return Num<float>::exp2(x); }
-__device__ __forceinline__ double exp2_neg(double x) { return exp2_f64(x); }
-
 // ---------------------------------------------------------------------------
 // cos(sqrt(z)) on 0 <= z <= (pi/2)^2 from the Taylor series of cos in
 // z = theta^2, sum_k (-z)^k / (2k)!, in Horner form.  FP32 stops after z^6
@@ -138,7 +134,7 @@ template <typename T> struct Lse2 {
     const T sh = (mn == Num<T>::ninf()) ? T(0) : mn;   // all -inf so far: keep s = 0
     T acc = s * Num<T>::exp2(m - sh);
 #pragma unroll
-    for (int k = 0; k < C; ++k) acc += exp2_neg(t[k] - sh);
+    for (int k = 0; k < C; ++k) acc += Num<T>::exp2(t[k] - sh);
     m = mn;
     s = acc;
   }

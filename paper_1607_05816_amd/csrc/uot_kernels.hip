@@ -1507,8 +1507,8 @@ int grid_contig_splits(int n, int64_t A, int band) {
   // among up to that many slices, the ones whose blocks, dealt to 256 compute
   // units, leave the busiest with the least: its blocks times their taps (and some
   // 64 more for a block's set-up).  3000 cells in FP64: 11 slices are 517 blocks,
-  // three on five of the units, and took 16.1 us; 10 are two on most, 15.8 us (14.4
-  // with their taps in LDS).
+  // three on five of the units, and took 16.6 us; 10, with their taps in LDS,
+  // take 14.9 us.
   int64_t best = sp, least = INT64_MAX;
   for (int64_t k = sp; k >= std::max<int64_t>(1, sp / 2); --k) {
     const int64_t cost = (blocks1 * k + 255) / 256 * ((taps + k - 1) / k + 64);
@@ -2018,7 +2018,6 @@ __global__ __launch_bounds__(kBlock) void k_batch_lse(const BItem* __restrict__ 
   __shared__ V4 tile[kBlock];
   __shared__ int item_sh;
   const T sc = T(kLog2e / eps_of(c, side));
-  const EpiK<T> K = epi_consts_of<T>(c, side, ep);
   const int n_items = *count;
   const int32_t* __restrict__ skip = half_of(side) == 0 ? bc->stop : bc->yskip;
   while (true) {
@@ -2080,6 +2079,7 @@ __global__ __launch_bounds__(kBlock) void k_batch_lse(const BItem* __restrict__ 
         }
       }
     }
+    const EpiK<T> K = epi_consts_of<T>(c, side, ep);   // (read per item: nine registers less in the products)
     ResAcc<T> ra;
     ra.init();
     const bool bal = bal_on<T>(ep, c);   // (block-uniform)
