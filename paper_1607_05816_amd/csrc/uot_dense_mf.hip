@@ -672,6 +672,11 @@ __global__ __launch_bounds__(kBlock, G == 4 ? 4 : 2) void k_batch_mf(const BItem
   __shared__ float sbox[4][6];
   __shared__ float tb[2 * 16][8];
   __shared__ int item_sh;
+  // the epilogue's factors: held in registers through the products they spill (22
+  // to 49 registers instead of 6 to 46; 4096 problems 333.7 ms instead of 328.6),
+  // and formed per item they cost small problems 1 %
+  __shared__ EpiK<float> K_sh;
+  if (threadIdx.x == 0) K_sh = epi_consts_of<float>(c, side, ep);
   uint32_t evaluated = 0;
   const float cc = float(kLog2e / eps_of(c, side));
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
@@ -691,10 +696,7 @@ __global__ __launch_bounds__(kBlock, G == 4 ? 4 : 2) void k_batch_mf(const BItem
     float m[G], tot[G], rc[G];
     mf_tile<DIM, G, SPLIT, 256>(xr + rb, totR, I.nrows, yc + cb, totC, w + cb, ce - cb, cc, pw + rb, st, sbox, tb,
                                 skip_tiles != 0, m, tot, rc, evaluated);
-    // (read for every item: held through the products they spill, 22 to 49
-    // registers instead of 6 to 46, and the 4096-problem batch takes 333.7 ms
-    // instead of 328.6)
-    const EpiK<float> K = epi_consts_of<float>(c, side, ep);
+    const EpiK<float> K = K_sh;
     ResAcc<float> ra;
     ra.init();
     const bool bal = bal_on<float>(ep, c);   // (block-uniform)
