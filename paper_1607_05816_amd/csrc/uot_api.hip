@@ -417,7 +417,8 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
     // solves pair the half-steps: X epilogue on lines of axis 0, Y epilogue on
     // lines of the last axis (2-D) or on planes (3-D)
     P.np_pair_y = P.dim == 2 ? (int)line_blocks((int)P.n[1], P.nb, P.n[0], P.parts_room) : (int)(P.nb * P.n[0]);
-    P.pair = P.line && (P.dim == 2 || line_plane_fits(P.n[1], P.n[2])) && P.np_pair_y <= P.parts_room;
+    P.pair = P.line && P.np_pair_y <= P.parts_room &&
+             (P.dim == 2 || line_plane_fits(dtype == UOT_F64, P.nb * P.n[0], P.n[1], P.n[2], P.c_max[1], P.c_max[2]));
   }
   P.o_mass = take(2 * e * std::max(std::max(parts_room, P.nparts_y), 1));
   for (int k = 0; k < 3; ++k) P.o_gtab[k] = take(P.geom == UOT_GEOM_GRID && k < P.dim ? e * (2 * P.n[k] - 1) * nst : 0);

@@ -814,6 +814,12 @@ int64_t line_blocks(int n, int64_t groups, int64_t per, int max_blocks) {
 }
 
 constexpr int kLineMaxCells = 4096;   // elements of a block: 1024 threads of 4
+constexpr size_t kLineLds = 160 * 1024;   // LDS of a compute unit
+// what a paired kernel of NT threads declares beside its dynamic LDS: the
+// partials of block_lse_reduce and control_block, and the few of the others
+template <typename T> constexpr size_t line_static_lds(int threads) {
+  return (size_t)threads * (2 * sizeof(T) + 2 * sizeof(float)) + 1024;
+}
 
 // segment length and LDS shape of a pass over nl lines of n cells:
 // the segments go over the waves when there are fewer groups of 16 columns
@@ -952,26 +958,51 @@ void launch_line_bary(const T* in, int64_t F, int64_t R, int n, double h, double
 #undef UOT_LN
 }
 
-bool line_plane_fits(int64_t n1, int64_t n2) { return n1 * n2 <= kLineMaxCells; }
+// planes of n1 x n2 cells, one per block: launch shape and dynamic LDS
+template <typename T> struct PlaneShape {
+  LineShape S1, S2;
+  int ts, nthr;
+  size_t lds;
+  PlaneShape(int n1, int n2, double c_max, int64_t blocks) {
+    const int ts_min = sizeof(T) == 4 ? 8 : 16;
+    int t2;
+    nthr = line_threads(n1 * n2, blocks);
+    // one segment length for both axes: the shorter of the two
+    line_shape(n2, n1, nthr, line_ts<T>(c_max), ts_min, S1, ts);
+    line_shape(n1, n2, nthr, ts, ts_min, S2, t2);
+    if (t2 != ts) {
+      ts = t2;
+      line_shape(n2, n1, nthr, ts, ts, S1, t2);
+    }
+    const size_t lb = std::max((size_t)S1.nl * S1.ldl, (size_t)S2.nl * S2.ldl);
+    const size_t pp = std::max((size_t)S1.ksn * S1.nl * S1.ldp, (size_t)S2.ksn * S2.nl * S2.ldp);
+    lds = sizeof(T) * (lb + 2 * pp);
+  }
+  bool fits() const { return lds + line_static_lds<T>(nthr) <= kLineLds; }
+};
+
+// Thin planes pad their short lines to a segment and to a tile, up to 76
+// elements for a line of a few cells, so it is the bytes that decide, with
+// the two block counts that one plan is launched with (the control step adds
+// a block).
+template <typename T> static bool plane_fits(int64_t blocks, int64_t n1, int64_t n2, double c_max) {
+  return n1 * n2 <= kLineMaxCells && PlaneShape<T>((int)n1, (int)n2, c_max, blocks).fits() &&
+         PlaneShape<T>((int)n1, (int)n2, c_max, blocks + 1).fits();
+}
+bool line_plane_fits(bool f64, int64_t planes, int64_t n1, int64_t n2, double c1_max, double c2_max) {
+  const double c = std::max(c1_max, c2_max);
+  return f64 ? plane_fits<double>(planes, n1, n2, c) : plane_fits<float>(planes, n1, n2, c);
+}
 
 template <typename T>
 void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1, double h2, double c1_max,
                        double c2_max, int side, const Ctrl* c, const EpiArgs<T>* ep, T* out, hipStream_t s) {
   const unsigned blocks = (unsigned)(F * n0) + (ep && ep->host_ctl ? 1 : 0);
   const int tot = n1 * n2;
-  const int nthr = line_threads(tot, blocks), ts_min = sizeof(T) == 4 ? 8 : 16;
-  LineShape S1, S2;
-  int ts, t2;
-  // one segment length for both axes: the shorter of the two
-  line_shape(n2, n1, nthr, line_ts<T>(std::max(c1_max, c2_max)), ts_min, S1, ts);
-  line_shape(n1, n2, nthr, ts, ts_min, S2, t2);
-  if (t2 != ts) {
-    ts = t2;
-    line_shape(n2, n1, nthr, ts, ts, S1, t2);
-  }
-  const size_t lb = std::max((size_t)S1.nl * S1.ldl, (size_t)S2.nl * S2.ldl);
-  const size_t pp = std::max((size_t)S1.ksn * S1.nl * S1.ldp, (size_t)S2.ksn * S2.nl * S2.ldp);
-  const size_t lds = sizeof(T) * (lb + 2 * pp);
+  const PlaneShape<T> sh(n1, n2, std::max(c1_max, c2_max), blocks);
+  const LineShape &S1 = sh.S1, &S2 = sh.S2;
+  const int ts = sh.ts, nthr = sh.nthr;
+  const size_t lds = sh.lds;
   const EpiArgs<T> none{};
 #define UOT_LN(TS, NT, EPT)                                                                                         \
   do {                                                                                                              \

@@ -269,8 +269,9 @@ bool line_bary_fits(int64_t F, int n);
 template <typename T>
 void launch_line_bary(const T* in, int64_t F, int64_t R, int n, double h, double c_max, int side, const Ctrl* c,
                       const EpiArgs<T>& ep, T* out, const BaryW& bw, hipStream_t s);
-// the last two axes of F fields of n0 x n1 x n2 cells, a plane per block
-bool line_plane_fits(int64_t n1, int64_t n2);
+// the last two axes of F fields of n0 x n1 x n2 cells, a plane per block;
+// line_plane_fits: whether the LDS of a launch over `planes` of them holds one
+bool line_plane_fits(bool f64, int64_t planes, int64_t n1, int64_t n2, double c1_max, double c2_max);
 template <typename T>
 void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1, double h2, double c1_max,
                        double c2_max, int side, const Ctrl* c, const EpiArgs<T>* ep, T* out, hipStream_t s);

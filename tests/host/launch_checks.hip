@@ -1,0 +1,241 @@
+// Launches of libuot without a GPU: the library's host code linked against
+// the recording HIP runtime below, which runs no kernel.
+//   launch_checks lines    solves, half-steps and objectives over lengths of lines
+//   launch_checks planes   solves over the planes that one block may hold
+// prints the largest dynamic LDS that each kernel was launched with.
+// Built host-only (tests/test_line_launches_cpu.py).
+#include <hip/hip_runtime.h>
+
+#include <cstdint>
+#include <cstdio>
+#include <cstdlib>
+#include <cstring>
+#include <map>
+#include <string>
+#include <vector>
+
+#include "uot.h"
+
+// ---------------------------------------------------------------------------
+// the recording runtime
+// ---------------------------------------------------------------------------
+namespace {
+struct Seen {
+  size_t lds = 0;
+  std::string shape;
+};
+std::map<const void*, Seen> g_seen;
+std::string g_shape;          // what the driver is running
+dim3 g_grid, g_block;
+size_t g_lds;
+char g_handle[64];            // every stream, event and graph
+}  // namespace
+
+extern "C" {
+hipError_t __hipPushCallConfiguration(dim3 g, dim3 b, size_t lds, hipStream_t) {
+  g_grid = g;
+  g_block = b;
+  g_lds = lds;
+  return hipSuccess;
+}
+hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t* s) {
+  *g = g_grid;
+  *b = g_block;
+  *lds = g_lds;
+  *s = nullptr;
+  return hipSuccess;
+}
+hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t lds, hipStream_t) {
+  Seen& s = g_seen[f];
+  if (lds > s.lds || s.shape.empty()) {
+    s.lds = lds;
+    s.shape = g_shape;
+  }
+  return hipSuccess;
+}
+hipError_t hipGetLastError() { return hipSuccess; }
+const char* hipGetErrorString(hipError_t) { return "recorded error"; }
+hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
+hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
+hipError_t hipDeviceGetAttribute(int* v, hipDeviceAttribute_t, int) { *v = 256; return hipSuccess; }
+hipError_t hipGetSymbolAddress(void** p, const void*) { *p = g_handle; return hipSuccess; }
+hipError_t hipOccupancyMaxActiveBlocksPerMultiprocessor(int* n, const void*, int, size_t) { *n = 4; return hipSuccess; }
+hipError_t hipStreamCreateWithFlags(hipStream_t* s, unsigned) { *s = (hipStream_t)g_handle; return hipSuccess; }
+hipError_t hipStreamDestroy(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamSynchronize(hipStream_t) { return hipSuccess; }
+hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamBeginCapture(hipStream_t, hipStreamCaptureMode) { return hipSuccess; }
+hipError_t hipStreamEndCapture(hipStream_t, hipGraph_t* g) { *g = (hipGraph_t)g_handle; return hipSuccess; }
+hipError_t hipGraphInstantiate(hipGraphExec_t* e, hipGraph_t, hipGraphNode_t*, char*, size_t) {
+  *e = (hipGraphExec_t)g_handle;
+  return hipSuccess;
+}
+hipError_t hipGraphLaunch(hipGraphExec_t, hipStream_t) { return hipSuccess; }
+hipError_t hipGraphExecDestroy(hipGraphExec_t) { return hipSuccess; }
+hipError_t hipGraphDestroy(hipGraph_t) { return hipSuccess; }
+hipError_t hipEventCreate(hipEvent_t* e) { *e = (hipEvent_t)g_handle; return hipSuccess; }
+hipError_t hipEventCreateWithFlags(hipEvent_t* e, unsigned) { return hipEventCreate(e); }
+hipError_t hipEventDestroy(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventRecord(hipEvent_t, hipStream_t) { return hipSuccess; }
+hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
+hipError_t hipEventElapsedTime(float* ms, hipEvent_t, hipEvent_t) { *ms = 1.f; return hipSuccess; }
+hipError_t hipMalloc(void** p, size_t n) { *p = std::malloc(n); return hipSuccess; }
+hipError_t hipFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipHostMalloc(void** p, size_t n, unsigned) { *p = std::calloc(1, n); return hipSuccess; }
+hipError_t hipHostFree(void* p) { std::free(p); return hipSuccess; }
+hipError_t hipMemsetAsync(void*, int, size_t, hipStream_t) { return hipSuccess; }
+// (what comes back from the device is zero but for its first word, the stop flag of a control block)
+hipError_t hipMemcpy(void* d, const void*, size_t n, hipMemcpyKind k) {
+  if (k == hipMemcpyDeviceToHost) {
+    std::memset(d, 0, n);
+    if (n >= 4) static_cast<char*>(d)[0] = 1;
+  }
+  return hipSuccess;
+}
+hipError_t hipMemcpyAsync(void* d, const void* s, size_t n, hipMemcpyKind k, hipStream_t) { return hipMemcpy(d, s, n, k); }
+}
+
+// ---------------------------------------------------------------------------
+// the driver
+// ---------------------------------------------------------------------------
+static int failures = 0;
+#define EXPECT(cond)                                                                                              \
+  do {                                                                                                            \
+    if (!(cond)) {                                                                                                \
+      std::fprintf(stderr, "FAILED %s:%d: %s (%s; %s)\n", __FILE__, __LINE__, #cond, uot_last_error(), g_shape.c_str()); \
+      ++failures;                                                                                                 \
+    }                                                                                                             \
+  } while (0)
+
+static void* const kDev = reinterpret_cast<void*>(0x10000);   // never dereferenced on the host
+static uot_ctx* ctx;
+
+static uot_geom grid(int dim, int64_t a, int64_t b, int64_t c) {
+  uot_geom g;
+  std::memset(&g, 0, sizeof(g));
+  g.kind = UOT_GEOM_GRID;
+  g.dim = dim;
+  const int64_t n[3] = {a, b, c};
+  for (int k = 0; k < dim; ++k) {
+    g.n[k] = n[k];
+    g.h[k] = 1.0 / 64;
+  }
+  return g;
+}
+static uot_problem problem(int dtype, const uot_geom& g) {
+  uot_problem pb;
+  std::memset(&pb, 0, sizeof(pb));
+  pb.dtype = dtype;
+  pb.geom = g;
+  pb.p = pb.q = pb.dx = pb.dy = kDev;
+  pb.F1.kind = pb.F2.kind = UOT_DIV_KL;
+  pb.F1.lambda = pb.F2.lambda = 0.1;
+  return pb;
+}
+// c = h^2 log2(e) / eps of those grids
+static uot_params params(double c) {
+  uot_params pr;
+  std::memset(&pr, 0, sizeof(pr));
+  pr.eps = 1.4426950408889634 / (64.0 * 64.0 * c);
+  pr.max_iter = 1;
+  pr.check_every = 2;
+  return pr;
+}
+static void note(const char* what, int dtype, const uot_geom& g, int nb, double c) {
+  char s[160];
+  std::snprintf(s, sizeof(s), "%s f%d %lldx%lldx%lld fields %d c %g", what, dtype == UOT_F32 ? 32 : 64, (long long)g.n[0],
+                (long long)g.n[1], (long long)g.n[2], nb, c);
+  g_shape = s;
+}
+static void solve(int dtype, const uot_geom& g, int nb, double c) {
+  note("solve", dtype, g, nb, c);
+  uot_problem pb = problem(dtype, g);
+  uot_params pr = params(c);
+  uot_result res;
+  size_t n = 0;
+  if (nb == 1) {
+    EXPECT(uot_workspace_size(&pb, &n) == UOT_OK);
+    EXPECT(uot_solve(ctx, &pb, &pr, kDev, kDev, kDev, n, &res) == UOT_OK);
+  } else {
+    EXPECT(uot_fields_workspace_size(&pb, nb, &n) == UOT_OK);
+    EXPECT(uot_solve_fields(ctx, &pb, nb, &pr, kDev, kDev, kDev, n, &res) == UOT_OK);
+  }
+}
+static void one_pass(int dtype, const uot_geom& g, double c) {
+  note("half-step and objective", dtype, g, 1, c);
+  uot_problem pb = problem(dtype, g);
+  const double eps = params(c).eps;
+  size_t n = 0;
+  double r = 0;
+  uot_objective_values o;
+  EXPECT(uot_workspace_size(&pb, &n) == UOT_OK);
+  EXPECT(uot_half_step(ctx, &pb, eps, 0, kDev, kDev, kDev, &r, kDev, n) == UOT_OK);
+  EXPECT(uot_objective(ctx, &pb, eps, kDev, kDev, nullptr, nullptr, &o, kDev, n) == UOT_OK);
+}
+
+// the kernels of a host-only build: what a launch names, and the kernel's symbol
+struct OffloadEntry {
+  uint64_t reserved;
+  uint16_t version, kind;
+  uint32_t flags;
+  const void* address;
+  const char* name;
+  uint64_t size, data;
+  void* aux;
+};
+extern "C" {
+extern const OffloadEntry __start_llvm_offload_entries[], __stop_llvm_offload_entries[];
+}
+
+// what the shapes below were launched with
+static void print_lds() {
+  for (const OffloadEntry* e = __start_llvm_offload_entries; e != __stop_llvm_offload_entries; ++e) {
+    const auto s = g_seen.find(e->address);
+    if (s != g_seen.end()) std::printf("%s %zu %s\n", e->name, s->second.lds, s->second.shape.c_str());
+  }
+}
+
+// the longest segments, and shorter ones
+static const double kC[] = {0.01, 0.3};
+
+// lines along either axis, few and many
+static void lines() {
+  for (int dt : {UOT_F32, UOT_F64})
+    for (double c : kC)
+      for (int64_t n = 1; n <= 4096; n += n < 1100 ? 1 : 7) {
+        for (int64_t m : {3, 600}) {
+          solve(dt, grid(2, n, m, 0), 1, c);
+          solve(dt, grid(2, m, n, 0), 1, c);
+        }
+        solve(dt, grid(1, n, 0, 0), 1, c);
+        one_pass(dt, grid(1, n, 0, 0), c);
+        one_pass(dt, grid(2, 3, n, 0), c);
+        one_pass(dt, grid(3, n, 5, 2), c);
+      }
+}
+
+// planes of up to 4096 cells and somewhat more, one per block, few blocks and many
+static void planes() {
+  for (int dt : {UOT_F32, UOT_F64})
+    for (double c : kC)
+      for (int64_t a = 1; a <= 4096; ++a)
+        for (int64_t b = 1; a * b <= 4200 && b <= 4096; ++b) {
+          solve(dt, grid(3, 2, a, b), 1, c);
+          if (a * b <= 1024) solve(dt, grid(3, 2, a, b), 200, c);
+        }
+}
+
+int main(int argc, char** argv) {
+  if (argc < 2 || uot_create(&ctx, nullptr) != UOT_OK) return 2;
+  const std::string what = argv[1];
+  if (what == "lines") lines();
+  if (what == "planes") planes();
+  print_lds();
+  uot_destroy(ctx);
+  if (failures) {
+    std::fprintf(stderr, "%d launch check(s) failed\n", failures);
+    return 1;
+  }
+  std::printf("launch checks passed\n");
+  return 0;
+}

@@ -1,0 +1,57 @@
+"""Shapes and inputs that the line passes (uot_grid_line.hip) once refused or
+answered less exactly than the passes they replaced, against the FP64 oracle.
+Tolerances of solves as in test_gpu_line.py: 1e-11 (FP64) and 1e-5 (FP32) of
+max(|u|_inf, eps) after a fixed iteration count."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import uot_oracle as O
+from tests.helpers import oracle_div, pot_rel_err, rounded
+
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+from paper_1607_05816_amd import uot as U  # noqa: E402
+
+DEV = torch.device("cuda:0")
+TOL = {torch.float64: 1e-11, torch.float32: 1e-5}
+DTYPES = [torch.float32, torch.float64]
+
+
+def T(a, dtype):
+    return torch.tensor(np.asarray(a), dtype=dtype, device=DEV)
+
+
+def npd_of(dtype):
+    return np.float32 if dtype == torch.float32 else np.float64
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("shape", [(3, 17, 240), (3, 240, 17), (3, 16, 256), (2, 4, 1000), (2, 1000, 4), (2, 1, 3000)])
+def test_thin_planes(shape, dtype):
+    """3-D grids whose last two axes form a plane that a block has no LDS for
+    (its short lines are padded), with and without a graph, several fields, and
+    the asynchronous solve: one pass per launch."""
+    eps = 1e-2
+    rng = np.random.default_rng(sum(shape))
+    size = int(np.prod(shape))
+    h = tuple(1.0 / max(n, 64) for n in shape)
+    p, q = (rounded(rng.uniform(0.2, 2.0, (2, size)), npd_of(dtype)) for _ in range(2))
+    d = rounded(np.full(size, float(np.prod(h))), npd_of(dtype))
+    F = U.KL(0.1)
+    kw = dict(eps0=0.1, eps_stages=2, iters_per_stage=3, tol=0.0, max_iter=10)
+    print("case thin planes", shape, dtype, flush=True)
+    uf, vf, _ = U.solve_fields(shape, h, T(p, dtype), T(q, dtype), T(d, dtype), T(d, dtype), F, F, eps, **kw)
+    for k in range(2):
+        prob = U.grid_problem(shape, h, T(p[k], dtype), T(q[k], dtype), T(d, dtype), T(d, dtype), F, F)
+        u, v, info = U.solve(prob, eps, **kw)
+        a = U.solve_async(prob, eps, **kw)
+        assert a.result()["iters"] == info["iters"] == 10
+        assert torch.equal(a.u, u) and torch.equal(a.v, v)
+        ref = O.solve(O.GridGeom(shape, h), np.log(p[k]), np.log(q[k]), np.log(d), np.log(d), oracle_div(F),
+                      oracle_div(F), eps, tol=0.0, max_iter=10, eps0=0.1, n_stages=2, iters_per_stage=3)
+        for x, y in ((u, "u"), (v, "v"), (uf[k], "u"), (vf[k], "v")):
+            assert pot_rel_err(x.cpu(), ref[y], eps) < TOL[dtype]

@@ -1,0 +1,85 @@
+"""Launches of the library's host code on a recording HIP runtime, without a GPU.
+
+Every library source is compiled for the host only and linked with
+tests/host/launch_checks.hip, whose runtime records launches and runs no
+kernel.  The driver solves over the shapes whose lines or planes one block
+holds; the largest dynamic LDS that each kernel was launched with, added to
+what the kernel declares itself (the metadata of the built library's code
+objects), has to fit the 160 KB of a compute unit.
+"""
+import os
+import re
+import subprocess
+
+import pytest
+
+ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+CSRC = os.path.join(ROOT, "paper_1607_05816_amd", "csrc")
+LIB = os.path.join(ROOT, "paper_1607_05816_amd", "libuot.so")
+SOURCES = ["uot_kernels.hip", "uot_grid_tf.hip", "uot_dense_mf.hip", "uot_api.hip", "uot_net.hip"]
+HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
+LLVM = "/opt/rocm/llvm/bin"
+LDS = 160 * 1024
+
+pytestmark = pytest.mark.skipif(not (os.path.exists(HIPCC) and os.path.exists(LLVM + "/clang++")),
+                                reason="needs the ROCm toolchain")
+
+
+def _run(cmd, **kw):
+    r = subprocess.run(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, **kw)
+    return r.returncode, r.stdout.decode(errors="replace")
+
+
+@pytest.fixture(scope="module")
+def driver(tmp_path_factory):
+    d = tmp_path_factory.mktemp("launches")
+    objs, procs = [], []
+    for src in [os.path.join(CSRC, s) for s in SOURCES] + [os.path.join(ROOT, "tests", "host", "launch_checks.hip")]:
+        objs.append(str(d / os.path.basename(src).replace(".hip", ".o")))
+        procs.append(subprocess.Popen(
+            [HIPCC, "-O1", "-std=c++17", "-fPIC", "--offload-arch=gfx950", "--offload-host-only", "--offload-new-driver",
+             "-Wno-unused-command-line-argument", "-I", os.path.join(ROOT, "include"), "-c", src, "-o", objs[-1]],
+            stdout=subprocess.PIPE, stderr=subprocess.STDOUT))
+    for p in procs:
+        out, _ = p.communicate()
+        assert p.returncode == 0, out.decode(errors="replace")
+    exe = str(d / "launch_checks")
+    rc, out = _run([LLVM + "/clang++", *objs, "-o", exe])
+    assert rc == 0, out
+    return exe
+
+
+@pytest.fixture(scope="module")
+def static_lds(tmp_path_factory):
+    """Static LDS of every kernel of the built library, by symbol."""
+    if not os.path.exists(LIB):
+        pytest.skip("needs the built library")
+    d = tmp_path_factory.mktemp("codeobj")
+    rc, out = _run([LLVM + "/llvm-objcopy", "--dump-section", ".hip_fatbin=" + str(d / "fat"), LIB, str(d / "copy")])
+    assert rc == 0, out
+    fat = (d / "fat").read_bytes()
+    sizes = {}
+    for m in re.finditer(b"\x7fELF", fat):
+        (d / "obj").write_bytes(fat[m.start():])
+        _, notes = _run([LLVM + "/llvm-readelf", "--notes", str(d / "obj")])
+        for kernel in notes.split(".agpr_count")[1:]:
+            name = re.search(r"\.name:\s+(\S+)", kernel).group(1)
+            sizes[name] = int(re.search(r"\.group_segment_fixed_size:\s+(\d+)", kernel).group(1))
+    assert sizes
+    return sizes
+
+
+@pytest.mark.parametrize("what", ["lines", "planes"])
+def test_lds_of_every_shape_fits(driver, static_lds, what):
+    rc, out = _run([driver, what], timeout=300)
+    assert rc == 0 and "launch checks passed" in out, out
+    seen = 0
+    for line in out.splitlines():
+        m = re.match(r"(_Z\S+) (\d+) (.*)", line)
+        if not m:
+            continue
+        name, dynamic, shape = m.group(1), int(m.group(2)), m.group(3)
+        assert name in static_lds, name
+        assert dynamic + static_lds[name] <= LDS, (name, shape, dynamic, static_lds[name])
+        seen += "k_line" in name or "k_plane" in name
+    assert seen >= 4
