@@ -236,9 +236,8 @@ __device__ __forceinline__ void epi_finish(const EpiArgs<T>& ep, const ResAcc<T>
 // loads of the partials
 struct CtrlSnap {
   int64_t l, max_iter;
-  int stage, n_stages;
+  int stage, n_stages, sn, sa;   // stages of this iteration, and of the two after it
   double tol;
-  CtrlSlot next;
 };
 
 __device__ __forceinline__ CtrlSnap ctrl_snap(const Ctrl* c, int par) {
@@ -248,21 +247,27 @@ __device__ __forceinline__ CtrlSnap ctrl_snap(const Ctrl* c, int par) {
   s.stage = c->stage[par];
   s.n_stages = c->n_stages;
   s.tol = c->tol;
-  s.next = slot_values(c, stage_at(c, s.l + 1), stage_at(c, s.l + 2), par);
+  s.sn = stage_at(c, s.l + 1);
+  s.sa = stage_at(c, s.l + 2);
   return s;
+}
+// the slot of the iteration after the one of `s`; not part of the snapshot, as
+// a block that carries it through its own tile pays 12 registers for it
+__device__ __forceinline__ CtrlSlot ctrl_next(const Ctrl* c, const CtrlSnap& s, int par) {
+  return slot_values(c, s.sn, s.sa, par);
 }
 
 // one thread: record r, count the iteration, fill the slot of the next
 // iteration (parity par ^ 1) with its eps stage, stop when done.  A stopped
 // solve skips the next iteration; the control step of a skipped iteration
 // passes the skip on (control_skip), so every later iteration skips too.
-static __device__ void control_finish(Ctrl* c, const CtrlSnap& s, double r, double du, double* __restrict__ hist,
-                                      int par) {
+static __device__ void control_finish(Ctrl* c, const CtrlSnap& s, const CtrlSlot& next, double r, double du,
+                                      double* __restrict__ hist, int par) {
   if (hist) hist[s.l] = r;
   c->res = r;
   c->du = du;
   c->iter = s.l + 1;
-  set_slot(c, par ^ 1, s.next);
+  set_slot(c, par ^ 1, next);
   const bool final_stage = s.stage >= s.n_stages;
   int status = 0;
   bool stop = false;
@@ -301,14 +306,14 @@ __device__ __forceinline__ void ctl_load(const ResPart* __restrict__ part, int n
 // block reduction of the shares and the control step (every thread of the
 // block calls it)
 template <int NT = kBlock>
-__device__ __forceinline__ void ctl_reduce_finish(Ctrl* c, const CtrlSnap& snap, float m, float den, float num,
-                                                  float du, double* __restrict__ hist, int par) {
+__device__ __forceinline__ void ctl_reduce_finish(Ctrl* c, const CtrlSnap& snap, const CtrlSlot& next, float m,
+                                                  float den, float num, float du, double* __restrict__ hist, int par) {
   __shared__ ResPart tot;
   __syncthreads();   // the block's own reductions before this one are complete
   block_res_reduce<float, NT>(m, den, num, du, &tot);
   __syncthreads();
   if (threadIdx.x == 0)
-    control_finish(c, snap, res_ratio(double(tot.num), double(tot.den)), double(tot.du), hist, par);
+    control_finish(c, snap, next, res_ratio(double(tot.num), double(tot.den)), double(tot.du), hist, par);
 }
 
 // Control step of iteration parity par by one block of NT threads.  One
@@ -320,6 +325,7 @@ template <int NT = kBlock>
 __device__ __forceinline__ void control_block(Ctrl* c, const ResPart* __restrict__ part, int nparts,
                                               double* __restrict__ hist, int nfields, int par) {
   const CtrlSnap snap = ctrl_snap(c, par);
+  const CtrlSlot next = ctrl_next(c, snap, par);
   if (nfields == 0) {
     float m, den, num, du;
     ctl_load<NT>(part, nparts, m, den, num, du);
@@ -328,7 +334,7 @@ __device__ __forceinline__ void control_block(Ctrl* c, const ResPart* __restrict
       if (threadIdx.x == 0) control_skip(c, par);
       return;
     }
-    ctl_reduce_finish<NT>(c, snap, m, den, num, du, hist, par);
+    ctl_reduce_finish<NT>(c, snap, next, m, den, num, du, hist, par);
     return;
   }
   if (c->skip[par]) {
@@ -367,7 +373,7 @@ __device__ __forceinline__ void control_block(Ctrl* c, const ResPart* __restrict
     }
     __syncthreads();
   }
-  if (threadIdx.x == 0) control_finish(c, snap, double(smax[0]), double(sdu[0]), hist, par);
+  if (threadIdx.x == 0) control_finish(c, snap, next, double(smax[0]), double(sdu[0]), hist, par);
 }
 
 // The block that hosts the control step (the last in x, added by the launch; the

@@ -126,7 +126,10 @@ __global__ __launch_bounds__(kBlock) void k_grid_tf(const float* __restrict__ in
   // opb > 1 only when one chunk holds all of a wave's tap tiles (the host
   // picks opb so), so the taps stay in registers across the output tiles
   __shared__ float smM[2][4][4][64], smS[2][4][4][64];
-  const EpiK<float> K = epi_consts_of<float>(c, side, ep);
+  // the epilogue's factors: held in registers through the products they cost 16
+  // of them and up to two waves per SIMD
+  __shared__ EpiK<float> K_sh;
+  if (threadIdx.x == 0) K_sh = epi_consts_of<float>(c, side, ep);
   ResAcc<float> ra;
   ra.init();
   for (int o = 0; o < nob; ++o) {
@@ -222,12 +225,13 @@ __global__ __launch_bounds__(kBlock) void k_grid_tf(const float* __restrict__ in
     tot.s = smS[pb][0][wv][lane];
 #pragma unroll
     for (int k = 1; k < 4; ++k) tot.merge(smM[pb][k][wv][lane], smS[pb][k][wv][lane]);
-    if (valid) epi_apply<float>(eo, tot.result(), xin, K, ep, ra);
+    if (valid) epi_apply<float>(eo, tot.result(), xin, K_sh, ep, ra);
     eo = eo_next;
     xin = xin_next;
   }
   epi_finish<float>(ep, ra, (int)lid);
-  if (hosting) ctl_reduce_finish(ep.host_ctl, hsnap, hm, hden, hnum, hdu, ep.host_hist, par);
+  if (hosting)
+    ctl_reduce_finish(ep.host_ctl, hsnap, ctrl_next(ep.host_ctl, hsnap, par), hm, hden, hnum, hdu, ep.host_hist, par);
 }
 
 // output tiles per block: 1 unless there are enough line groups to fill the

@@ -314,7 +314,8 @@ __global__ __launch_bounds__(kBlock) void k_grid_contig(const T* __restrict__ in
     }
   }
   epi_finish<T>(ep, ra, (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x);
-  if (hosting) ctl_reduce_finish(ep.host_ctl, hsnap, hm, hden, hnum, hdu, ep.host_hist, par);
+  if (hosting)
+    ctl_reduce_finish(ep.host_ctl, hsnap, ctrl_next(ep.host_ctl, hsnap, par), hm, hden, hnum, hdu, ep.host_hist, par);
 }
 
 // ---------------------------------------------------------------------------

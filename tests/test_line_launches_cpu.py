@@ -13,12 +13,13 @@ import subprocess
 
 import pytest
 
+from tests import codeobj
+
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 CSRC = os.path.join(ROOT, "paper_1607_05816_amd", "csrc")
-LIB = os.path.join(ROOT, "paper_1607_05816_amd", "libuot.so")
 SOURCES = ["uot_kernels.hip", "uot_grid_tf.hip", "uot_dense_mf.hip", "uot_api.hip", "uot_net.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-LLVM = "/opt/rocm/llvm/bin"
+LLVM = codeobj.LLVM
 LDS = 160 * 1024
 
 pytestmark = pytest.mark.skipif(not (os.path.exists(HIPCC) and os.path.exists(LLVM + "/clang++")),
@@ -51,22 +52,9 @@ def driver(tmp_path_factory):
 
 @pytest.fixture(scope="module")
 def static_lds(tmp_path_factory):
-    """Static LDS of every kernel of the built library, by symbol."""
-    if not os.path.exists(LIB):
+    if not codeobj.available():
         pytest.skip("needs the built library")
-    d = tmp_path_factory.mktemp("codeobj")
-    rc, out = _run([LLVM + "/llvm-objcopy", "--dump-section", ".hip_fatbin=" + str(d / "fat"), LIB, str(d / "copy")])
-    assert rc == 0, out
-    fat = (d / "fat").read_bytes()
-    sizes = {}
-    for m in re.finditer(b"\x7fELF", fat):
-        (d / "obj").write_bytes(fat[m.start():])
-        _, notes = _run([LLVM + "/llvm-readelf", "--notes", str(d / "obj")])
-        for kernel in notes.split(".agpr_count")[1:]:
-            name = re.search(r"\.name:\s+(\S+)", kernel).group(1)
-            sizes[name] = int(re.search(r"\.group_segment_fixed_size:\s+(\d+)", kernel).group(1))
-    assert sizes
-    return sizes
+    return {k: v["lds"] for k, v in codeobj.kernels(tmp_path_factory.mktemp("codeobj")).items()}
 
 
 @pytest.mark.parametrize("what", ["lines", "planes"])
