@@ -1452,7 +1452,8 @@ int bary_t(uot_ctx* ctx, const uot_bary_problem* pb, const uot_params* pr, T* u,
   hipStream_t s = ctx->work;
   if ((rc = begin(ctx))) return rc;
   // paired line passes: the combine runs between the passes of a row's fields
-  const bool pair = P.pair && P.dim == 2 && line_bary_fits(pb->n, (int)P.n[1]);
+  const bool pair = P.pair && P.dim == 2 &&
+                    line_bary_fits(pb->dtype == UOT_F64, pb->n, P.n[0], (int)P.n[1], P.c_max[1]);
   Bufs<T> B = carve<T>(P, ws);
   const int64_t size = P.N, nb = pb->n;
   const bool mixed = P.gk == 4 && has_tf16(P) && pr->tol < kMixedSwitchTol;

@@ -936,18 +936,36 @@ void launch_line_pair(const T* in, int64_t F, int64_t R, int n, double h, double
 }
 
 // F fields of a line in one block, with room for their products side by side
-bool line_bary_fits(int64_t F, int n) { return F * n <= kLineMaxCells; }
+// and a row of log h: launch shape and dynamic LDS
+template <typename T> struct BaryShape {
+  LineShape S;
+  int ts, nthr;
+  size_t lds;
+  BaryShape(int F, int n, double c_max, int64_t blocks) {
+    nthr = line_threads(F * n, blocks);
+    line_shape(F, n, nthr, line_ts<T>(c_max), sizeof(T) == 4 ? 8 : 16, S, ts);
+    lds = line_lds_bytes<T>(S) + sizeof(T) * (size_t)(F * n + n);
+  }
+  bool fits() const { return lds + line_static_lds<T>(nthr) <= kLineLds; }
+};
+// (launched over R rows, with and without the block of the control step)
+template <typename T> static bool bary_fits(int64_t F, int64_t R, int n, double c_max) {
+  return F * n <= kLineMaxCells && BaryShape<T>((int)F, n, c_max, R).fits() &&
+         BaryShape<T>((int)F, n, c_max, R + 1).fits();
+}
+bool line_bary_fits(bool f64, int64_t F, int64_t R, int n, double c_max) {
+  return f64 ? bary_fits<double>(F, R, n, c_max) : bary_fits<float>(F, R, n, c_max);
+}
 
 template <typename T>
 void launch_line_bary(const T* in, int64_t F, int64_t R, int n, double h, double c_max, int side, const Ctrl* c,
                       const EpiArgs<T>& ep, T* out, const BaryW& bw, hipStream_t s) {
   const unsigned blocks = (unsigned)R + (ep.host_ctl ? 1 : 0);
   const int tot = (int)F * n;
-  LineShape S;
-  int ts;
-  const int nthr = line_threads(tot, blocks);
-  line_shape((int)F, n, nthr, line_ts<T>(c_max), sizeof(T) == 4 ? 8 : 16, S, ts);
-  const size_t lds = line_lds_bytes<T>(S) + sizeof(T) * (size_t)(tot + n);
+  const BaryShape<T> sh((int)F, n, c_max, blocks);
+  const LineShape& S = sh.S;
+  const int ts = sh.ts, nthr = sh.nthr;
+  const size_t lds = sh.lds;
 #define UOT_LN(TS, NT, EPT)                                                                                          \
   do {                                                                                                               \
     line_big_lds(k_line_pair<T, TS, NT, EPT, 2>, lds);                                                               \

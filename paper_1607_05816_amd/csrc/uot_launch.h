@@ -264,8 +264,9 @@ void launch_line(const T* in, int64_t A, int n, int64_t B, double h, double c_ma
 template <typename T>
 void launch_line_pair(const T* in, int64_t F, int64_t R, int n, double h, double c_max, int max_blocks, int side,
                       const Ctrl* c, const EpiArgs<T>* ep, T* out, hipStream_t s);
-// ... with the barycentre combine over the F fields as the epilogue
-bool line_bary_fits(int64_t F, int n);
+// ... with the barycentre combine over the F fields as the epilogue, a block
+// per row; line_bary_fits: whether its LDS holds the F lines of a row
+bool line_bary_fits(bool f64, int64_t F, int64_t R, int n, double c_max);
 template <typename T>
 void launch_line_bary(const T* in, int64_t F, int64_t R, int n, double h, double c_max, int side, const Ctrl* c,
                       const EpiArgs<T>& ep, T* out, const BaryW& bw, hipStream_t s);

@@ -2,6 +2,7 @@
 // the recording HIP runtime below, which runs no kernel.
 //   launch_checks lines    solves, half-steps and objectives over lengths of lines
 //   launch_checks planes   solves over the planes that one block may hold
+//   launch_checks barycenters   ... over the rows of several fields that it may hold
 // prints the largest dynamic LDS that each kernel was launched with.
 // Built host-only (tests/test_line_launches_cpu.py).
 #include <hip/hip_runtime.h>
@@ -161,6 +162,24 @@ static void solve(int dtype, const uot_geom& g, int nb, double c) {
     EXPECT(uot_solve_fields(ctx, &pb, nb, &pr, kDev, kDev, kDev, n, &res) == UOT_OK);
   }
 }
+static void barycenter(int dtype, const uot_geom& g, int nb, double c) {
+  note("barycentre", dtype, g, nb, c);
+  static const std::vector<double> alpha(64, 1.0);
+  uot_bary_problem bp;
+  std::memset(&bp, 0, sizeof(bp));
+  bp.dtype = dtype;
+  bp.n = nb;
+  bp.geom = g;
+  bp.p = bp.dx = bp.dy = kDev;
+  bp.alpha = alpha.data();
+  bp.F1.kind = bp.F2.kind = UOT_DIV_KL;
+  bp.F1.lambda = bp.F2.lambda = 0.1;
+  uot_params pr = params(c);
+  uot_result res;
+  size_t n = 0;
+  EXPECT(uot_bary_workspace_size(&bp, &n) == UOT_OK);
+  EXPECT(uot_barycenter(ctx, &bp, &pr, kDev, kDev, kDev, kDev, n, &res) == UOT_OK);
+}
 static void one_pass(int dtype, const uot_geom& g, double c) {
   note("half-step and objective", dtype, g, 1, c);
   uot_problem pb = problem(dtype, g);
@@ -225,11 +244,23 @@ static void planes() {
         }
 }
 
+// barycentres, a row of every field in one block
+static void barycenters() {
+  for (int dt : {UOT_F32, UOT_F64})
+    for (double c : kC)
+      for (int nb = 1; nb <= 64; ++nb)
+        for (int64_t n = 1; nb * n <= 4200 && n <= 4096; ++n) {
+          barycenter(dt, grid(2, 3, n, 0), nb, c);
+          if (nb * n <= 1024) barycenter(dt, grid(2, 400, n, 0), nb, c);
+        }
+}
+
 int main(int argc, char** argv) {
   if (argc < 2 || uot_create(&ctx, nullptr) != UOT_OK) return 2;
   const std::string what = argv[1];
   if (what == "lines") lines();
   if (what == "planes") planes();
+  if (what == "barycenters") barycenters();
   print_lds();
   uot_destroy(ctx);
   if (failures) {

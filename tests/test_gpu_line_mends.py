@@ -55,3 +55,21 @@ def test_thin_planes(shape, dtype):
                       oracle_div(F), eps, tol=0.0, max_iter=10, eps0=0.1, n_stages=2, iters_per_stage=3)
         for x, y in ((u, "u"), (v, "v"), (uf[k], "u"), (vf[k], "v")):
             assert pot_rel_err(x.cpu(), ref[y], eps) < TOL[dtype]
+
+
+@pytest.mark.parametrize("n", [3500, 3900])
+def test_barycenter_of_long_rows(n):
+    """One FP64 input whose row fits a block's LDS, and one whose row does not."""
+    eps, shape = 1e-3, (16, n)
+    rng = np.random.default_rng(n)
+    h = (1.0 / 64, 1.0 / n)
+    p = rng.uniform(0.2, 2.0, (1, 16 * n))
+    d = np.full(16 * n, h[0] * h[1])
+    F = U.KL(0.1)
+    print("case barycentre of long rows", n, flush=True)
+    t = [T(a, torch.float64) for a in (p, d, d)]
+    u, v, logh, _ = U.barycenter(shape, h, t[0], [1.0], t[1], t[2], F, F, eps, tol=0.0, max_iter=3)
+    ref = O.barycenter(O.GridGeom(shape, h), np.log(p), np.ones(1), np.log(d), np.log(d), oracle_div(F), oracle_div(F),
+                       eps, tol=0.0, max_iter=3)
+    assert pot_rel_err(u.cpu(), ref["u"], eps) < 1e-11
+    assert pot_rel_err(v.cpu(), ref["v"], eps) < 1e-11

@@ -57,7 +57,7 @@ def static_lds(tmp_path_factory):
     return {k: v["lds"] for k, v in codeobj.kernels(tmp_path_factory.mktemp("codeobj")).items()}
 
 
-@pytest.mark.parametrize("what", ["lines", "planes"])
+@pytest.mark.parametrize("what", ["lines", "planes", "barycenters"])
 def test_lds_of_every_shape_fits(driver, static_lds, what):
     rc, out = _run([driver, what], timeout=300)
     assert rc == 0 and "launch checks passed" in out, out
