@@ -858,9 +858,7 @@ int run_loop(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration, uot
     if (!pr->use_graph || timing) return UOT_OK;
     HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     for (int k = 0; k < chunk; ++k) it(k);
-    HIP_TRY(hipStreamEndCapture(s, &graph));
-    HIP_TRY(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
-    return UOT_OK;
+    return end_capture(s, &graph, &exec);
   };
   auto release = [&] {
     if (exec) (void)hipGraphExecDestroy(exec);
@@ -887,6 +885,7 @@ int run_loop(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration, uot
         if (second) (*iteration2)(k);
         else iteration(k);
       }
+      if ((rc = check_launches("iteration chunk"))) break;
     }
     launched += chunk;
     if (hipMemcpyAsync(ctx->pinned, dctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -940,6 +939,16 @@ int run_loop(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration, uot
   return UOT_OK;
 }
 
+// gives up a pending asynchronous solve, after what it enqueued has run
+void drop_pending(uot_ctx* ctx) {
+  (void)hipStreamSynchronize(ctx->work);
+  if (ctx->pending_exec) (void)hipGraphExecDestroy(ctx->pending_exec);
+  if (ctx->pending_graph) (void)hipGraphDestroy(ctx->pending_graph);
+  ctx->pending_exec = nullptr;
+  ctx->pending_graph = nullptr;
+  ctx->pending = false;
+}
+
 // The asynchronous form of run_loop: enqueue ceil(max_iter / chunk) chunks
 // without polling (the iterations after the device stops are no-ops: each
 // kernel of a skipped iteration returns at once), then a stream-ordered copy
@@ -955,11 +964,8 @@ int run_async(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration) {
   if (pr->use_graph) {
     HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     for (int k = 0; k < chunk; ++k) iteration(k);
-    HIP_TRY(hipStreamEndCapture(s, &graph));
-    if (hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0) != hipSuccess) {
-      (void)hipGraphDestroy(graph);
-      return fail(UOT_E_HIP, "hipGraphInstantiate failed");
-    }
+    const int rc = end_capture(s, &graph, &exec);
+    if (rc) return rc;
   }
   ctx->pending = true;   // from here the context owns the graph
   ctx->pending_graph = graph;
@@ -974,7 +980,7 @@ int run_async(uot_ctx* ctx, Ctrl* dctrl, const uot_params* pr, F&& iteration) {
   }
   HIP_TRY(hipEventRecord(ctx->ev_t1, s));
   HIP_TRY(hipMemcpyAsync(ctx->pinned, dctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s));
-  return UOT_OK;
+  return check_launches("asynchronous solve");
 }
 
 // Morton-ordered copies of both clouds for the tile-factored dense product:
@@ -1205,22 +1211,25 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
   auto iteration = iteration_with(P);
   auto iteration2 = iteration_with(P2);
   const double final_tol = pr->tol;
-  if (async) {
-    if ((rc = run_async(ctx, B.ctrl, pr, iteration))) return rc;
-  } else {
-    rc = run_loop(ctx, B.ctrl, pr, iteration, res, mixed ? &iteration2 : nullptr, &final_tol);
-    if (rc) return rc;
+  // the potentials in the caller's order
+  auto outputs = [&]() -> int {
+    if (P.sorted()) {
+      launch_scatter<T>(uo, px, P.N, u, s);
+      launch_scatter<T>(vo, py, P.M, v, s);
+    }
+    if (P.pair) pair_output<T>(P, uo, u, s);
+    return check_launches("output of the potentials");
+  };
+  if (async) {   // the result waits for uot_sync_result
+    rc = run_async(ctx, B.ctrl, pr, iteration);
+    if (!rc) rc = outputs();
+    if (!rc) rc = finish(ctx);
+    if (rc) drop_pending(ctx);
+    return rc;
   }
-  if (P.sorted()) {
-    launch_scatter<T>(uo, px, P.N, u, s);
-    launch_scatter<T>(vo, py, P.M, v, s);
-    HIP_TRY(hipGetLastError());
-  }
-  if (P.pair) {
-    pair_output<T>(P, uo, u, s);
-    HIP_TRY(hipGetLastError());
-  }
-  if (async) return finish(ctx);   // the result waits for uot_sync_result
+  rc = run_loop(ctx, B.ctrl, pr, iteration, res, mixed ? &iteration2 : nullptr, &final_tol);
+  if (rc) return rc;
+  if ((rc = outputs())) return rc;
   if (log_z) *log_z = ctx->pinned->zeta;
   if ((rc = finish(ctx))) return rc;
   if (res->status == -3) return fail(UOT_E_NONFINITE, "non-finite residual");
@@ -2485,8 +2494,7 @@ int batch_t(uot_ctx* ctx, const uot_batch_problem* pb, const uot_params* pr, T* 
   if (pr->use_graph && !timing) {
     HIP_TRY(hipStreamBeginCapture(s, hipStreamCaptureModeThreadLocal));
     for (int k = 0; k < chunk; ++k) iteration(k & 1);
-    HIP_TRY(hipStreamEndCapture(s, &graph));
-    HIP_TRY(hipGraphInstantiate(&exec, graph, nullptr, nullptr, 0));
+    if ((rc = end_capture(s, &graph, &exec))) return rc;
   }
   auto t0 = std::chrono::steady_clock::now();
   int64_t launched = 0;
@@ -2496,6 +2504,7 @@ int batch_t(uot_ctx* ctx, const uot_batch_problem* pb, const uot_params* pr, T* 
       if (hipGraphLaunch(exec, s) != hipSuccess) { rc = fail(UOT_E_HIP, "hipGraphLaunch failed"); break; }
     } else {
       for (int k = 0; k < chunk; ++k) iteration(k & 1);
+      if ((rc = check_launches("batch chunk"))) break;
     }
     launched += chunk;
     if (hipMemcpyAsync(ctx->pinned, ctrl, sizeof(Ctrl), hipMemcpyDeviceToHost, s) != hipSuccess ||
@@ -2660,11 +2669,7 @@ int uot_sync_result(uot_ctx* ctx, uot_result* res) {
   const hipError_t e = hipStreamSynchronize(ctx->work);
   float ms = 0.f;
   const hipError_t et = e == hipSuccess ? hipEventElapsedTime(&ms, ctx->ev_t0, ctx->ev_t1) : e;
-  if (ctx->pending_exec) (void)hipGraphExecDestroy(ctx->pending_exec);
-  if (ctx->pending_graph) (void)hipGraphDestroy(ctx->pending_graph);
-  ctx->pending_exec = nullptr;
-  ctx->pending_graph = nullptr;
-  ctx->pending = false;
+  drop_pending(ctx);
   if (e != hipSuccess) return fail(UOT_E_HIP, std::string("asynchronous solve failed: ") + hipGetErrorString(e));
   if (et != hipSuccess) return fail(UOT_E_HIP, std::string("hipEventElapsedTime: ") + hipGetErrorString(et));
   const Ctrl& c = *ctx->pinned;

@@ -40,6 +40,28 @@ int fail(int code, const std::string& msg);
     if (e_ != hipSuccess) return ::uot::fail(UOT_E_HIP, std::string(#expr) + ": " + hipGetErrorString(e_)); \
   } while (0)
 
+// Ends the capture of the launches enqueued since hipStreamBeginCapture and
+// instantiates them.  A launch that failed is an error here: the graph would
+// run without it, and the error it left would be reported by a later call.
+inline int end_capture(hipStream_t s, hipGraph_t* graph, hipGraphExec_t* exec) {
+  const hipError_t launched = hipGetLastError();
+  hipError_t e = hipStreamEndCapture(s, graph);
+  if (launched == hipSuccess && e == hipSuccess) e = hipGraphInstantiate(exec, *graph, nullptr, nullptr, 0);
+  if (launched == hipSuccess && e == hipSuccess) return UOT_OK;
+  if (*graph) (void)hipGraphDestroy(*graph);
+  *graph = nullptr;
+  *exec = nullptr;
+  (void)hipGetLastError();
+  return fail(UOT_E_HIP, std::string("capture of an iteration chunk failed: ") +
+                             hipGetErrorString(launched != hipSuccess ? launched : e));
+}
+
+// the error of a launch enqueued directly, taken so that no later call reports it
+inline int check_launches(const char* what) {
+  const hipError_t e = hipGetLastError();
+  return e == hipSuccess ? UOT_OK : fail(UOT_E_HIP, std::string(what) + ": " + hipGetErrorString(e));
+}
+
 // stream handshake: the library stream waits for the caller's stream at the
 // start of a call, and the caller's stream waits for the library's at the end
 inline int begin(uot_ctx* ctx) {

@@ -3,7 +3,9 @@
 //   launch_checks lines    solves, half-steps and objectives over lengths of lines
 //   launch_checks planes   solves over the planes that one block may hold
 //   launch_checks barycenters   ... over the rows of several fields that it may hold
-// prints the largest dynamic LDS that each kernel was launched with.
+// print the largest dynamic LDS that each kernel was launched with;
+//   launch_checks failing   a launch that fails is reported by its own call and
+//                           leaves no error behind
 // Built host-only (tests/test_line_launches_cpu.py).
 #include <hip/hip_runtime.h>
 
@@ -27,6 +29,9 @@ struct Seen {
 };
 std::map<const void*, Seen> g_seen;
 std::string g_shape;          // what the driver is running
+long g_launches = 0;          // launches so far
+long g_fail_at = -1;          // the launch that fails
+hipError_t g_last = hipSuccess;
 dim3 g_grid, g_block;
 size_t g_lds;
 char g_handle[64];            // every stream, event and graph
@@ -52,9 +57,14 @@ hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t lds, hipStr
     s.lds = lds;
     s.shape = g_shape;
   }
+  if (g_launches++ == g_fail_at) return g_last = hipErrorInvalidConfiguration;
   return hipSuccess;
 }
-hipError_t hipGetLastError() { return hipSuccess; }
+hipError_t hipGetLastError() {
+  const hipError_t e = g_last;
+  g_last = hipSuccess;
+  return e;
+}
 const char* hipGetErrorString(hipError_t) { return "recorded error"; }
 hipError_t hipFuncSetAttribute(const void*, hipFuncAttribute, int) { return hipSuccess; }
 hipError_t hipGetDevice(int* d) { *d = 0; return hipSuccess; }
@@ -255,13 +265,52 @@ static void barycenters() {
         }
 }
 
+// every launch of a call fails in turn
+template <typename F> static void each_launch_fails(const char* what, F&& call) {
+  g_shape = what;
+  g_launches = 0;
+  g_fail_at = -1;
+  EXPECT(call() == UOT_OK && hipGetLastError() == hipSuccess);
+  const long n = g_launches;
+  EXPECT(n > 0);
+  for (long k = 0; k < n; ++k) {
+    g_shape = std::string(what) + ", launch " + std::to_string(k) + " of " + std::to_string(n);
+    g_launches = 0;
+    g_fail_at = k;
+    EXPECT(call() == UOT_E_HIP);
+    EXPECT(hipGetLastError() == hipSuccess);
+    g_fail_at = -1;
+    EXPECT(call() == UOT_OK);   // the context still works
+  }
+}
+
+static void failing() {
+  const uot_geom shapes[] = {grid(1, 100, 0, 0), grid(1, 3000, 0, 0), grid(2, 40, 50, 0), grid(3, 6, 20, 30)};
+  uot_result res;
+  for (int dt : {UOT_F32, UOT_F64})
+    for (const uot_geom& g : shapes)
+      for (int graph : {0, 1}) {
+        uot_problem pb = problem(dt, g);
+        uot_params pr = params(0.01);
+        pr.use_graph = graph;
+        size_t n = 0;
+        EXPECT(uot_workspace_size(&pb, &n) == UOT_OK);
+        each_launch_fails("solve", [&] { return uot_solve(ctx, &pb, &pr, kDev, kDev, kDev, n, &res); });
+        each_launch_fails("asynchronous solve", [&] {
+          const int rc = uot_solve_async(ctx, &pb, &pr, kDev, kDev, kDev, n);
+          return rc ? rc : uot_sync_result(ctx, &res);
+        });
+      }
+}
+
 int main(int argc, char** argv) {
   if (argc < 2 || uot_create(&ctx, nullptr) != UOT_OK) return 2;
   const std::string what = argv[1];
   if (what == "lines") lines();
   if (what == "planes") planes();
   if (what == "barycenters") barycenters();
-  print_lds();
+  if (what == "failing") failing();
+  else print_lds();
   uot_destroy(ctx);
   if (failures) {
     std::fprintf(stderr, "%d launch check(s) failed\n", failures);

@@ -71,3 +71,11 @@ def test_lds_of_every_shape_fits(driver, static_lds, what):
         assert dynamic + static_lds[name] <= LDS, (name, shape, dynamic, static_lds[name])
         seen += "k_line" in name or "k_plane" in name
     assert seen >= 4
+
+
+def test_a_failing_launch_is_reported_by_its_call(driver):
+    """Every launch of a solve fails in turn, with and without a graph,
+    synchronous and asynchronous: the call returns the error, no error is left for
+    the next one, and the context goes on working."""
+    rc, out = _run([driver, "failing"], timeout=300)
+    assert rc == 0 and "launch checks passed" in out, out
