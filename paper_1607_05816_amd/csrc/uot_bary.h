@@ -147,19 +147,25 @@ __device__ __forceinline__ T bary_mean(const T* t2, int64_t stride, int nm, cons
   } else {
     // the power mean about the largest input, r + log(sum alpha_k e^{gam (t_k
     // - r)} / sum alpha) / gam with gam = eps / (eps + lam): 1 / gam magnifies
-    // what the sum rounds (gam is small where transport matters), so it is
-    // carried as its difference from 1
+    // what the sum rounds (gam is small where transport matters), so a sum near 1
+    // is carried as its difference from 1; a small one (the largest input has
+    // little weight, the others lie far below it) would cancel there and is
+    // taken as it is, its terms being positive
     const T gam = eps / (eps + T(F2.lam));
     T r = Num<T>::ninf();
     for (int k = 0; k < nm; ++k) r = Num<T>::fmax(r, t2[k * stride]);
     if (r == Num<T>::ninf()) return r;
-    T acc = T(0), asum = T(0);
+    T acc = T(0), asum = T(0), sum = T(0);
     for (int k = 0; k < nm; ++k) {
-      const T al = T(w.a[k]);
-      acc = Num<T>::fma(al, expm1_log2(gam * (t2[k * stride] - r)), acc);
+      const T al = T(w.a[k]), t = gam * (t2[k * stride] - r);
+      T e;
+      acc = Num<T>::fma(al, expm1_exp2(t, e), acc);
+      sum = Num<T>::fma(al, e, sum);
       asum += al;
     }
-    logh = r * T(kLn2) + Num<T>::log1p(acc / asum) / gam;
+    const T x = acc / asum;
+    const T lg = x < T(-0.5) ? Num<T>::log(sum / asum) : Num<T>::log1p(x);
+    logh = r * T(kLn2) + lg / gam;
   }
   return logh;
 }

@@ -82,7 +82,8 @@ template <typename T> __device__ __forceinline__ T epi_weight(T pot, T k, T kl, 
 }
 // e^x - 1 at x = t ln 2: the Taylor polynomial to degree 7 for |x| < 1/4
 // (remainder below 4e-10 of x), else 2^t - 1
-__device__ __forceinline__ float expm1_log2(float t) {
+// (and e = 2^t)
+__device__ __forceinline__ float expm1_exp2(float t, float& e) {
   const float x = t * float(kLn2);
   float p = 1.f / 5040.f;
   p = __builtin_fmaf(p, x, 1.f / 720.f);
@@ -91,7 +92,30 @@ __device__ __forceinline__ float expm1_log2(float t) {
   p = __builtin_fmaf(p, x, 1.f / 6.f);
   p = __builtin_fmaf(p, x, 0.5f);
   p = __builtin_fmaf(p * x, x, x);
-  return __builtin_fabsf(x) < 0.25f ? p : __builtin_amdgcn_exp2f(t) - 1.f;
+  e = __builtin_amdgcn_exp2f(t);
+  return __builtin_fabsf(x) < 0.25f ? p : e - 1.f;
+}
+__device__ __forceinline__ float expm1_log2(float t) {
+  float e;
+  return expm1_exp2(t, e);
+}
+// ... to degree 12 (remainder below 1e-17 of x)
+__device__ __forceinline__ double expm1_exp2(double t, double& e) {
+  const double x = t * kLn2;
+  double p = 1.0 / 479001600.0;
+  p = __builtin_fma(p, x, 1.0 / 39916800.0);
+  p = __builtin_fma(p, x, 1.0 / 3628800.0);
+  p = __builtin_fma(p, x, 1.0 / 362880.0);
+  p = __builtin_fma(p, x, 1.0 / 40320.0);
+  p = __builtin_fma(p, x, 1.0 / 5040.0);
+  p = __builtin_fma(p, x, 1.0 / 720.0);
+  p = __builtin_fma(p, x, 1.0 / 120.0);
+  p = __builtin_fma(p, x, 1.0 / 24.0);
+  p = __builtin_fma(p, x, 1.0 / 6.0);
+  p = __builtin_fma(p, x, 0.5);
+  p = __builtin_fma(p * x, x, x);
+  e = exp2_f64(t);
+  return __builtin_fabs(x) < 0.25 ? p : e - 1.0;
 }
 __device__ __forceinline__ double expm1_log2(double t) { return ::expm1(t * kLn2); }
 

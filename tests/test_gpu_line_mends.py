@@ -73,3 +73,34 @@ def test_barycenter_of_long_rows(n):
                        eps, tol=0.0, max_iter=3)
     assert pot_rel_err(u.cpu(), ref["u"], eps) < 1e-11
     assert pot_rel_err(v.cpu(), ref["v"], eps) < 1e-11
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("shape", [(16, 40), (300,)])
+@pytest.mark.parametrize("alpha", [(1e-8, 1 - 1e-8), (0.01, 0.99), (0.5, 0.5)])
+def test_kl_barycenter_weights(alpha, shape, dtype):
+    """Two inputs on the two halves of the grid under a small KL weight: on one
+    half the input of weight alpha[0] alone counts, e^{gam (t_1 - t_0)} of the
+    other being below 1e-10.  log h of one iteration is off by the rounding of a
+    sum of two terms of exponents up to 40, over gam, and by that of the
+    products (a few roundings of their exponents): E below."""
+    eps, lam = 4e-3, 6e-3
+    npd = npd_of(dtype)
+    size = int(np.prod(shape))
+    h = tuple(1.0 / max(n, 40) for n in shape)
+    right = (np.arange(size) % shape[-1]) >= shape[-1] // 2
+    p = rounded(np.stack([np.where(right, 0.0, 1.0), np.where(right, 1.0, 0.0)]), npd)
+    d = rounded(np.full(size, float(np.prod(h))), npd)
+    F1, F2 = U.KL(0.2), U.KL(lam)
+    print("case bary weights", alpha, shape, dtype, flush=True)
+    u, v, logh, _ = U.barycenter(shape, h, T(p, dtype), list(alpha), T(d, dtype), T(d, dtype), F1, F2, eps, tol=0.0,
+                                 max_iter=1)
+    with np.errstate(divide="ignore"):
+        ref = O.barycenter(O.GridGeom(shape, h), np.log(p), np.array(alpha), np.log(d), np.log(d), oracle_div(F1),
+                           oracle_div(F2), eps, tol=0.0, max_iter=1)
+    gam, rnd = eps / (eps + lam), np.finfo(npd).eps / 2
+    E = rnd * (8 * 40 / gam + 16 * np.max(np.abs(ref["logh"])))
+    off_h = float(np.max(np.abs(logh.cpu().double().numpy() - ref["logh"])))
+    # v = eps lam / (lam + eps) (log h - log s), log s off like the products
+    off_v = float(np.max(np.abs(v.cpu().double().numpy() - ref["v"])))
+    assert off_h < E and off_v < eps * E * 4
