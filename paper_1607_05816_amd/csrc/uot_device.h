@@ -188,6 +188,15 @@ struct Ctrl {
   unsigned long long pairs;
 };
 
+// What le = log2(e) / eps leaves beyond a double: (log2(e) - le eps) / eps, the
+// product taken exactly and log2(e) to twice a double's digits.  A double has
+// no second half as a float has in it, and a rounding of le, the same for
+// every cell, moves the level of the potentials lam / eps times as far.
+constexpr double kLog2eLo = 2.0355273740931033e-17;
+__host__ __device__ inline double le_rest(double eps, double le) {
+  return (__builtin_fma(-le, eps, kLog2e) + kLog2eLo) * le * kLn2;
+}
+
 // what the slot of an iteration holds: its stage, and the eps after it
 struct CtrlSlot {
   int sn;

@@ -56,24 +56,25 @@ template <typename T> struct EpiK {
   T kw, kwl;   // log2(e) / eps_w
   ProxK<T> k;  // eps, and the factor of KL or growth
 };
-// k + kl = r
-template <typename T> __device__ __forceinline__ void epi_parts(double r, T& k, T& kl) {
-  k = T(r);
-  kl = T(r - double(k));
+// k + kl = log2(e) / eps (le: rounded to a double)
+template <typename T> __device__ __forceinline__ void epi_parts(double eps, double le, T& k, T& kl) {
+  k = T(le);
+  kl = sizeof(T) == 4 ? T(le - double(k)) : T(le_rest(eps, le));
 }
-// from the control block's values (le: log2(e) / eps, le_w that of w)
+// from the control block's values (le: log2(e) / eps, eps_w and le_w those of w)
 template <typename T>
-__device__ __forceinline__ EpiK<T> epi_consts(double eps, double le, double le_w, double coef, double zeta) {
+__device__ __forceinline__ EpiK<T> epi_consts(double eps, double le, double eps_w, double le_w, double coef,
+                                              double zeta) {
   EpiK<T> k;
   k.zeta = T(zeta);
-  epi_parts<T>(le, k.ke, k.kel);
-  epi_parts<T>(le_w, k.kw, k.kwl);
+  epi_parts<T>(eps, le, k.ke, k.kel);
+  epi_parts<T>(eps_w, le_w, k.kw, k.kwl);
   k.k.set(eps, coef);
   return k;
 }
 // pot (k + kl) + a
 template <typename T> __device__ __forceinline__ T epi_scale(T pot, T k, T kl, T a) {
-  return Num<T>::fma(pot, k, sizeof(T) == 4 ? Num<T>::fma(pot, kl, a) : a);
+  return Num<T>::fma(pot, k, Num<T>::fma(pot, kl, a));
 }
 // the weight of a potential in the next product, (pot / eps + log d) log2(e)
 // with a = log d log2(e); infinite potentials stay what they are
@@ -165,7 +166,7 @@ __device__ __forceinline__ EpiK<T> epi_consts_of(const Ctrl* __restrict__ c, int
   if (ep.mode == EPI_RAW) return k;
   // (w feeds the next half-step, at its eps)
   const int p = par_of(side), h = half_of(side);
-  return epi_consts<T>(c->eps[p], c->le[p], c->le[p ^ h], c->coef[p][h], c->zeta);
+  return epi_consts<T>(c->eps[p], c->le[p], c->eps[p ^ h], c->le[p ^ h], c->coef[p][h], c->zeta);
 }
 
 template <typename T>

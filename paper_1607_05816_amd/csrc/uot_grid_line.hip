@@ -57,8 +57,8 @@ template <> struct LineNum<float> {
   static __device__ __forceinline__ float exp2(float x) { return __builtin_amdgcn_exp2f(x); }
   // maximum over the four lanes l % 16 + {0, 16, 32, 48}
   static __device__ __forceinline__ float max_rows(float x) { return max_over_rows(x); }
-  // 2^x for x = a b in FP32: the rounding of the product (up to 2^-24 of an
-  // exponent of 45) put back as a factor
+  // 2^x for x = a b: the rounding of the product (up to 2^-24 of an exponent of
+  // 45, 2^-53 of one of 473 in FP64) put back as a factor
   static __device__ __forceinline__ float exp2_prod(float a, float b) {
     const float p = a * b;
     const float lo = __builtin_fmaf(a, b, -p);
@@ -79,8 +79,20 @@ template <> struct LineNum<double> {
     x = __builtin_fmax(x, __shfl_xor(x, 16));
     return __builtin_fmax(x, __shfl_xor(x, 32));
   }
-  static __device__ __forceinline__ double exp2_prod(double a, double b) { return exp2(a * b); }
+  static __device__ __forceinline__ double exp2_prod(double a, double b) {
+    const double p = a * b;
+    const double lo = __builtin_fma(a, b, -p);
+    const double v = exp2(p);
+    return __builtin_fma(v, lo * kLn2, v);
+  }
 };
+
+// c = h2 log2(e) / eps of a pass, rounded once in FP64 too
+template <typename T> __device__ __forceinline__ T line_c(double h2, double eps, double le) {
+  const double p = h2 * le;
+  if constexpr (sizeof(T) == 4) return T(p);
+  return p + __builtin_fma(h2, le_rest(eps, le), __builtin_fma(h2, le, -p));
+}
 
 // The launch-wide operands of a pass at one c: lane (q, l) holds, for its taps
 // b VB 4 + VB q + s of a segment (VB consecutive ones per block of 4 VB), the
@@ -306,7 +318,7 @@ __global__ __launch_bounds__(NT) void k_line(const T* __restrict__ in, int64_t A
     valid = A - a0 < S.nl ? (int)(A - a0) : S.nl;
   }
   const bool skip = skip_side(c, side);
-  const double le = c->le[par_of(side)];
+  const double eps = c->eps[par_of(side)], le = c->le[par_of(side)];
   const int tot = S.nl * n;
   int l[EPT], i[EPT];
   int64_t el[EPT];
@@ -331,7 +343,7 @@ __global__ __launch_bounds__(NT) void k_line(const T* __restrict__ in, int64_t A
   for (int k = 0; k < EPT; ++k) xe[k] = epi_load<T>(el[k], ep);
   __builtin_amdgcn_sched_barrier(0);
   Op op;
-  op.init(c32 ? T(float(h2 * le)) : T(h2 * le));
+  op.init(c32 ? T(line_c<float>(h2, eps, le)) : line_c<T>(h2, eps, le));
   const EpiK<T> K = epi_consts_of<T>(c, side, ep);
   __builtin_amdgcn_sched_barrier(0);
   // (keeps the loads ahead of the branch)
@@ -412,6 +424,7 @@ __global__ __launch_bounds__(NT, NT == 1024 || (sizeof(T) == 4 && NT == 256 && T
   // of the passes are built meanwhile
   const bool skip = skip_side(c, side);
   const bool same = half_of(side) == 0 || MODE == 0;
+  const double eps = c->eps[par], eps_w = same ? eps : c->eps_after[par];
   const double le = c->le[par], le_w = same ? le : c->le_after[par];
   const int tot = S.nl * n;
   int l[EPT], i[EPT];
@@ -440,9 +453,9 @@ __global__ __launch_bounds__(NT, NT == 1024 || (sizeof(T) == 4 && NT == 256 && T
   }
   __builtin_amdgcn_sched_barrier(0);
   Op op;
-  op.init(T(h2 * le));
+  op.init(line_c<T>(h2, eps, le));
   EpiK<T> K{};
-  if constexpr (MODE != 0) K = epi_consts<T>(c->eps[par], le, le_w, c->coef[par][half_of(side)], c->zeta);
+  if constexpr (MODE != 0) K = epi_consts<T>(eps, le, eps_w, le_w, c->coef[par][half_of(side)], c->zeta);
   __builtin_amdgcn_sched_barrier(0);
   // (keeps the loads ahead of the branch)
 #pragma unroll
@@ -462,7 +475,7 @@ __global__ __launch_bounds__(NT, NT == 1024 || (sizeof(T) == 4 && NT == 256 && T
   ResAcc<T> ra;
   ra.init();
   if constexpr (MODE == 1) {
-    if (le_w != le) op.init(T(h2 * le_w));
+    if (le_w != le) op.init(line_c<T>(h2, eps_w, le_w));
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
       T w = Num<T>::ninf();
@@ -474,7 +487,7 @@ __global__ __launch_bounds__(NT, NT == 1024 || (sizeof(T) == 4 && NT == 256 && T
     // cell i at t2[l n + i]
     T* const t2 = ps + S.ksn * S.nl * S.ldp;
     T* const lh = t2 + tot;
-    if (le_w != le) op.init(T(h2 * le_w));
+    if (le_w != le) op.init(line_c<T>(h2, eps_w, le_w));
     T r[EPT];
 #pragma unroll
     for (int k = 0; k < EPT; ++k) {
@@ -562,6 +575,7 @@ __global__ __launch_bounds__(NT) void k_plane_pair(const T* __restrict__ in, int
   const unsigned f = grp / (unsigned)n0;
   const int64_t obase = (int64_t)f * n0 * tot + (grp - f * (unsigned)n0);
   const bool skip = skip_side(c, side);
+  const double eps = c->eps[par], eps_w = FULL ? c->eps_after[par] : eps;
   const double le = c->le[par], le_w = FULL ? c->le_after[par] : le;
   int i1[EPT], i2[EPT];
   int64_t el[EPT];
@@ -582,11 +596,11 @@ __global__ __launch_bounds__(NT) void k_plane_pair(const T* __restrict__ in, int
     for (int k = 0; k < EPT; ++k) xe[k] = epi_load<T>(el[k], ep);
   }
   __builtin_amdgcn_sched_barrier(0);
-  const T c1 = T(h1 * le), c2 = T(h2 * le);
+  const T c1 = line_c<T>(h1, eps, le), c2 = line_c<T>(h2, eps, le);
   Op op;
   op.init(FULL ? c1 : c2);
   EpiK<T> K{};
-  if constexpr (FULL) K = epi_consts<T>(c->eps[par], le, le_w, c->coef[par][1], c->zeta);
+  if constexpr (FULL) K = epi_consts<T>(eps, le, eps_w, le_w, c->coef[par][1], c->zeta);
   __builtin_amdgcn_sched_barrier(0);
   // (keeps the loads ahead of the branch)
 #pragma unroll
@@ -615,7 +629,7 @@ __global__ __launch_bounds__(NT) void k_plane_pair(const T* __restrict__ in, int
     __syncthreads();
     line_pass<T, TS, NT>(op, S2, buf, pm, ps);
     __syncthreads();
-    if (le_w != le) op.init(T(h2 * le_w));
+    if (le_w != le) op.init(line_c<T>(h2, eps_w, le_w));
 #pragma unroll
     for (int k = 0; k < EPT; ++k)
       if (ok[k]) {
@@ -631,7 +645,7 @@ __global__ __launch_bounds__(NT) void k_plane_pair(const T* __restrict__ in, int
   __syncthreads();
   line_pass<T, TS, NT>(op, S2, buf, pm, ps);
   __syncthreads();
-  const T c1w = T(h1 * le_w);
+  const T c1w = line_c<T>(h1, eps_w, le_w);
   op.init(c1w);
 #pragma unroll
   for (int k = 0; k < EPT; ++k)
@@ -684,9 +698,9 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape 
   const double tol = c->tol;
   int sn = stage_at(c, l);
   double eps = c->eps_tab[sn], le = kLog2e / eps;
-  EpiK<T> KX = epi_consts<T>(eps, le, le, ctrl_coef(c, 0, eps), 0.0), KY;
+  EpiK<T> KX = epi_consts<T>(eps, le, eps, le, ctrl_coef(c, 0, eps), 0.0), KY;
   Op op;
-  op.init(T(h2 * le));
+  op.init(line_c<T>(h2, eps, le));
 #pragma unroll
   for (int k = 0; k < EPT; ++k) {
     const int i = threadIdx.x + k * NT;
@@ -703,7 +717,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape 
     const int sn1 = stage_at(c, l + 1);
     const double eps1 = sn1 == sn ? eps : c->eps_tab[sn1], le1 = sn1 == sn ? le : kLog2e / eps1;
     if (it == 0 || sn1 != sn || KY.ke != KX.ke)
-      KY = epi_consts<T>(eps, le, le1, ctrl_coef(c, 1, eps), 0.0);
+      KY = epi_consts<T>(eps, le, eps1, le1, ctrl_coef(c, 1, eps), 0.0);
     __syncthreads();
     ResAcc<T> ra;
     ra.init();
@@ -728,7 +742,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape 
     line_pass<T, TS, NT>(op, S, buf, pm, ps);
     __syncthreads();
     ++l;
-    if (sn1 != sn) op.init(T(h2 * le1));
+    if (sn1 != sn) op.init(line_c<T>(h2, eps1, le1));
     ResAcc<T> none;
     none.init();
 #pragma unroll
@@ -743,7 +757,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape 
       sn = sn1;
       eps = eps1;
       le = le1;
-      KX = epi_consts<T>(eps, le, le, ctrl_coef(c, 0, eps), 0.0);
+      KX = epi_consts<T>(eps, le, eps, le, ctrl_coef(c, 0, eps), 0.0);
     }
     if (stopped) break;
   }

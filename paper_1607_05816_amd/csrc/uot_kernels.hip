@@ -55,7 +55,7 @@ __global__ void k_init_pot(const T* __restrict__ v0, const T* __restrict__ logd,
   if (w) {
     // (the arithmetic of the epilogues, so a solve resumed from its v repeats it)
     T k, kl;
-    epi_parts<T>(c->le[which_eps & 1], k, kl);
+    epi_parts<T>(c->eps[which_eps & 1], c->le[which_eps & 1], k, kl);
     w[i] = (p == Num<T>::pinf()) ? Num<T>::ninf() : epi_weight<T>(p, k, kl, logd[i % size] * T(kLog2e));
   }
 }
@@ -1195,7 +1195,7 @@ __global__ __launch_bounds__(kBlock) void k_bary_root(const T* __restrict__ T2, 
   const T* __restrict__ t2 = T2 + (valid ? j : size - 1);   // every lane takes part in the shuffles
   const T eps = T(eps_of(c, side));
   T kw, kwl;
-  epi_parts<T>(le_next_of(c, side), kw, kwl);
+  epi_parts<T>(eps_next_of(c, side), le_next_of(c, side), kw, kwl);
   ProxK<T> K;
   K.init(F2, eps_of(c, side));
   const T logh = bary_root<T>(t2, size, nm, la, F2, eps, sub, L);
@@ -1220,7 +1220,7 @@ __global__ __launch_bounds__(kBlock) void k_bary_combine(const T* __restrict__ T
   if (j >= size) return;
   const T eps = T(eps_of(c, side));
   T kw, kwl;
-  epi_parts<T>(le_next_of(c, side), kw, kwl);
+  epi_parts<T>(eps_next_of(c, side), le_next_of(c, side), kw, kwl);
   ProxK<T> K;
   K.init(F2, eps_of(c, side));
   const T logh = bary_mean<T>(T2 + j, size, nm, la, F2, eps);   // (TV and RG: k_bary_root)
@@ -1250,7 +1250,7 @@ __global__ __launch_bounds__(kBlock) void k_growth_combine(const T* __restrict__
   const int64_t j = (int64_t)blockIdx.x * kBlock + threadIdx.x;
   if (j >= size) return;
   T kw, kwl;
-  epi_parts<T>(le_next_of(c, side), kw, kwl);
+  epi_parts<T>(eps_next_of(c, side), le_next_of(c, side), kw, kwl);
   ProxK<T> K;
   K.init(F, eps_of(c, side));
   Lse2<T> a;

@@ -104,3 +104,59 @@ def test_kl_barycenter_weights(alpha, shape, dtype):
     # v = eps lam / (lam + eps) (log h - log s), log s off like the products
     off_v = float(np.max(np.abs(v.cpu().double().numpy() - ref["v"])))
     assert off_h < E and off_v < eps * E * 4
+
+
+def _lse_long(w, cost):
+    """log sum_j exp(w_j - cost_ij) in 80 bits."""
+    t = w[None, :] - cost
+    m = t.max(axis=1)
+    return m + np.log(np.exp(t - m[:, None]).sum(axis=1))
+
+
+@pytest.mark.parametrize("kind", ["loop", "slices", "lines", "pair", "planes", "fields", "points"])
+def test_fp64_weights_carry_no_bias(kind):
+    """FP64, equality constraints, one iteration from v0 of order 1 at eps 1e-6:
+    u = -eps S(v0), v = -eps S(u), each passing through a weight pot log2(e) / eps.
+    A rounding of log2(e) / eps is the same for every cell, so it shows in the mean
+    of (v - exact) / exact over the cells (2 x up to 1.1e-16), where the others
+    average out to 4e-17 and less, and twice ln 2's own, 3.3e-17 each: 1.1e-16
+    bounds the mean."""
+    L = np.longdouble
+    log2e = 1 / np.log(L(2))
+    # the eps of this range whose log2(e) / eps is rounded furthest down
+    cand = 1e-6 * (1 + np.arange(4096) / 8192.0)
+    off = np.array([(L(float(log2e / L(e))) * L(e) - log2e) / log2e for e in cand], dtype=np.float64)
+    eps = float(cand[int(np.argmin(off))])
+    assert off.min() < -0.9e-16
+    rng = np.random.default_rng(4)
+    shape = {"loop": (200,), "slices": (700,), "lines": (2, 4, 1100), "pair": (20, 24), "planes": (5, 8, 10),
+             "fields": (12, 16), "points": (400,)}[kind]
+    size, h = int(np.prod(shape)), tuple(1e-3 for _ in shape)
+    print("case fp64 bias", kind, eps, flush=True)
+    t = [T(a, torch.float64) for a in (np.ones(size), np.full(size, 0.5), 1 + 2e-6 * rng.random(size))]
+    v0 = t[2].cpu().numpy()
+    if kind == "points":
+        x, y = rng.random((2, 1, size)) * 1e-3 * size
+        prob = U.points_problem(T(x, torch.float64), T(y, torch.float64), t[0], t[0], t[1], t[1], U.EQ(), U.EQ())
+        cost = (L(1) * x[0][:, None] - y[0][None, :]) ** 2
+    else:
+        cost = L(0)
+        for k, n in enumerate(shape):
+            i = np.indices(shape)[k].reshape(-1).astype(L) * L(h[k])
+            cost = cost + (i[:, None] - i[None, :]) ** 2
+        wf = dict(cost=U.WF(2.0)) if kind == "slices" else {}
+        if wf:
+            cost = -2 * np.log(np.cos(np.sqrt(cost) * (np.arctan(L(1)) * 2 / L(2.0))))
+        prob = U.grid_problem(shape, h, t[0], t[0], t[1], t[1], U.EQ(), U.EQ(), **wf)
+    cost = cost / L(eps)
+    ld = np.log(L(0.5))
+    u_ref = -L(eps) * _lse_long(L(1) * v0 / L(eps) + ld, cost)
+    v_ref = -L(eps) * _lse_long(u_ref / L(eps) + ld, cost.T)
+    if kind == "fields":
+        both = [torch.stack([a, a]) for a in (t[0], t[2])]
+        got = U.solve_fields(shape, h, both[0], both[0], t[1], t[1], U.EQ(), U.EQ(), eps, tol=0.0, max_iter=1,
+                             v0=both[1])[1][1]
+    else:
+        got = U.solve(prob, eps, tol=0.0, max_iter=1, v0=t[2])[1]
+    bias = float(np.mean((got.cpu().numpy().astype(L) - v_ref) / v_ref))
+    assert abs(bias) < 1.1e-16, bias
