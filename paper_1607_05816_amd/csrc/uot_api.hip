@@ -1349,9 +1349,9 @@ int objective_t(uot_ctx* ctx, const uot_problem* pb, double eps, const T* u, con
       g.n[k] = P.n[k];
       g.h[k] = P.h[k];
     }
-    const double le = kLog2e / eps;
-    // product of the weights `in` into D[1] (D[2] is scratch)
-    auto product = [&](const double* in) {
+    // product of the weights `in` into D[1] (D[2] is scratch); axis `moment`
+    // with the kernel times that axis' cost (a direct pass, FP64 data)
+    auto product = [&](const double* in, int moment = -1) {
       EpiArgs<double> raw{};
       raw.mode = EPI_RAW;
       const double* src = in;
@@ -1360,44 +1360,79 @@ int objective_t(uot_ctx* ctx, const uot_problem* pb, double eps, const T* u, con
         int64_t A = 1, Bn = 1;
         for (int j = 0; j < k; ++j) A *= P.n[j];
         for (int j = k + 1; j < P.dim; ++j) Bn *= P.n[j];
-        launch_line<double>(src, A, (int)P.n[k], Bn, P.h[k], P.h[k] * P.h[k] * le, 1 << 30, 0, B.ctrl, raw, s,
-                            sizeof(T) == 4);   // (the kernel of a solve on FP32 data)
+        if constexpr (std::is_same<T, double>::value) {
+          if (k == moment) {
+            launch_gtab_cost<T>(B.gcost, (int)P.n[k], P.h[k], eps, P.cost, s);
+            T* tabs[3] = {B.gcost, B.gcost, B.gcost};
+            if (k == P.dim - 1) contig_pass<T>(P, k, src, A, tabs, 0, B.ctrl, raw, s);
+            else strided_pass<T>(P, k, src, A, Bn, tabs, 0, B.ctrl, raw, s);
+            src = raw.out;
+            continue;
+          }
+        }
+        launch_line<double>(src, A, (int)P.n[k], Bn, P.h[k], P.h[k] * P.h[k] * (kLog2e / eps), 1 << 30, 0, B.ctrl, raw,
+                            s, sizeof(T) == 4);   // (the kernel of a solve on FP32 data)
         src = raw.out;
       }
     };
-    auto weight = [&](const T* pot, const T* d, int axis, double* o) { launch_obj_weight<T>(pot, d, P.N, le, g, axis, o, s); };
+    auto weight = [&](const T* pot, const T* d, int axis, double* o) { launch_obj_weight(pot, d, P.N, eps, g, axis, o, s); };
     double* o = part;
-    auto moment = [&](const T* pot, const T* d, int axis) {   // sum of D[1] against (pot, d) and a coordinate
-      weight(pot, d, axis, D[3]);
-      launch_obj_sum(D[3], D[1], P.N, o, s);
+    auto sum_with = [&](const double* w) {   // sum of 2^{w + D[1]}
+      launch_obj_sum(w, D[1], P.N, o, s);
       o += nbx;
     };
+    auto moment = [&](const T* pot, const T* d, int axis) {   // sum of D[1] against (pot, d) and a coordinate
+      weight(pot, d, axis, D[3]);
+      sum_with(D[3]);
+    };
+    // the transport cost.  FP64 data: sum_ij R_ij |x_i - y_j|^2 axis by axis, a
+    // sum of positive terms.  FP32 data: second moments less twice the cross
+    // moments, products the line passes take; the difference loses up to
+    // |x|^2 / cost of FP64's digits, which FP32 potentials do not have.
+    constexpr bool positive = std::is_same<T, double>::value;
     weight(v, dy, -1, D[0]);
     product(D[0]);
     launch_obj_side64<T>(u, D[1], pp, dx, P.N, eps, F1, pi1, o, s);
     o += 4 * nbx;
-    moment(u, dx, -2);
+    if (!positive) moment(u, dx, -2);
+    if (positive) {
+      weight(u, dx, -1, D[3]);
+      for (int k = 0; k < P.dim; ++k) {
+        product(D[0], k);
+        sum_with(D[3]);
+      }
+    }
     weight(u, dx, -1, D[0]);
     product(D[0]);
     launch_obj_side64<T>(v, D[1], qq, dy, P.N, eps, F2, pi2, o, s);
     o += 4 * nbx;
-    moment(v, dy, -2);
+    if (!positive) moment(v, dy, -2);
     weight(nullptr, dy, -1, D[0]);
     product(D[0]);
     moment(nullptr, dx, -1);
-    for (int k = 0; k < P.dim; ++k) {
-      weight(v, dy, k, D[0]);
-      product(D[0]);
-      moment(u, dx, k);
+    if (!positive) {
+      for (int k = 0; k < P.dim; ++k) {
+        weight(v, dy, k, D[0]);
+        product(D[0]);
+        moment(u, dx, k);
+      }
     }
     if ((rc = fetch(o - part))) return rc;
-    for (int q = 0; q < 4; ++q) {
-      sx[q] = sum(q, nbx, 4);
-      sy[q] = sum(5 * nbx + q, nbx, 4);
-    }
-    cost = sum(4 * nbx, nbx, 1) + sum(9 * nbx, nbx, 1);
-    mK = sum(10 * nbx, nbx, 1);
-    for (int k = 0; k < P.dim; ++k) cost -= 2.0 * sum((11 + k) * nbx, nbx, 1);
+    int64_t at = 0;   // block sums, in the order of the launches
+    auto next = [&](int per) {
+      const int64_t first = at;
+      at += per * nbx;
+      return first;
+    };
+    int64_t f = next(4);
+    for (int q = 0; q < 4; ++q) sx[q] = sum(f + q, nbx, 4);
+    for (int k = 0; k < (positive ? P.dim : 1); ++k) cost += sum(next(1), nbx, 1);
+    f = next(4);
+    for (int q = 0; q < 4; ++q) sy[q] = sum(f + q, nbx, 4);
+    if (!positive) cost += sum(next(1), nbx, 1);
+    mK = sum(next(1), nbx, 1);
+    if (!positive)
+      for (int k = 0; k < P.dim; ++k) cost -= 2.0 * sum(next(1), nbx, 1);
   } else {
     // grids of the WF cost, or of a few cells per kernel width
     launch_log<T>(dx, B.logdx, P.N, 0, s);

@@ -222,7 +222,7 @@ template <typename T>
 int launch_obj_side(const T* pot, const T* S, const T* p, const T* d, int64_t n, double eps, const DivDev& F,
                     T* pi_out, double* part, hipStream_t s);
 template <typename T> int launch_sum_exp2(const T* a, const T* b, int64_t n, double* part, hipStream_t s);
-// FP64 objective (uot_objective.hip).  Grids: log2 weights pot le + log2 d
+// FP64 objective (uot_objective.hip).  Grids: log2 weights pot log2(e) / eps + log2 d
 // (pot null: 0), plus log2 of coordinate `axis` of the cell centre (-1: none,
 // -2: of its squared norm); a side's four sums from its product S; sums of
 // 2^{a + b} (per block of 256 elements)
@@ -232,7 +232,7 @@ struct GridCells {
   double h[3];
 };
 template <typename T>
-void launch_obj_weight(const T* pot, const T* d, int64_t n, double le, const GridCells& g, int axis, double* out,
+void launch_obj_weight(const T* pot, const T* d, int64_t n, double eps, const GridCells& g, int axis, double* out,
                        hipStream_t s);
 template <typename T>
 void launch_obj_side64(const T* pot, const double* S, const T* p, const T* d, int64_t n, double eps, const DivDev& F,

@@ -6,14 +6,20 @@
 #include "uot_launch.h"
 
 // ---------------------------------------------------------------------------
-// Every product here is evaluated in FP64, whatever the type of the
+// The products here are evaluated in FP64, whatever the type of the
 // potentials: in FP32 a product of exponents near 10^3 is off by 1e-6 and
 // more, as much as a converged solve's potentials are worth.
 // Grids: FP64 line passes (uot_grid_line.hip) on weights built from the
-// potentials (k_obj_weight); the transport cost is
+// potentials (k_obj_weight).  The transport cost of FP64 data is a product per
+// axis with that axis' kernel times its cost, a sum of positive terms; of FP32
+// data
 //   sum_ij R_ij |x_i - y_j|^2 = sum_i R_i. |x_i|^2 + sum_j R_.j |y_j|^2
 //                               - 2 sum_i x_i . sum_j R_ij y_j,
-// one more product per axis, with the (positive) cell coordinates as weights.
+// one line pass product per axis with the (positive) cell coordinates as
+// weights: its cancellation, |x|^2 / cost, stays below what FP32 potentials
+// leave, but took FP64's (4e-9 at 256 cells, eps 6e-6).
+// Grids of the WF cost or of kernels of a few cells keep products in the data's
+// type (uot_api.hip).
 // Point clouds: one pass over the pairs (k_obj_points) gives a row's product
 // and, for rows X, its cost moment and its row of K dy: the distance is shared,
 // two exp2 per pair.  It is bound by FP64 issue (about 60 operations per pair;
@@ -89,11 +95,13 @@ template <int Q> __device__ __forceinline__ void block_sums(const double (&v)[Q]
 template <typename T> __device__ __forceinline__ double obj_logd(T d) {
   return double(Num<T>::log(d) * T(kLog2e));
 }
-// log2 weight of a potential, pot / eps + log d; a potential of +inf (left by
-// a vanishing product) carries no mass
-template <typename T> __device__ __forceinline__ double obj_weight(const T* pot, const T* d, int64_t i, double le) {
-  const double p = pot ? double(pot[i]) : 0.0;
-  return p == __builtin_inf() ? -__builtin_inf() : p * le + obj_logd<T>(d[i]);
+// log2 weight of a potential, pot / eps + log d, with le + lo = log2(e) / eps; a
+// potential of +inf (left by a vanishing product) carries no mass
+template <typename T>
+__device__ __forceinline__ double obj_weight(const T* pot, const T* d, int64_t i, double le, double lo) {
+  const double p = pot ? double(pot[i]) : 0.0, a = obj_logd<T>(d[i]);
+  if (p == __builtin_inf()) return -__builtin_inf();
+  return p == -__builtin_inf() ? p : __builtin_fma(p, le, __builtin_fma(p, lo, a));
 }
 
 }  // namespace
@@ -103,10 +111,11 @@ template <typename T> __device__ __forceinline__ double obj_weight(const T* pot,
 // norm
 template <typename T>
 __global__ __launch_bounds__(kB) void k_obj_weight(const T* __restrict__ pot, const T* __restrict__ d, int64_t n,
-                                                   double le, GridCells g, int axis, double* __restrict__ out) {
+                                                   double le, double lo, GridCells g, int axis,
+                                                   double* __restrict__ out) {
   const int64_t i = (int64_t)blockIdx.x * kB + threadIdx.x;
   if (i >= n) return;
-  double w = obj_weight<T>(pot, d, i, le);
+  double w = obj_weight<T>(pot, d, i, le, lo);
   if (axis != -1) {
     double x[3] = {0, 0, 0}, r = 0.0;
     int64_t j = i;
@@ -154,7 +163,7 @@ __global__ __launch_bounds__(kB) void k_obj_sum(const double* __restrict__ a, co
 template <typename T, int DIM, int COST, bool FULL>
 __global__ __launch_bounds__(kB) void k_obj_points(const T* __restrict__ xr, int64_t Nr, const T* __restrict__ yc,
                                                    const T* __restrict__ pot, const T* __restrict__ d, int64_t Mc,
-                                                   int64_t cps, double le, double kc, double a2, double cut2,
+                                                   int64_t cps, double le, double lo, double kc, double a2, double cut2,
                                                    double* __restrict__ part) {
   constexpr int C = 8, Q = FULL ? 4 : 2;
   __shared__ double ty[DIM][kB], tw[kB], tk[FULL ? kB : 1];
@@ -169,7 +178,7 @@ __global__ __launch_bounds__(kB) void k_obj_points(const T* __restrict__ xr, int
     __syncthreads();
 #pragma unroll
     for (int k = 0; k < DIM; ++k) ty[k][threadIdx.x] = j < ce ? double(yc[k * Mc + j]) : 0.0;
-    tw[threadIdx.x] = j < ce ? obj_weight<T>(pot, d, j, le) : -__builtin_inf();
+    tw[threadIdx.x] = j < ce ? obj_weight<T>(pot, d, j, le, lo) : -__builtin_inf();
     if (FULL) tk[threadIdx.x] = j < ce ? obj_logd<T>(d[j]) : -__builtin_inf();
     __syncthreads();
     const int cnt = ce - c0 < kB ? (int)(ce - c0) : kB;
@@ -267,9 +276,10 @@ template <typename T> static double as_data(double k) { return double(T(k)); }
 static unsigned obj_blocks(int64_t n) { return (unsigned)((n + kB - 1) / kB); }
 
 template <typename T>
-void launch_obj_weight(const T* pot, const T* d, int64_t n, double le, const GridCells& g, int axis, double* out,
+void launch_obj_weight(const T* pot, const T* d, int64_t n, double eps, const GridCells& g, int axis, double* out,
                        hipStream_t s) {
-  hipLaunchKernelGGL(k_obj_weight<T>, dim3(obj_blocks(n)), dim3(kB), 0, s, pot, d, n, le, g, axis, out);
+  const double le = kLog2e / eps;
+  hipLaunchKernelGGL(k_obj_weight<T>, dim3(obj_blocks(n)), dim3(kB), 0, s, pot, d, n, le, le_rest(eps, le), g, axis, out);
 }
 template <typename T>
 void launch_obj_side64(const T* pot, const double* S, const T* p, const T* d, int64_t n, double eps, const DivDev& F,
@@ -282,14 +292,15 @@ void launch_obj_sum(const double* a, const double* b, int64_t n, double* part, h
 
 template <typename T, bool FULL>
 static void obj_points_t(int dim, const T* xr, int64_t Nr, const T* yc, const T* pot, const T* d, int64_t Mc, int nsplit,
-                         double le, const CostArgs& cost, double* part, hipStream_t s) {
+                         double eps, const CostArgs& cost, double* part, hipStream_t s) {
+  const double le = kLog2e / eps, lo = le_rest(eps, le);
   const int64_t cps = ((Mc + nsplit - 1) / nsplit + 7) / 8 * 8;
   const dim3 grid(obj_blocks(Nr), (unsigned)nsplit);
   const double a2 = as_data<T>(cost.kind == 1 ? 0.25 * M_PI * M_PI / (cost.cut * cost.cut) : 0.0);
   const double cut2 = as_data<T>(cost.cut * cost.cut);
   const double kc = as_data<T>(cost.kind == 1 ? 2.0 * kLn2 * le : le);
 #define UOT_OP(D, C) \
-  hipLaunchKernelGGL((k_obj_points<T, D, C, FULL>), grid, dim3(kB), 0, s, xr, Nr, yc, pot, d, Mc, cps, le, kc, a2, cut2, part)
+  hipLaunchKernelGGL((k_obj_points<T, D, C, FULL>), grid, dim3(kB), 0, s, xr, Nr, yc, pot, d, Mc, cps, le, lo, kc, a2, cut2, part)
   if (cost.kind == 1) {
     if (dim == 1) UOT_OP(1, 1);
     else if (dim == 2) UOT_OP(2, 1);
@@ -306,13 +317,12 @@ template <typename T>
 void launch_obj_points(bool full, int dim, const T* xr, int64_t Nr, const T* yc, const T* pot_c, const T* dc, int64_t Mc,
                        int nsplit, double eps, const CostArgs& cost, const T* pot_r, const T* p, const T* dr,
                        const DivDev& F, T* pi_out, double* part, double* out, hipStream_t s) {
-  const double le = kLog2e / eps;
   if (full) {
-    obj_points_t<T, true>(dim, xr, Nr, yc, pot_c, dc, Mc, nsplit, le, cost, part, s);
+    obj_points_t<T, true>(dim, xr, Nr, yc, pot_c, dc, Mc, nsplit, eps, cost, part, s);
     hipLaunchKernelGGL((k_obj_points_finish<T, true>), dim3(obj_blocks(Nr)), dim3(kB), 0, s, part, nsplit, Nr, pot_r, p,
                        dr, eps, F, pi_out, out);
   } else {
-    obj_points_t<T, false>(dim, xr, Nr, yc, pot_c, dc, Mc, nsplit, le, cost, part, s);
+    obj_points_t<T, false>(dim, xr, Nr, yc, pot_c, dc, Mc, nsplit, eps, cost, part, s);
     hipLaunchKernelGGL((k_obj_points_finish<T, false>), dim3(obj_blocks(Nr)), dim3(kB), 0, s, part, nsplit, Nr, pot_r, p,
                        dr, eps, F, pi_out, out);
   }

@@ -160,3 +160,33 @@ def test_fp64_weights_carry_no_bias(kind):
         got = U.solve(prob, eps, tol=0.0, max_iter=1, v0=t[2])[1]
     bias = float(np.mean((got.cpu().numpy().astype(L) - v_ref) / v_ref))
     assert abs(bias) < 1.1e-16, bias
+
+
+@pytest.mark.parametrize("shape", [(256,), (600,), (24, 40), (6, 8, 20)])
+def test_fp64_transport_cost_of_a_near_plan(shape):
+    """FP64 transport cost of a plan along the diagonal (eps at the smallest the line
+    passes take, nearly equal potentials), 1e-2 to 1e-6 of the second moments of
+    its marginals, against 80-bit sums.  A term's exponent, up to X in natural
+    units, is put together from the potentials, log weights, cost and log cost
+    with about 8 roundings of 2^-53 X."""
+    L = np.longdouble
+    rng = np.random.default_rng(9)
+    h = tuple(1.0 / max(shape) for _ in shape)
+    eps = h[0] ** 2 * 1.4427 / 3.5
+    size = int(np.prod(shape))
+    print("case near plan", shape, eps, flush=True)
+    d = np.full(size, float(np.prod(h)))
+    u = eps * (300 + rng.uniform(-2, 2, size))
+    v = eps * (-300 + np.log(1 / d) + rng.uniform(-2, 2, size))
+    prob = U.grid_problem(shape, h, *(T(a, torch.float64) for a in (np.ones(size), np.ones(size), d, d)), U.KL(0.1), U.KL(0.1))
+    got = U.objective(prob, eps, T(u, torch.float64), T(v, torch.float64))
+    C = L(0)
+    for k, n in enumerate(shape):
+        i = np.indices(shape)[k].reshape(-1).astype(L) * L(h[k])
+        C = C + (i[:, None] - i[None, :]) ** 2
+    R = np.exp((L(1) * u[:, None] + v[None, :] - C) / L(eps)) * d[:, None] * L(1) * d[None, :]
+    X = float(np.max(np.abs(u)) + np.max(np.abs(v))) / eps + 60
+    E = 8 * 2.0 ** -53 * X
+    assert got["transport_cost"] == pytest.approx(float((R * C).sum()), rel=E, abs=0)
+    assert got["mass1"] == pytest.approx(float(R.sum()), rel=E, abs=0)
+    assert got["mass2"] == pytest.approx(float(R.sum()), rel=E, abs=0)
