@@ -132,9 +132,11 @@ __device__ __forceinline__ int quot(int a, unsigned r, int d) { return d == 1 ? 
 // The pass over nl lines in buf (line l, tap t at buf[l ldl + t], shifted):
 // the block's waves take the groups of 16 columns and, ksn at a time, the
 // segments; each leaves its partial (m, s) of every output i of a line at
-// pm / ps[(ks nl + l) ldp + i].
-template <typename T, int TS, int NT>
-__device__ __forceinline__ void line_pass(const LineOp<T, TS>& op, const LineShape& S, const T* buf, T* pm, T* ps) {
+// pm / ps[(ks nl + l) ldp + i].  PART: over tiles output tiles from tile0 of one
+// line, outputs counted from there.
+template <typename T, int TS, int NT, bool PART = false>
+__device__ __forceinline__ void line_pass(const LineOp<T, TS>& op, const LineShape& S, const T* buf, T* pm, T* ps,
+                                          int tile0 = 0, int tiles = 0) {
   using N = LineNum<T>;
   using V4 = typename N::V4;
   constexpr int TPL = TS / 4, VB = LineOp<T, TS>::VB;
@@ -142,7 +144,7 @@ __device__ __forceinline__ void line_pass(const LineOp<T, TS>& op, const LineSha
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
   const int q = lane >> 4, li = lane & 15;
   const int ks = wv & (S.ksn - 1), gstep = W >> S.ksh;
-  const int ncol = S.nl * S.nt;
+  const int ncol = PART ? tiles : S.nl * S.nt;
   const int G = (ncol + 15) >> 4;
   T er[4];   // offsets e of the result rows
 #pragma unroll
@@ -150,13 +152,13 @@ __device__ __forceinline__ void line_pass(const LineOp<T, TS>& op, const LineSha
   for (int g = wv >> S.ksh; g < G; g += gstep) {
     const int col = g * 16 + li;
     const int cc = col < ncol ? col : ncol - 1;
-    const int line = S.nl == 1 ? 0 : quot(cc, S.rt, S.nt);
+    const int line = PART || S.nl == 1 ? 0 : quot(cc, S.rt, S.nt);
     const int I = cc - line * S.nt;
     const T* wl = buf + line * S.ldl + VB * q;
     T M[4], R[4];
     // segment seg: al[r] (its shift for row r) and a[r] (its sum)
     auto segment = [&](int seg, T (&al)[4], T (&a)[4]) {
-      const T d = T(seg * TS - I * 16) + T(0.5 * (TS - 1) - 7.5);
+      const T d = T(seg * TS - (PART ? tile0 + I : I) * 16) + T(0.5 * (TS - 1) - 7.5);
       T z[TPL];
       T m = Num<T>::ninf();
 #pragma unroll
@@ -364,6 +366,40 @@ __global__ __launch_bounds__(NT) void k_line(const T* __restrict__ in, int64_t A
   for (int k = 0; k < EPT; ++k)
     if (ok[k]) epi_apply<T>(el[k], line_result<T>(S, pm, ps, l[k], i[k]), xe[k], K, ep, ra);
   epi_finish<T, NT>(ep, ra, (int)grp);
+}
+
+// ---------------------------------------------------------------------------
+// One raw pass of lines as in k_line, few long ones: a block holds one line and
+// takes `tiles` output tiles of it (parts blocks to a line).  One block a line
+// left most of the chip idle: an objective of 3000 cells took 1.31 ms.
+// ---------------------------------------------------------------------------
+template <typename T, int TS, int NT, int EPT>
+__global__ __launch_bounds__(NT) void k_line_part(const T* __restrict__ in, int64_t B, int tiles, unsigned parts,
+                                                  LineShape S, double h2, int side, const Ctrl* __restrict__ c,
+                                                  T* __restrict__ out, int c32) {
+  using Op = LineOp<T, TS>;
+  if (skip_side(c, side)) return;
+  T* const buf = line_lds<T>();
+  T* const pm = buf + S.ldl;
+  T* const ps = pm + S.ksn * S.ldp;
+  const int n = S.n;
+  const unsigned line = blockIdx.x / parts, a = line / (unsigned)B;
+  const int tile0 = (int)(blockIdx.x - line * parts) * tiles;
+  const int64_t base = (int64_t)a * n * B + (line - a * (unsigned)B);
+  const double eps = c->eps[par_of(side)], le = c->le[par_of(side)];
+  Op op;
+  op.init(c32 ? T(line_c<float>(h2, eps, le)) : line_c<T>(h2, eps, le));
+#pragma unroll
+  for (int k = 0; k < EPT; ++k) {
+    const int i = threadIdx.x + k * NT;
+    if (i < n) buf[i] = Op::shifted(in[base + i * B], i, op.c);
+  }
+  line_pad<T, TS, NT>(S, buf);
+  __syncthreads();
+  line_pass<T, TS, NT, true>(op, S, buf, pm, ps, tile0, tiles);
+  __syncthreads();
+  const int i0 = tile0 * 16, cnt = n - i0 < tiles * 16 ? n - i0 : tiles * 16;
+  for (int i = threadIdx.x; i < cnt; i += NT) out[base + (i0 + i) * B] = line_result<T>(S, pm, ps, 0, i);
 }
 
 // ---------------------------------------------------------------------------
@@ -838,13 +874,14 @@ template <typename T> constexpr size_t line_static_lds(int threads) {
 // segment length and LDS shape of a pass over nl lines of n cells:
 // the segments go over the waves when there are fewer groups of 16 columns
 // than waves, in shorter segments if need be
-static void line_shape(int nl, int n, int threads, int ts_max, int ts_min, LineShape& S, int& ts) {
+// (tiles: a block's output tiles where it takes a part of one line)
+static void line_shape(int nl, int n, int threads, int ts_max, int ts_min, LineShape& S, int& ts, int tiles = 0) {
   const int W = threads / 64;
   if (threads == 1024) ts_max = std::min(ts_max, 32);
   S.nl = nl;
   S.n = n;
   S.nt = (n + 15) / 16;
-  const int G = (nl * S.nt + 15) / 16;
+  const int G = ((tiles ? tiles : nl * S.nt) + 15) / 16;
   int ks = 1;
   while (ks < 8 && G * ks * 2 <= W) ks *= 2;
   ts = ts_max;
@@ -855,7 +892,7 @@ static void line_shape(int nl, int n, int threads, int ts_max, int ts_min, LineS
   S.ksh = 0;
   while ((1 << S.ksh) < ks) ++S.ksh;
   S.ldl = S.nseg * ts + 4;
-  S.ldp = S.nt * 16 + 4;
+  S.ldp = (tiles ? tiles : S.nt) * 16 + 4;
   S.rn = (unsigned)(((1ull << 32) + n - 1) / n);
   S.rt = (unsigned)(((1ull << 32) + S.nt - 1) / S.nt);
 }
@@ -900,9 +937,41 @@ static int line_threads(int tot, int64_t blocks) {
     }                                      \
   }
 
+// A raw pass over fewer than 256 lines of more than 16 tiles: parts of a line of
+// at least 16 tiles (a wave's columns), up to 256 blocks
+template <typename T>
+static bool launch_line_part(const T* in, int64_t A, int n, int64_t B, double h, double c_max, int side, const Ctrl* c,
+                             T* out, hipStream_t s, bool c32) {
+  const int64_t lines = A * B;
+  const int nt = (n + 15) / 16;
+  if (nt <= 16 || lines > 128) return false;
+  const int want = (int)std::min<int64_t>((nt + 15) / 16, 256 / lines);
+  const int tiles = ((nt + want - 1) / want + 15) / 16 * 16;
+  if (tiles >= nt) return false;
+  const unsigned parts = (unsigned)((nt + tiles - 1) / tiles), blocks = (unsigned)lines * parts;
+  const int tot = n;
+  const int nthr = line_threads(tot, 1);
+  LineShape S;
+  int ts;
+  line_shape(1, n, nthr, line_ts<T>(c_max), sizeof(T) == 4 ? 8 : 16, S, ts, tiles);
+  const size_t lds = line_lds_bytes<T>(S);
+#define UOT_LN(TS, NT, EPT)                                                                                        \
+  do {                                                                                                             \
+    if constexpr (NT != 256) {                                                                                     \
+      line_big_lds(k_line_part<T, TS, NT, EPT>, lds);                                                              \
+      hipLaunchKernelGGL((k_line_part<T, TS, NT, EPT>), dim3(blocks), dim3(NT), lds, s, in, B, tiles, parts, S,    \
+                         h * h, side, c, out, c32 ? 1 : 0);                                                        \
+    }                                                                                                              \
+  } while (0)
+  UOT_LINE_TS(UOT_LN)
+#undef UOT_LN
+  return true;
+}
+
 template <typename T>
 void launch_line(const T* in, int64_t A, int n, int64_t B, double h, double c_max, int max_blocks, int side,
                  const Ctrl* c, const EpiArgs<T>& ep, hipStream_t s, bool c32) {
+  if (ep.mode == EPI_RAW && launch_line_part<T>(in, A, n, B, h, c_max, side, c, ep.out, s, c32)) return;
   const int lsh = B > 1 ? line_lsh(n, A, B, max_blocks) : line_lsh(n, 1, A, max_blocks);
   const unsigned blocks = (unsigned)(B > 1 ? line_blocks(n, A, B, max_blocks) : line_blocks(n, 1, A, max_blocks));
   const int tot = n << lsh;

@@ -190,3 +190,29 @@ def test_fp64_transport_cost_of_a_near_plan(shape):
     assert got["transport_cost"] == pytest.approx(float((R * C).sum()), rel=E, abs=0)
     assert got["mass1"] == pytest.approx(float(R.sum()), rel=E, abs=0)
     assert got["mass2"] == pytest.approx(float(R.sum()), rel=E, abs=0)
+
+
+@pytest.mark.parametrize("dtype,rel", [(torch.float64, 1e-10), (torch.float32, 2e-5)])
+@pytest.mark.parametrize("shape", [(256,), (257,), (272,), (513,), (1025,), (4096,), (3, 600), (600, 3), (2, 3, 700), (300, 2, 2)])
+def test_objective_of_long_lines(shape, dtype, rel):
+    """Lines whose columns are shared among blocks, against the oracle (FP64 to 1e-10
+    as in test_gpu_parity.py; FP32: the kernel's constant is rounded to 2^-24, of
+    exponents up to 100, and so are the log weights)."""
+    rng = np.random.default_rng(sum(shape))
+    npd = npd_of(dtype)
+    size = int(np.prod(shape))
+    h = tuple(1.0 / max(n, 64) for n in shape)
+    eps = 2e-2
+    print("case objective of long lines", shape, dtype, flush=True)
+    p, q = (rounded(rng.uniform(0.2, 2.0, size), npd) for _ in range(2))
+    d = rounded(np.full(size, float(np.prod(h))), npd)
+    u, v = (rounded(eps * rng.uniform(-3, 3, size), npd) for _ in range(2))
+    F = U.KL(0.3)
+    prob = U.grid_problem(shape, h, *(T(a, dtype) for a in (p, q, d, d)), F, F)
+    got = U.objective(prob, eps, T(u, dtype), T(v, dtype), marginals=True)
+    ref = O.objective(O.GridGeom(shape, h), p, q, d, d, oracle_div(F), oracle_div(F), eps, u, v)
+    for k, r in (("primal", "primal"), ("dual", "dual"), ("transport_cost", "transport_cost"), ("mass1", "mass"),
+                 ("massK", "mK")):
+        assert got[k] == pytest.approx(ref[r], rel=rel, abs=0), k
+    for k in ("pi1", "pi2"):
+        np.testing.assert_allclose(got[k].cpu().double().numpy(), ref[k], rtol=rel)
