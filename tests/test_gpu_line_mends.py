@@ -216,3 +216,25 @@ def test_objective_of_long_lines(shape, dtype, rel):
         assert got[k] == pytest.approx(ref[r], rel=rel, abs=0), k
     for k in ("pi1", "pi2"):
         np.testing.assert_allclose(got[k].cpu().double().numpy(), ref[k], rtol=rel)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("shape", [(40,), (63, 20), (64, 20), (65, 20), (32, 32, 32), (70, 12, 10)])
+def test_half_step_residual(shape, dtype):
+    """The residual of one half-step, from one partial to several hundred.  Partials
+    are FP32 (a rounding per cell and merge, 2^-24 each, averaged over the cells):
+    1e-5 of r, which is of order 1."""
+    rng = np.random.default_rng(sum(shape))
+    npd = npd_of(dtype)
+    size, eps = int(np.prod(shape)), 2e-2
+    h = tuple(1.0 / max(n, 32) for n in shape)
+    print("case half-step residual", shape, dtype, flush=True)
+    p, q = (rounded(rng.uniform(0.2, 2.0, size), npd) for _ in range(2))
+    d = rounded(np.full(size, float(np.prod(h))), npd)
+    pin, pold = (rounded(eps * rng.uniform(-2, 2, size), npd) for _ in range(2))
+    F = U.KL(0.3)
+    prob = U.grid_problem(shape, h, *(T(a, dtype) for a in (p, q, d, d)), F, F)
+    new, S, r = U.half_step(prob, eps, 0, T(pin, dtype), T(pold, dtype))
+    Sr = O.GridGeom(shape, h).lse_x(pin / eps + np.log(d), eps)
+    un = eps * 0.3 / (0.3 + eps) * (np.log(p) - Sr)
+    assert r == pytest.approx(O.marginal_residual(Sr, pold, un, np.log(d), eps), rel=1e-5)
