@@ -342,11 +342,12 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
     // the line passes take every axis or none (squared Euclidean cost, the
     // default choice or grid_kernel 2): what they leave to the older passes
     // is kernels of a few cells (c above their limit), the WF cost, the
-    // direct and FP16 forms asked for by name, and long 1-D grids
+    // direct and FP16 forms asked for by name, long 1-D grids, and few long lines
     P.line = (grid_kernel == 0 || grid_kernel == 2) && g.cost == UOT_COST_SQEUCLID && eps_min > 0;
     for (int k = 0; k < g.dim; ++k) {
       P.c_max[k] = eps_min > 0 ? g.h[k] * g.h[k] * kLog2e / eps_min : INFINITY;
-      P.line = P.line && line_applies(dtype == UOT_F64, P.c_max[k]);
+      P.line = P.line && line_applies(dtype == UOT_F64, P.c_max[k]) &&
+               (g.dim == 1 || nb * (sz / g.n[k]) >= line_min_lines(dtype == UOT_F64, P.tf_axis[k], k == g.dim - 1, g.n[k]));
     }
     // (1-D: one block, for a whole solve of a short line)
     P.loop = P.line && g.dim == 1 && nb == 1 && g.n[0] <= line_loop_max(dtype == UOT_F64);
@@ -418,7 +419,14 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
     // lines of the last axis (2-D) or on planes (3-D)
     P.np_pair_y = P.dim == 2 ? (int)line_blocks((int)P.n[1], P.nb, P.n[0], P.parts_room) : (int)(P.nb * P.n[0]);
     P.pair = P.line && P.np_pair_y <= P.parts_room &&
-             (P.dim == 2 || line_plane_fits(dtype == UOT_F64, P.nb * P.n[0], P.n[1], P.n[2], P.c_max[1], P.c_max[2]));
+             (P.dim == 2 || line_plane_pays(dtype == UOT_F64, P.nb * P.n[0], P.n[1], P.n[2], P.c_max[1], P.c_max[2]));
+    // few large planes in FP32: a pass per launch has no more work than the
+    // older passes' launches hide (us an iteration: 8 x 80 x 80 35.3 / 30.2, 4 x
+    // 65 x 65 32.1 / 29.4; from 20 x 100 x 100 on 44.7 / 64.0)
+    if (P.line && !P.pair && P.dim == 3 && dtype == UOT_F32 && P.n[1] * P.n[2] > 4096 && nb * P.N < 65536) {
+      P.line = false;
+      P.nparts_x = P.nparts_y = grid_final_parts(P);
+    }
   }
   P.o_mass = take(2 * e * std::max(std::max(parts_room, P.nparts_y), 1));
   for (int k = 0; k < 3; ++k) P.o_gtab[k] = take(P.geom == UOT_GEOM_GRID && k < P.dim ? e * (2 * P.n[k] - 1) * nst : 0);

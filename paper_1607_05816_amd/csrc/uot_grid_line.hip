@@ -842,6 +842,24 @@ template <typename T> static int line_ts(double c) {
   return 0;
 }
 
+// Lines along a long axis that a line pass needs to keep up with the passes
+// over parts of lines (0: any number will do), as a block holds a whole line.
+// Measured (us an iteration, these passes / the others; tf: the tile-factored
+// pass takes the axis; last: contiguous):
+//   FP64, last: 24 x 560 51 / 47, 32 x 560 57 / 61, 16 x 850 77 / 60, 32 x 1000 94 / 91,
+//     40 x 2048 303 / 328, 16 x 4096 1070 / 524; first: 4096 x 8 1071 / 2555
+//   FP32 tf, last: 8 x 896 31 / 30, 64 x 1024 34 / 35, 64 x 2048 100 / 79, 72 x 2048 103 /
+//     107, 72 x 4096 364 / 304, 100 x 4096 365 / 415; first: 512 x 8 16 / 23, 896 x 40
+//     36 / 30, 1024 x 64 35 / 29, 1024 x 72 36 / 41, 2048 x 128 105 / 94, 2048 x 150 110 / 131
+//   FP32 else, last: 8 x 1000 33 / 35, 30 x 1500 63 / 55, 64 x 1500 64 / 77, 64 x 2050 148 /
+//     134, 100 x 2050 154 / 185; first: 1500 x 8 63 / 116
+int64_t line_min_lines(bool f64, bool tf, bool last, int64_t n) {
+  if (f64) return last && n > 512 ? (n < 768 ? 32 : 40) : 0;
+  if (tf && last) return n < 1024 ? 0 : n < 3072 ? 72 : 96;
+  if (tf) return n < 704 ? 0 : n < 1536 ? 72 : 144;
+  return last && n > 1024 ? (n <= 2048 ? 56 : 72) : 0;
+}
+
 bool line_applies(bool f64, double c) { return (f64 ? line_ts<double>(c) : line_ts<float>(c)) > 0; }
 
 // Lines per block: one while that gives fewer than 512 blocks (two per
@@ -1080,19 +1098,39 @@ template <typename T> struct PlaneShape {
     lds = sizeof(T) * (lb + 2 * pp);
   }
   bool fits() const { return lds + line_static_lds<T>(nthr) <= kLineLds; }
+  // taps that a wave of the block takes one after another in a pass along each axis
+  int chain() const {
+    auto of = [&](const LineShape& S) {
+      const int G = (S.nl * S.nt + 15) / 16, gw = nthr / 64 / S.ksn;
+      return (G + gw - 1) / gw * ((S.nseg + S.ksn - 1) / S.ksn) * ts;
+    };
+    return of(S1) + of(S2);
+  }
 };
 
-// Thin planes pad their short lines to a segment and to a tile, up to 76
-// elements for a line of a few cells, so it is the bytes that decide, with
-// the two block counts that one plan is launched with (the control step adds
-// a block).
-template <typename T> static bool plane_fits(int64_t blocks, int64_t n1, int64_t n2, double c_max) {
-  return n1 * n2 <= kLineMaxCells && PlaneShape<T>((int)n1, (int)n2, c_max, blocks).fits() &&
-         PlaneShape<T>((int)n1, (int)n2, c_max, blocks + 1).fits();
+// Whether a plane per block pays.  Thin planes pad their short lines to a
+// segment and to a tile, up to 76 elements for a line of a few cells, so the
+// LDS is counted in bytes, for the two block counts that one plan is launched
+// with (the control step adds a block).  A plane's four passes are a chain in
+// one block, which a pass per launch spreads over the chip.  Measured (us an
+// iteration, paired / a pass per launch): FP32 chains of up to 128 taps 23.6 /
+// 29.0 (8 x 48 x 48) and 26.1 / 26.9 (4 x 64 x 64), of 136 38.7 / 27.4 (4 x 8 x 256),
+// of 272 66.7 / 31.2 (16 x 16 x 256).  FP64 (four elements a thread spill, 221
+// registers): 1024 cells and chains of up to 64 taps 55.8 / 61.6 (64 x 20 x 48) and
+// 41.3 / 48.5 (64 x 32 x 32), beyond either 45.3 / 35.0 (4 x 30 x 40), 79.4 / 58.3
+// (64 x 4 x 200), 91.6 / 32.7 (4 x 64 x 64).
+template <typename T> static bool plane_pays(int64_t blocks, int64_t n1, int64_t n2, double c_max) {
+  constexpr bool f32 = sizeof(T) == 4;
+  if (n1 * n2 > (f32 ? kLineMaxCells : 1024)) return false;
+  for (int host = 0; host < 2; ++host) {
+    const PlaneShape<T> sh((int)n1, (int)n2, c_max, blocks + host);
+    if (!sh.fits() || sh.chain() > (f32 ? 128 : 64)) return false;
+  }
+  return true;
 }
-bool line_plane_fits(bool f64, int64_t planes, int64_t n1, int64_t n2, double c1_max, double c2_max) {
+bool line_plane_pays(bool f64, int64_t planes, int64_t n1, int64_t n2, double c1_max, double c2_max) {
   const double c = std::max(c1_max, c2_max);
-  return f64 ? plane_fits<double>(planes, n1, n2, c) : plane_fits<float>(planes, n1, n2, c);
+  return f64 ? plane_pays<double>(planes, n1, n2, c) : plane_pays<float>(planes, n1, n2, c);
 }
 
 template <typename T>
@@ -1107,7 +1145,8 @@ void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1
   const EpiArgs<T> none{};
 #define UOT_LN(TS, NT, EPT)                                                                                         \
   do {                                                                                                              \
-    if (ep) {                                                                                                       \
+    if constexpr (sizeof(T) == 8 && NT * EPT > 1024) {                                                              \
+    } else if (ep) {                                                                                                \
       line_big_lds(k_plane_pair<T, TS, NT, EPT, true>, lds);                                                        \
       hipLaunchKernelGGL((k_plane_pair<T, TS, NT, EPT, true>), dim3(blocks), dim3(NT), lds, s, in, n0, S1, S2,      \
                          h1 * h1, h2 * h2, side, c, *ep, out);                                                      \

@@ -254,6 +254,9 @@ void launch_grid_tf(const float* in, int64_t A, int n, int64_t B, bool strided, 
 // blocks over `groups` groups of `per` lines of n cells, at most max_blocks
 // where lines of 16 cells or more allow it
 bool line_applies(bool f64, double c);
+// lines along an axis of n cells (last: contiguous; tf: the tile-factored pass
+// takes it) below which the other passes are faster
+int64_t line_min_lines(bool f64, bool tf, bool last, int64_t n);
 int64_t line_blocks(int n, int64_t groups, int64_t per, int max_blocks);
 // one pass over A x n x B cells with the epilogue ep (c32: c rounded to FP32)
 template <typename T>
@@ -271,8 +274,9 @@ template <typename T>
 void launch_line_bary(const T* in, int64_t F, int64_t R, int n, double h, double c_max, int side, const Ctrl* c,
                       const EpiArgs<T>& ep, T* out, const BaryW& bw, hipStream_t s);
 // the last two axes of F fields of n0 x n1 x n2 cells, a plane per block;
-// line_plane_fits: whether the LDS of a launch over `planes` of them holds one
-bool line_plane_fits(bool f64, int64_t planes, int64_t n1, int64_t n2, double c1_max, double c2_max);
+// line_plane_pays: whether a launch over `planes` of them can hold one and is
+// faster than a pass per launch
+bool line_plane_pays(bool f64, int64_t planes, int64_t n1, int64_t n2, double c1_max, double c2_max);
 template <typename T>
 void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1, double h2, double c1_max,
                        double c2_max, int side, const Ctrl* c, const EpiArgs<T>* ep, T* out, hipStream_t s);

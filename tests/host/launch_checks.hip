@@ -4,6 +4,7 @@
 //   launch_checks planes   solves over the planes that one block may hold
 //   launch_checks barycenters   ... over the rows of several fields that it may hold
 // print the largest dynamic LDS that each kernel was launched with;
+//   launch_checks routes   the pass kernels of solves on either side of the rules
 //   launch_checks failing   a launch that fails is reported by its own call and
 //                           leaves no error behind
 // Built host-only (tests/test_line_launches_cpu.py).
@@ -303,6 +304,24 @@ static void failing() {
       }
 }
 
+// the pass kernels a solve launches
+static void route(int dtype, const uot_geom& g, double c) {
+  g_seen.clear();
+  solve(dtype, g, 1, c);
+  std::printf("route %s:", g_shape.c_str());
+  for (const OffloadEntry* e = __start_llvm_offload_entries; e != __stop_llvm_offload_entries; ++e)
+    if (g_seen.count(e->address) && (std::strstr(e->name, "k_line") || std::strstr(e->name, "k_plane") || std::strstr(e->name, "k_grid")))
+      std::printf(" %s", e->name);
+  std::printf("\n");
+}
+static void routes() {
+  for (int dt : {UOT_F32, UOT_F64})
+    for (const uot_geom& g : {grid(2, 8, 512, 0), grid(2, 8, 2048, 0), grid(2, 200, 2048, 0), grid(2, 2048, 8, 0), grid(2, 8, 2050, 0),
+                              grid(2, 2050, 8, 0), grid(3, 8, 32, 32), grid(3, 8, 64, 64), grid(3, 8, 16, 256), grid(3, 8, 80, 80),
+                              grid(3, 30, 80, 80)})
+      route(dt, g, 0.01);
+}
+
 int main(int argc, char** argv) {
   if (argc < 2 || uot_create(&ctx, nullptr) != UOT_OK) return 2;
   const std::string what = argv[1];
@@ -310,6 +329,7 @@ int main(int argc, char** argv) {
   if (what == "planes") planes();
   if (what == "barycenters") barycenters();
   if (what == "failing") failing();
+  else if (what == "routes") routes();
   else print_lds();
   uot_destroy(ctx);
   if (failures) {

@@ -238,3 +238,26 @@ def test_half_step_residual(shape, dtype):
     Sr = O.GridGeom(shape, h).lse_x(pin / eps + np.log(d), eps)
     un = eps * 0.3 / (0.3 + eps) * (np.log(p) - Sr)
     assert r == pytest.approx(O.marginal_residual(Sr, pold, un, np.log(d), eps), rel=1e-5)
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("shape", [(31, 560), (32, 560), (8, 1030), (8, 1024), (1024, 9), (2050, 3), (4, 30, 40), (8, 16, 256),
+                                   (2, 65, 65)])
+def test_solves_beside_the_line_rules(shape, dtype):
+    """Grids on both sides of where the line passes are taken (few long lines, planes
+    of long chains), against the oracle."""
+    eps = 1e-2
+    rng = np.random.default_rng(sum(shape))
+    size = int(np.prod(shape))
+    h = tuple(1.0 / max(n, 64) for n in shape)
+    p, q = (rounded(rng.uniform(0.2, 2.0, size), npd_of(dtype)) for _ in range(2))
+    d = rounded(np.full(size, float(np.prod(h))), npd_of(dtype))
+    F = U.KL(0.1)
+    print("case beside the line rules", shape, dtype, flush=True)
+    prob = U.grid_problem(shape, h, *(T(a, dtype) for a in (p, q, d, d)), F, F)
+    u, v, info = U.solve(prob, eps, eps0=0.1, eps_stages=2, iters_per_stage=2, tol=0.0, max_iter=7)
+    ref = O.solve(O.GridGeom(shape, h), np.log(p), np.log(q), np.log(d), np.log(d), oracle_div(F), oracle_div(F), eps,
+                  tol=0.0, max_iter=7, eps0=0.1, n_stages=2, iters_per_stage=2)
+    assert info["iters"] == 7
+    assert pot_rel_err(u.cpu(), ref["u"], eps) < TOL[dtype]
+    assert pot_rel_err(v.cpu(), ref["v"], eps) < TOL[dtype]

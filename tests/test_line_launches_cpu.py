@@ -79,3 +79,25 @@ def test_a_failing_launch_is_reported_by_its_call(driver):
     the next one, and the context goes on working."""
     rc, out = _run([driver, "failing"], timeout=300)
     assert rc == 0 and "launch checks passed" in out, out
+
+
+# where the line passes are the faster ones (see line_min_lines, line_plane_pays):
+# L lines, P lines and planes in pairs, S a line pass per launch, - the other passes
+ROUTES = {
+    "f32": {(8, 512): "L", (8, 2048): "-", (200, 2048): "L", (2048, 8): "-", (8, 2050): "-", (2050, 8): "L",
+            (8, 32, 32): "P", (8, 64, 64): "P", (8, 16, 256): "S", (8, 80, 80): "-", (30, 80, 80): "S"},
+    "f64": {(8, 512): "L", (8, 2048): "-", (200, 2048): "L", (2048, 8): "L", (8, 2050): "-", (2050, 8): "L",
+            (8, 32, 32): "P", (8, 64, 64): "S", (8, 16, 256): "S", (8, 80, 80): "S", (30, 80, 80): "S"},
+}
+
+
+def test_routes_of_grid_solves(driver):
+    rc, out = _run([driver, "routes"], timeout=300)
+    assert rc == 0 and "launch checks passed" in out, out
+    got = {"f32": {}, "f64": {}}
+    for m in re.finditer(r"route solve (f\d\d) (\d+)x(\d+)x(\d+) \S+ \d+ c \S+:(.*)", out):
+        shape = tuple(int(x) for x in m.group(2, 3, 4) if x != "0")
+        names = m.group(5)
+        got[m.group(1)][shape] = ("P" if "k_plane_pair" in names else "L" if "k_line_pair" in names
+                                  else "S" if "6k_lineI" in names else "-")
+    assert got == ROUTES
