@@ -1504,8 +1504,17 @@ int bary_t(uot_ctx* ctx, const uot_bary_problem* pb, const uot_params* pr, T* u,
   hipStream_t s = ctx->work;
   if ((rc = begin(ctx))) return rc;
   // paired line passes: the combine runs between the passes of a row's fields
-  const bool pair = P.pair && P.dim == 2 &&
-                    line_bary_fits(pb->dtype == UOT_F64, pb->n, P.n[0], (int)P.n[1], P.c_max[1]);
+  bool pair = P.pair && P.dim == 2 &&
+              line_bary_fits(pb->dtype == UOT_F64, pb->n, P.n[0], (int)P.n[1], P.c_max[1]);
+  if (pair && (pb->F2.kind == UOT_DIV_TV || pb->F2.kind == UOT_DIV_RG)) {
+    const int passes = line_bary_root_passes(pb->dtype == UOT_F64, pb->n, P.n[0], (int)P.n[1],
+                                             pb->F2.kind == UOT_DIV_TV || pb->F2.alpha > 0, P.tf_axis[0] && P.tf_axis[1]);
+    pair = passes == 2;
+    if (passes == 0) {
+      P.line = P.pair = false;
+      P.nparts_x = P.nparts_y = grid_final_parts(P);
+    }
+  }
   Bufs<T> B = carve<T>(P, ws);
   const int64_t size = P.N, nb = pb->n;
   const bool mixed = P.gk == 4 && has_tf16(P) && pr->tol < kMixedSwitchTol;

@@ -50,6 +50,15 @@ __device__ __forceinline__ T bary_fa(const T* t2, int64_t stride, int n, const B
   return acc;
 }
 
+// lanes per cell: one to a breakpoint, up to a wave (two_breaks: TV, RG with a
+// lower bound)
+__host__ __device__ inline int bary_lanes(int nm, bool two_breaks) {
+  const int nbp = two_breaks ? 2 * nm : nm;
+  int L = 2;
+  while (L < nbp && L < 64) L *= 2;
+  return L;
+}
+
 // log h of TV / RG at one cell, by L lanes (a power of two; sub: this lane's
 // index among them; every lane of the wave calls it): t2[k stride] = log2 s_k
 template <typename T>

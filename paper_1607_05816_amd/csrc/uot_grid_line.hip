@@ -537,9 +537,7 @@ __global__ __launch_bounds__(NT, NT == 1024 || (sizeof(T) == 4 && NT == 256 && T
     const bool root = ep.F.kind == 2 || ep.F.kind == 3;
     if (root) {
       // L lanes to a cell; lanes past the last cell repeat it
-      const int nbp = S.nl * ((ep.F.kind == 2 || ep.F.has_lo) ? 2 : 1);
-      int L = 2;
-      while (L < nbp && L < 64) L *= 2;
+      const int L = bary_lanes(S.nl, ep.F.kind == 2 || ep.F.has_lo);
       const int sub = threadIdx.x & (L - 1);
       for (int j0 = 0; j0 < n; j0 += NT / L) {
         const int j = j0 + (int)threadIdx.x / L;
@@ -1056,6 +1054,28 @@ template <typename T> static bool bary_fits(int64_t F, int64_t R, int n, double 
 }
 bool line_bary_fits(bool f64, int64_t F, int64_t R, int n, double c_max) {
   return f64 ? bary_fits<double>(F, R, n, c_max) : bary_fits<float>(F, R, n, c_max);
+}
+
+// Passes of a barycentre whose combine finds a root (TV, RG) over F inputs of
+// R x n cells.  A block of the paired pass holds a row's n cells and searches
+// them in rounds of NT / L, every round 2 F evaluations of F terms (bary_root),
+// while the combine of its own launch spreads all cells over the chip: pairing
+// wins while the rounds are few, or while a few inputs of many cells make the
+// transposed store of the products the dearer part.  Where it does not, a pass
+// per launch, except on the smallest grids, whose time is that of their
+// launches and whose older passes (FP32: tile-factored axes, tf) take fewer
+// cells a block.  Measured (us an iteration, TV, paired / a pass per launch /
+// older passes): FP32 16 x 64 x 64 33.1 / 37.0 / 35.2, 10 x 112 x 112 46.0 / 40.5 /
+// 40.2, 48 x 64 x 64 147 / 80 / 83, 10 x 80 x 80 40.0 / 41.5 / 33.1, 30 x 64 x 64 - /
+// 57.1 / 53.4, 20 x 50 x 50 - / 48.4 / 47.3, 10 x 150 x 150 65.5 / 70.3 / 95.6; FP64 8 x 64 x 64 35.4 / 37.3 / 41.0, 24 x 96 x 96 176 / 112 /
+// 214, 12 x 48 x 48 57.4 / 55.5 / 51.7, 12 x 160 x 160 153 / 167 / 373.
+int line_bary_root_passes(bool f64, int64_t F, int64_t R, int n, bool two_breaks, bool tf) {
+  const int64_t cells = F * R * n;
+  const int L = bary_lanes((int)F, two_breaks), NT = line_threads((int)F * n, R);
+  const int64_t rounds = (n + NT / L - 1) / (NT / L), evals = rounds * F;
+  const bool many = evals >= (f64 ? 24 : rounds > 2 ? 30 : 48);
+  if (!many || (F <= 12 && cells >= 200000)) return 2;
+  return cells < (!f64 && tf ? 130000 : 56000) ? 0 : 1;
 }
 
 template <typename T>

@@ -1892,9 +1892,7 @@ template <typename T>
 void launch_bary_combine(const T* T2, int nm, int64_t size, const BaryW& la, const DivDev& F2, const T* logdy, T* v, T* w, T* logh, const Ctrl* c, int side,
                          hipStream_t s) {
   if (F2.kind == 2 || F2.kind == 3) {
-    const int nbp = nm * ((F2.kind == 2 || F2.has_lo) ? 2 : 1);
-    int L = 2;
-    while (L < nbp && L < 64) L *= 2;
+    const int L = bary_lanes(nm, F2.kind == 2 || F2.has_lo);
     const unsigned blocks = ceil_div(size * L, kBlock);
 #define UOT_BR(LL)                                                                                               \
   hipLaunchKernelGGL((k_bary_root<T, LL>), dim3(blocks), dim3(kBlock), 0, s, T2, nm, size, la, F2, logdy, v, w, \

@@ -270,6 +270,10 @@ void launch_line_pair(const T* in, int64_t F, int64_t R, int n, double h, double
 // ... with the barycentre combine over the F fields as the epilogue, a block
 // per row; line_bary_fits: whether its LDS holds the F lines of a row
 bool line_bary_fits(bool f64, int64_t F, int64_t R, int n, double c_max);
+// the passes of a barycentre of TV / RG that fits: 2 paired, 1 one per launch,
+// 0 the older ones (two_breaks: TV, RG with a lower bound; tf: the
+// tile-factored passes take both axes)
+int line_bary_root_passes(bool f64, int64_t F, int64_t R, int n, bool two_breaks, bool tf);
 template <typename T>
 void launch_line_bary(const T* in, int64_t F, int64_t R, int n, double h, double c_max, int side, const Ctrl* c,
                       const EpiArgs<T>& ep, T* out, const BaryW& bw, hipStream_t s);

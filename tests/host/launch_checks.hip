@@ -173,8 +173,8 @@ static void solve(int dtype, const uot_geom& g, int nb, double c) {
     EXPECT(uot_solve_fields(ctx, &pb, nb, &pr, kDev, kDev, kDev, n, &res) == UOT_OK);
   }
 }
-static void barycenter(int dtype, const uot_geom& g, int nb, double c) {
-  note("barycentre", dtype, g, nb, c);
+static void barycenter(int dtype, const uot_geom& g, int nb, double c, int kind = UOT_DIV_KL, double alpha2 = 0.0) {
+  note(kind == UOT_DIV_KL ? "barycentre KL" : kind == UOT_DIV_TV ? "barycentre TV" : "barycentre RG", dtype, g, nb, c);
   static const std::vector<double> alpha(64, 1.0);
   uot_bary_problem bp;
   std::memset(&bp, 0, sizeof(bp));
@@ -185,6 +185,9 @@ static void barycenter(int dtype, const uot_geom& g, int nb, double c) {
   bp.alpha = alpha.data();
   bp.F1.kind = bp.F2.kind = UOT_DIV_KL;
   bp.F1.lambda = bp.F2.lambda = 0.1;
+  bp.F2.kind = kind;
+  bp.F2.alpha = alpha2;
+  bp.F2.beta = 1.3;
   uot_params pr = params(c);
   uot_result res;
   size_t n = 0;
@@ -304,10 +307,10 @@ static void failing() {
       }
 }
 
-// the pass kernels a solve launches
-static void route(int dtype, const uot_geom& g, double c) {
+// the pass kernels a call launches
+template <typename Call> static void route(Call&& call) {
   g_seen.clear();
-  solve(dtype, g, 1, c);
+  call();
   std::printf("route %s:", g_shape.c_str());
   for (const OffloadEntry* e = __start_llvm_offload_entries; e != __stop_llvm_offload_entries; ++e)
     if (g_seen.count(e->address) && (std::strstr(e->name, "k_line") || std::strstr(e->name, "k_plane") || std::strstr(e->name, "k_grid")))
@@ -319,7 +322,18 @@ static void routes() {
     for (const uot_geom& g : {grid(2, 8, 512, 0), grid(2, 8, 2048, 0), grid(2, 200, 2048, 0), grid(2, 2048, 8, 0), grid(2, 8, 2050, 0),
                               grid(2, 2050, 8, 0), grid(3, 8, 32, 32), grid(3, 8, 64, 64), grid(3, 8, 16, 256), grid(3, 8, 80, 80),
                               grid(3, 30, 80, 80)})
-      route(dt, g, 0.01);
+      route([&] { solve(dt, g, 1, 0.01); });
+  const int bary[][3] = {{2, 64, 64}, {8, 50, 50}, {10, 80, 80}, {10, 81, 81}, {10, 150, 150}, {12, 48, 48}, {16, 64, 64},
+                         {20, 50, 50}, {24, 20, 40}, {24, 96, 96}, {30, 64, 64}, {33, 40, 60}, {60, 32, 32}};
+  for (int dt : {UOT_F32, UOT_F64})
+    for (const auto& b : bary) {
+      const uot_geom g = grid(2, b[1], b[2], 0);
+      route([&] { barycenter(dt, g, b[0], 0.01, UOT_DIV_TV); });
+      if (b[0] == 12 || b[0] == 24) {
+        route([&] { barycenter(dt, g, b[0], 0.01, UOT_DIV_KL); });
+        route([&] { barycenter(dt, g, b[0], 0.01, UOT_DIV_RG); });
+      }
+    }
 }
 
 int main(int argc, char** argv) {

@@ -261,3 +261,28 @@ def test_solves_beside_the_line_rules(shape, dtype):
     assert info["iters"] == 7
     assert pot_rel_err(u.cpu(), ref["u"], eps) < TOL[dtype]
     assert pot_rel_err(v.cpu(), ref["v"], eps) < TOL[dtype]
+
+
+@pytest.mark.parametrize("dtype", DTYPES)
+@pytest.mark.parametrize("F2", [U.TV(0.1), U.RG(0.7, 1.3), U.RG(0.0, 1.3)])
+@pytest.mark.parametrize("shape,nb", [((16, 64), 16), ((20, 40), 24), ((48, 48), 12), ((40, 60), 33)])
+def test_barycenter_root_passes(shape, nb, F2, dtype):
+    """Barycentres whose combine finds a root, on either side of where it runs
+    between paired line passes; bounds as in test_barycenter_matches_oracle."""
+    eps = 5e-3
+    rng = np.random.default_rng(nb)
+    size = int(np.prod(shape))
+    h = tuple(1.0 / max(n, 64) for n in shape)
+    p = rounded(rng.uniform(0.5, 2.3, (nb, size)), npd_of(dtype))
+    d = rounded(np.full(size, float(np.prod(h))), npd_of(dtype))
+    alpha = np.arange(1, nb + 1) / (nb * (nb + 1) / 2)
+    F1 = U.KL(0.2)
+    print("case barycentre root", shape, nb, F2, dtype, flush=True)
+    u, v, logh, _ = U.barycenter(shape, h, T(p, dtype), alpha, T(d, dtype), T(d, dtype), F1, F2, eps, tol=0.0,
+                                 max_iter=6)
+    ref = O.barycenter(O.GridGeom(shape, h), np.log(p), alpha, np.log(d), np.log(d), oracle_div(F1), oracle_div(F2),
+                       eps, tol=0.0, max_iter=6)
+    # (a range may be met exactly before the sixth iteration: the solve stops there)
+    assert pot_rel_err(u.cpu(), ref["u"], eps) < TOL[dtype]
+    assert pot_rel_err(v.cpu(), ref["v"], eps) < TOL[dtype]
+    assert np.max(np.abs(logh.cpu().numpy() - ref["logh"])) / np.max(np.abs(ref["logh"])) < 10 * TOL[dtype]

@@ -91,13 +91,49 @@ ROUTES = {
 }
 
 
-def test_routes_of_grid_solves(driver):
+@pytest.fixture(scope="module")
+def routes(driver):
     rc, out = _run([driver, "routes"], timeout=300)
     assert rc == 0 and "launch checks passed" in out, out
+    return out
+
+
+def test_routes_of_grid_solves(routes):
     got = {"f32": {}, "f64": {}}
-    for m in re.finditer(r"route solve (f\d\d) (\d+)x(\d+)x(\d+) \S+ \d+ c \S+:(.*)", out):
+    for m in re.finditer(r"route solve (f\d\d) (\d+)x(\d+)x(\d+) \S+ \d+ c \S+:(.*)", routes):
         shape = tuple(int(x) for x in m.group(2, 3, 4) if x != "0")
         names = m.group(5)
         got[m.group(1)][shape] = ("P" if "k_plane_pair" in names else "L" if "k_line_pair" in names
                                   else "S" if "6k_lineI" in names else "-")
     assert got == ROUTES
+
+
+# ... and the paired passes with the combine among them (line_bary_root_passes): B paired,
+# S a line pass per launch, - the other passes
+BARY_ROUTES = {
+    "f32": {(2, 64, 64): "B", (8, 50, 50): "B", (10, 80, 80): "-", (10, 81, 81): "S", (10, 150, 150): "B", (12, 48, 48): "B",
+            (16, 64, 64): "B", (20, 50, 50): "-", (24, 20, 40): "-", (24, 96, 96): "S", (30, 64, 64): "-",
+            (33, 40, 60): "S", (60, 32, 32): "-"},
+    "f64": {(2, 64, 64): "B", (8, 50, 50): "B", (10, 80, 80): "S", (10, 81, 81): "S", (10, 150, 150): "B", (12, 48, 48): "-",
+            (16, 64, 64): "S", (20, 50, 50): "-", (24, 20, 40): "-", (24, 96, 96): "S", (30, 64, 64): "S",
+            (33, 40, 60): "S", (60, 32, 32): "S"},
+}
+
+
+def test_routes_of_barycenters(routes):
+    got = {"f32": {}, "f64": {}}
+    others = {}
+    for m in re.finditer(r"route barycentre (\S+) (f\d\d) (\d+)x(\d+)x\S+ fields (\d+) c \S+:(.*)", routes):
+        kind, dtype, n0, n1, nb = m.group(1), m.group(2), *(int(x) for x in m.group(3, 4, 5))
+        names = m.group(6)
+        way = "B" if re.search(r"k_line_pairI\S+Li2EE", names) else "S" if "6k_lineI" in names else "-"
+        if kind == "TV":
+            got[dtype][nb, n0, n1] = way
+        else:
+            others[kind, dtype, nb, n0, n1] = way
+    assert got == BARY_ROUTES
+    # a mean needs no search; a range without a lower bound has one breakpoint an input
+    for dtype in ("f32", "f64"):
+        assert others["KL", dtype, 24, 96, 96] == "B" and others["KL", dtype, 24, 20, 40] == "B"
+        assert others["RG", dtype, 24, 96, 96] == "S"
+    assert others["RG", "f64", 24, 20, 40] == "-" and others["RG", "f64", 12, 48, 48] == "B"
