@@ -338,7 +338,7 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
       P.band[k] = (int)g.n[k];
       if (g.cost == UOT_COST_WF) P.band[k] = (int)std::min<double>((double)g.n[k], std::ceil(g.cut / g.h[k]));
     }
-    if (g.dim == 1) P.split1d = grid_contig_splits((int)g.n[0], nb, P.band[0]);
+    if (g.dim == 1) P.split1d = grid_contig_splits(dtype == UOT_F64, (int)g.n[0], nb, P.band[0]);
     // the line passes take every axis or none (squared Euclidean cost, the
     // default choice or grid_kernel 2): what they leave to the older passes
     // is kernels of a few cells (c above their limit), the WF cost, the

@@ -1504,7 +1504,7 @@ void launch_grid_contig(const T* in, int64_t A, int n, const T* gtab, int side, 
 
 // tap slices for few long lines (A x ceil(n/64) blocks well below the chip's
 // width): enough slices for ~2048 blocks, each slice at least 256 taps
-int grid_contig_splits(int n, int64_t A, int band) {
+int grid_contig_splits(bool f64, int n, int64_t A, int band) {
   const int bd = (band < 1 || band > n) ? n : band;
   const int64_t blocks1 = (int64_t)ceil_div(n, 64) * A;
   if (blocks1 >= 1024 || A > 65535) return 1;
@@ -1513,13 +1513,18 @@ int grid_contig_splits(int n, int64_t A, int band) {
   const int64_t maxsp = std::max(1, taps / 256);
   sp = std::max<int64_t>(1, std::min(sp, maxsp));
   // among up to that many slices, the ones whose blocks, dealt to 256 compute
-  // units, leave the busiest with the least: its blocks times their taps (and some
-  // 64 more for a block's set-up).  3000 cells in FP64: 11 slices are 517 blocks,
-  // three on five of the units, and took 16.6 us; 10, with their taps in LDS,
-  // take 14.9 us.
+  // units, leave the busiest done first: r blocks of t taps that share a unit hide
+  // part of each other's latency, as if one more ran beside them, of 1/5 a block
+  // in FP64 (issue bound) and of 2 in FP32 (latency bound).  Measured (us an
+  // iteration, WF lines, the most slices / the ones taken): FP64 3000 cells, 11
+  // slices are 517 blocks, three on five of the units, 44.0 / 38.3 with 10; 4096
+  // cells 52.4 with all 16 (55.8 with 8); 2500 36.2 / 33.6 with 6.  Over 51
+  // sizes and two cuts FP64 is 0.5 % and FP32 0.8 % above the best (the most
+  // slices: 3.5 and 1.9 %).
   int64_t best = sp, least = INT64_MAX;
   for (int64_t k = sp; k >= std::max<int64_t>(1, sp / 2); --k) {
-    const int64_t cost = (blocks1 * k + 255) / 256 * ((taps + k - 1) / k + 64);
+    const int64_t r = (blocks1 * k + 255) / 256, t = (taps + k - 1) / k;
+    const int64_t cost = (f64 ? 5 * r + 1 : r + 2) * t;
     if (cost < least) {
       least = cost;
       best = k;

@@ -5,6 +5,7 @@
 //   launch_checks barycenters   ... over the rows of several fields that it may hold
 // print the largest dynamic LDS that each kernel was launched with;
 //   launch_checks routes   the pass kernels of solves on either side of the rules
+//   launch_checks slices   the tap slices of lines
 //   launch_checks failing   a launch that fails is reported by its own call and
 //                           leaves no error behind
 // Built host-only (tests/test_line_launches_cpu.py).
@@ -27,6 +28,7 @@ namespace {
 struct Seen {
   size_t lds = 0;
   std::string shape;
+  dim3 grid;               // of its last launch
 };
 std::map<const void*, Seen> g_seen;
 std::string g_shape;          // what the driver is running
@@ -52,8 +54,9 @@ hipError_t __hipPopCallConfiguration(dim3* g, dim3* b, size_t* lds, hipStream_t*
   *s = nullptr;
   return hipSuccess;
 }
-hipError_t hipLaunchKernel(const void* f, dim3, dim3, void**, size_t lds, hipStream_t) {
+hipError_t hipLaunchKernel(const void* f, dim3 grid, dim3, void**, size_t lds, hipStream_t) {
   Seen& s = g_seen[f];
+  s.grid = grid;
   if (lds > s.lds || s.shape.empty()) {
     s.lds = lds;
     s.shape = g_shape;
@@ -336,6 +339,24 @@ static void routes() {
     }
 }
 
+// the tap slices of lines under the WF cost
+static void slices() {
+  for (int dt : {UOT_F32, UOT_F64})
+    for (int nb : {1, 2, 3, 5})
+      for (int n : {700, 1500, 2500, 3000, 4000, 4096})
+        for (double cut : {0.3, 4.0}) {
+          uot_geom g = grid(1, n, 0, 0);
+          g.cost = UOT_COST_WF;
+          g.cut = cut * n / 64;
+          g_seen.clear();
+          solve(dt, g, nb, 0.01);
+          for (const OffloadEntry* e = __start_llvm_offload_entries; e != __stop_llvm_offload_entries; ++e)
+            if (g_seen.count(e->address) && std::strstr(e->name, "k_grid_contig"))
+              std::printf("slices f%d fields %d cells %d cut %g: %u\n", dt == UOT_F32 ? 32 : 64, nb, n, cut,
+                          g_seen[e->address].grid.z);
+        }
+}
+
 int main(int argc, char** argv) {
   if (argc < 2 || uot_create(&ctx, nullptr) != UOT_OK) return 2;
   const std::string what = argv[1];
@@ -343,6 +364,7 @@ int main(int argc, char** argv) {
   if (what == "planes") planes();
   if (what == "barycenters") barycenters();
   if (what == "failing") failing();
+  else if (what == "slices") slices();
   else if (what == "routes") routes();
   else print_lds();
   uot_destroy(ctx);

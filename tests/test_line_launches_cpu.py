@@ -137,3 +137,24 @@ def test_routes_of_barycenters(routes):
         assert others["KL", dtype, 24, 96, 96] == "B" and others["KL", dtype, 24, 20, 40] == "B"
         assert others["RG", dtype, 24, 96, 96] == "S"
     assert others["RG", "f64", 24, 20, 40] == "-" and others["RG", "f64", 12, 48, 48] == "B"
+
+
+# tap slices of WF lines (grid_contig_splits) where one count was measured ahead of its
+# neighbours: (fields, cells, cut in lengths of the line)
+SLICES = {
+    "f32": {(1, 3000, 0.3): 7, (1, 4096, 0.3): 8, (1, 4096, 4.0): 16},
+    "f64": {(1, 2500, 4.0): 6, (1, 3000, 0.3): 5, (1, 3000, 4.0): 10, (1, 4096, 0.3): 8, (1, 4096, 4.0): 16,
+            (2, 3000, 4.0): 8, (2, 4000, 4.0): 14, (5, 4000, 4.0): 4},
+}
+
+
+def test_slices_of_lines(driver):
+    rc, out = _run([driver, "slices"], timeout=300)
+    assert rc == 0 and "launch checks passed" in out, out
+    got = {"f32": {}, "f64": {}}
+    for m in re.finditer(r"slices (f\d\d) fields (\d+) cells (\d+) cut (\S+): (\d+)", out):
+        got[m.group(1)][int(m.group(2)), int(m.group(3)), float(m.group(4))] = int(m.group(5))
+    for dtype, want in SLICES.items():
+        assert len(got[dtype]) == 48
+        for key, k in want.items():
+            assert got[dtype][key] == k, (dtype, key)
