@@ -1161,11 +1161,12 @@ void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1
   const PlaneShape<T> sh(n1, n2, std::max(c1_max, c2_max), blocks);
   const LineShape &S1 = sh.S1, &S2 = sh.S2;
   const int ts = sh.ts, nthr = sh.nthr;
+  // (FP64: planes of up to 1024 cells, whose chains rule out 32 taps over 1024 threads)
   const size_t lds = sh.lds;
   const EpiArgs<T> none{};
 #define UOT_LN(TS, NT, EPT)                                                                                         \
   do {                                                                                                              \
-    if constexpr (sizeof(T) == 8 && NT * EPT > 1024) {                                                              \
+    if constexpr (sizeof(T) == 8 && (NT * EPT > 1024 || (TS > 16 && NT == 1024))) {                                 \
     } else if (ep) {                                                                                                \
       line_big_lds(k_plane_pair<T, TS, NT, EPT, true>, lds);                                                        \
       hipLaunchKernelGGL((k_plane_pair<T, TS, NT, EPT, true>), dim3(blocks), dim3(NT), lds, s, in, n0, S1, S2,      \
@@ -1185,7 +1186,7 @@ void launch_plane_pair(const T* in, int64_t F, int n0, int n1, int n2, double h1
 // Measured (us per iteration, this kernel / the launches): FP32 64 cells 3.4 /
 // 11.9, 256 4.3 / 15.5, 512 7.2 / 21.2, 768 17.3 / 22.4, 1024 26.3 / 22.7; FP64
 // 64 5.3 / 15.5, 256 9.2 / 23.9, 512 22.2 / 31.2, 768 50.2 / 31.9.
-int line_loop_max(bool f64) { return f64 ? 512 : 768; }
+int line_loop_max(bool f64) { return f64 ? 512 : 768; }   // (512 threads, in FP32 up to 1024)
 
 template <typename T>
 void launch_line_loop(int n, double h, double c_max, Ctrl* c, const EpiArgs<T>& ex, const EpiArgs<T>& ey, double* hist,
@@ -1197,7 +1198,7 @@ void launch_line_loop(int n, double h, double c_max, Ctrl* c, const EpiArgs<T>& 
   const size_t lds = line_lds_bytes<T>(S);
 #define UOT_LN(TS, NT, EPT)                                                                                         \
   do {                                                                                                              \
-    if constexpr (NT != 256)                                                                                        \
+    if constexpr (NT == 512 || (sizeof(T) == 4 && NT * EPT == 1024 && NT != 256))                                   \
       hipLaunchKernelGGL((k_line_loop<T, TS, NT, EPT>), dim3(1), dim3(NT), lds, s, S, h * h, c, ex, ey, hist, chunk); \
   } while (0)
   UOT_LINE_TS(UOT_LN)

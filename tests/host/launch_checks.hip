@@ -3,6 +3,7 @@
 //   launch_checks lines    solves, half-steps and objectives over lengths of lines
 //   launch_checks planes   solves over the planes that one block may hold
 //   launch_checks barycenters   ... over the rows of several fields that it may hold
+//   launch_checks instances     solves of 1-D grids and planes at every segment length
 // print the largest dynamic LDS that each kernel was launched with;
 //   launch_checks routes   the pass kernels of solves on either side of the rules
 //   launch_checks slices   the tap slices of lines
@@ -261,6 +262,17 @@ static void planes() {
         }
 }
 
+// 1-D grids and planes under every segment length
+static void instances() {
+  for (int dt : {UOT_F32, UOT_F64})
+    for (double c : {0.01, 0.1, 0.3, 0.7, 1.5, 3.0}) {
+      for (int64_t n = 1; n <= 800; ++n) solve(dt, grid(1, n, 0, 0), 1, c);
+      for (int64_t a = 1; a <= 256; ++a)
+        for (int64_t b = 1; a * b <= 4096 && b <= 256; ++b)
+          for (int m : {2, 400}) solve(dt, grid(3, m, a, b), 1, c);
+    }
+}
+
 // barycentres, a row of every field in one block
 static void barycenters() {
   for (int dt : {UOT_F32, UOT_F64})
@@ -363,6 +375,7 @@ int main(int argc, char** argv) {
   if (what == "lines") lines();
   if (what == "planes") planes();
   if (what == "barycenters") barycenters();
+  if (what == "instances") instances();
   if (what == "failing") failing();
   else if (what == "slices") slices();
   else if (what == "routes") routes();

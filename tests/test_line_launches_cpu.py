@@ -73,6 +73,15 @@ def test_lds_of_every_shape_fits(driver, static_lds, what):
     assert seen >= 4
 
 
+def test_every_loop_and_plane_kernel_is_reached(driver, static_lds):
+    rc, out = _run([driver, "instances"], timeout=300)
+    assert rc == 0 and "launch checks passed" in out, out
+    for kernel in ("k_line_loop", "k_plane_pair"):
+        built = {name for name in static_lds if kernel in name}
+        launched = {name for name in re.findall(r"^(_Z\S+)", out, re.M) if kernel in name}
+        assert built and built == launched
+
+
 def test_a_failing_launch_is_reported_by_its_call(driver):
     """Every launch of a solve fails in turn, with and without a graph,
     synchronous and asynchronous: the call returns the error, no error is left for
