@@ -1149,7 +1149,9 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
   }
   log_into<T>(pb->q, B.logq, nb * P.M, 1, py, B.t1, s);
   log_into<T>(pb->dy, B.logdy, P.M, 0, py, B.t1, s);
-  if (P.geom == UOT_GEOM_GRID && !P.line)
+  // (the whole iteration in one block forms its own kernel and weights)
+  const bool loop = P.loop && !mass;
+  if (P.geom == UOT_GEOM_GRID && !P.line && !loop)
     for (int k = 0; k < P.dim; ++k) launch_gtab<T>(B.gtab[k], (int)P.n[k], P.h[k], B.ctrl, P.nst, P.cost, s);
   if (!P.pair) launch_init_pot<T>(nullptr, B.logdx, uo, nullptr, nb * P.N, P.N, B.ctrl, 0, s);
   const T* v0 = static_cast<const T*>(pr->v0);
@@ -1157,7 +1159,7 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
     launch_gather<T>(v0, py, P.M, 1, vo, s);
     v0 = vo;
   }
-  launch_init_pot<T>(v0, B.logdy, vo, B.wv, nb * P.M, P.M, B.ctrl, 0, s);
+  launch_init_pot<T>(v0, B.logdy, vo, loop ? nullptr : B.wv, nb * P.M, P.M, B.ctrl, 0, s);
   HIP_TRY(hipGetLastError());
   if (P.dense_mf) {
     if ((rc = tune_dense_mf<T>(ctx, P, pbs.geom, B, s))) return rc;
@@ -1185,7 +1187,7 @@ int solve_t(uot_ctx* ctx, const uot_problem* pb, const uot_params* pr, T* u, T* 
   auto iteration_with = [&](const Plan& PP) {
     return [&, pp = &PP](int k) {
       const int par = k & 1;
-      if (pp->loop && !mass) {
+      if (loop) {
         // (one launch for the chunk)
         if (k == 0)
           timed(0, [&] {

@@ -328,7 +328,8 @@ template <typename Call> static void route(Call&& call) {
   call();
   std::printf("route %s:", g_shape.c_str());
   for (const OffloadEntry* e = __start_llvm_offload_entries; e != __stop_llvm_offload_entries; ++e)
-    if (g_seen.count(e->address) && (std::strstr(e->name, "k_line") || std::strstr(e->name, "k_plane") || std::strstr(e->name, "k_grid")))
+    if (g_seen.count(e->address) && (std::strstr(e->name, "k_line") || std::strstr(e->name, "k_plane") || std::strstr(e->name, "k_grid") ||
+                                      std::strstr(e->name, "k_gtab")))
       std::printf(" %s", e->name);
   std::printf("\n");
 }
@@ -338,6 +339,9 @@ static void routes() {
                               grid(2, 2050, 8, 0), grid(3, 8, 32, 32), grid(3, 8, 64, 64), grid(3, 8, 16, 256), grid(3, 8, 80, 80),
                               grid(3, 30, 80, 80)})
       route([&] { solve(dt, g, 1, 0.01); });
+  for (int dt : {UOT_F32, UOT_F64})
+    for (int n : {40, 500, 1000})
+      route([&] { solve(dt, grid(1, n, 0, 0), 1, 0.01); });
   const int bary[][3] = {{2, 64, 64}, {8, 50, 50}, {10, 80, 80}, {10, 81, 81}, {10, 150, 150}, {12, 48, 48}, {16, 64, 64},
                          {20, 50, 50}, {24, 20, 40}, {24, 96, 96}, {30, 64, 64}, {33, 40, 60}, {60, 32, 32}};
   for (int dt : {UOT_F32, UOT_F64})

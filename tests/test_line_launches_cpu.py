@@ -111,10 +111,20 @@ def test_routes_of_grid_solves(routes):
     got = {"f32": {}, "f64": {}}
     for m in re.finditer(r"route solve (f\d\d) (\d+)x(\d+)x(\d+) \S+ \d+ c \S+:(.*)", routes):
         shape = tuple(int(x) for x in m.group(2, 3, 4) if x != "0")
+        if len(shape) == 1:
+            continue
         names = m.group(5)
         got[m.group(1)][shape] = ("P" if "k_plane_pair" in names else "L" if "k_line_pair" in names
                                   else "S" if "6k_lineI" in names else "-")
     assert got == ROUTES
+
+
+def test_whole_iterations_build_no_kernel_table(routes):
+    for dtype in ("f32", "f64"):
+        names = {int(n): names for n, names in re.findall(rf"route solve {dtype} (\d+)x0x0 \S+ \d+ c \S+:(.*)", routes)}
+        for n in (40, 500):
+            assert "k_line_loop" in names[n] and "k_gtab" not in names[n]
+        assert "k_line_loop" not in names[1000] and "k_gtab" in names[1000]
 
 
 # ... and the paired passes with the combine among them (line_bary_root_passes): B paired,
