@@ -1778,6 +1778,10 @@ int time_half_step_t(uot_ctx* ctx, const uot_problem* pb, int nb, double eps, co
   const int dk = (pb->geom.kind == UOT_GEOM_POINTS && grid_kernel >= 2 && grid_kernel <= 4) ? grid_kernel : 1;
   int rc = make_plan(P, pb->dtype, pb->geom, nb, 1, pb->geom.kind == UOT_GEOM_GRID ? grid_kernel : 0, eps, dk);
   if (rc) return rc;
+  if (P.loop) {   // (the pass of half_step_t)
+    P.line = true;
+    P.nparts_x = P.nparts_y = 1;
+  }
   if ((rc = check_ws(P, ws, wsb))) return rc;
   if (!v || !ms || !nk || reps < 1) return fail(UOT_E_INVALID, "v, ms, n_kernels and reps >= 1 are required");
   hipStream_t s = ctx->work;

@@ -342,6 +342,20 @@ static void routes() {
   for (int dt : {UOT_F32, UOT_F64})
     for (int n : {40, 500, 1000})
       route([&] { solve(dt, grid(1, n, 0, 0), 1, 0.01); });
+  for (int dt : {UOT_F32, UOT_F64})
+    for (int n : {40, 500, 1000}) {
+      const uot_geom g = grid(1, n, 0, 0);
+      uot_problem pb = problem(dt, g);
+      const double eps = params(0.01).eps;
+      size_t wsb = 0;
+      double r = 0, ms[3];
+      int nk = 0;
+      EXPECT(uot_workspace_size(&pb, &wsb) == UOT_OK);
+      note("half-step", dt, g, 1, 0.01);
+      route([&] { EXPECT(uot_half_step(ctx, &pb, eps, 0, kDev, kDev, kDev, &r, kDev, wsb) == UOT_OK); });
+      note("timed", dt, g, 1, 0.01);
+      route([&] { EXPECT(uot_time_half_step(ctx, &pb, eps, kDev, 1, ms, &nk, kDev, wsb, 0) == UOT_OK && nk == 1); });
+    }
   const int bary[][3] = {{2, 64, 64}, {8, 50, 50}, {10, 80, 80}, {10, 81, 81}, {10, 150, 150}, {12, 48, 48}, {16, 64, 64},
                          {20, 50, 50}, {24, 20, 40}, {24, 96, 96}, {30, 64, 64}, {33, 40, 60}, {60, 32, 32}};
   for (int dt : {UOT_F32, UOT_F64})

@@ -127,6 +127,15 @@ def test_whole_iterations_build_no_kernel_table(routes):
         assert "k_line_loop" not in names[1000] and "k_gtab" in names[1000]
 
 
+def test_the_timed_half_step_is_the_one_that_runs(routes):
+    got = {}
+    for what, dtype, n, names in re.findall(r"route (half-step|timed) (f\d\d) (\d+)x0x0 \S+ \d+ c \S+:(.*)", routes):
+        got.setdefault((dtype, int(n)), {})[what] = names
+    assert len(got) == 6
+    for key, names in got.items():
+        assert names["timed"] == names["half-step"], key
+
+
 # ... and the paired passes with the combine among them (line_bary_root_passes): B paired,
 # S a line pass per launch, - the other passes
 BARY_ROUTES = {
