@@ -358,15 +358,15 @@ FP16_PASS_NAMES = ["k_grid_tf<false, 4>", "k_grid_tf<true, 4>"]
 # HBM bytes per launch (calibrated FETCH_SIZE read + WRITE_SIZE written) of the
 # two passes at both launch shapes, from the two counter runs of
 # `bench.py --pmc-workload`; they hold for the kernel source they were taken
-# on (sha256 of the pass's file and the headers it includes) and are reported
+# on (sha256 of the passes' files and the headers they include) and are reported
 # as null otherwise.
-TRAFFIC_SOURCES = ["uot_grid_tf.hip", "uot_epilogue.h", "uot_device.h", "uot_launch.h"]
-TRAFFIC_SOURCE_SHA256 = "d9b3651b18eab72e4f6947301386994449ffd7a674a62e3dfb3e752cbb12d178"
+TRAFFIC_SOURCES = ["uot_grid_tf.hip", "uot_grid_line.hip", "uot_epilogue.h", "uot_device.h", "uot_launch.h", "uot_bary.h"]
+TRAFFIC_SOURCE_SHA256 = "a848ff99cf69a7a50f5d8c19fb439cdd96b24a50dcdf93027c8b48c326d42292"
 TRAFFIC_BYTES = {
-    ('k_grid_tf<false, 4>', 1): (2251937, 259840),
-    ('k_grid_tf<false, 4>', 256): (67279922, 67108864),
-    ('k_grid_tf<true, 4>', 1): (3097137, 523671),
-    ('k_grid_tf<true, 4>', 256): (406611194, 134348800),
+    ("k_line, last axis", 1): (384838, 262144),
+    ("k_line, last axis", 256): (67339402, 67108864),
+    ("k_line, first axis + epilogue", 1): (1181007, 528384),
+    ("k_line, first axis + epilogue", 256): (203691170, 134479872),
 }
 
 
@@ -375,11 +375,11 @@ TRAFFIC_BYTES = {
 # runs of `bench.py --pmc-workload batch`; valid for the source they were
 # taken on (sha256 of the product's file and the headers it includes).
 BATCH_TRAFFIC_SOURCES = ["uot_dense_mf.hip", "uot_epilogue.h", "uot_device.h", "uot_launch.h"]
-BATCH_TRAFFIC_SHA256 = "86daf7ddf1869f35e617ac634e1a1fd373555e3f650af5956bd573c51650a9c6"
+BATCH_TRAFFIC_SHA256 = "7333143548205d4844be9e6de731eb79ec92ac93d155f5a25599a4433431dbe3"
 # (kernel, rows per item) -> (bytes read, bytes written, pair evaluations) of
 # one launch that holds every problem (the counter workload: all 4096
 # problems active, warm maxima)
-BATCH_TRAFFIC_BYTES = {("k_batch_mf", 256): (281937227, 81684312, 3782323547)}
+BATCH_TRAFFIC_BYTES = {("k_batch_mf", 256): (283670847, 106031934, 3782323547)}
 
 
 def _sha256(names):
@@ -399,18 +399,9 @@ def batch_traffic(kernel, tile_rows):
     return BATCH_TRAFFIC_BYTES.get((kernel, tile_rows))
 
 
-def tf_source_sha256():
-    import hashlib
-    h = hashlib.sha256()
-    for name in TRAFFIC_SOURCES:
-        with open(os.path.join(ROOT, "paper_1607_05816_amd", "csrc", name), "rb") as f:
-            h.update(f.read())
-    return h.hexdigest()
-
-
 def traffic(kernel, fields):
     """(bytes read, bytes written) per launch, or None once the kernel changed."""
-    if tf_source_sha256() != TRAFFIC_SOURCE_SHA256:
+    if _sha256(TRAFFIC_SOURCES) != TRAFFIC_SOURCE_SHA256:
         return None
     return TRAFFIC_BYTES.get((kernel, fields))
 
@@ -436,8 +427,8 @@ def grid_roofline(U, probs, last, ctx, torch, np, nb_fields=256):
     if tr is not None:
         out["traffic"] = float(sum(tr))
         out["traffic_read_written"] = list(tr)
-        # the X-side strided pass reads its input, log p, u_old, log dx and
-        # writes u, w (4 B each per cell); the contiguous pass reads w, writes t
+        # the pass along the first axis reads its input, log p, u_old, log dx and
+        # writes u, w (4 B each per cell); that along the last reads w, writes t
         out["traffic_algorithmic"] = float(N_GRID * N_GRID * 4 * (6 if k == 1 else 2))
     pb = probs[0][1]
     p = pb.p.reshape(1, -1).expand(nb_fields, -1).contiguous()
@@ -713,6 +704,33 @@ def pmc_workload_batch(U, torch, np, dev, ctx, iters=10):
         int(info["iters"].max()), info["product"], int(info["tile_rows"])), flush=True)
 
 
+def pmc_workload_lines(U, torch, np, dev, ctx):
+    """The launches the line passes' counters are read on, after a 256 MiB
+    device copy (the calibration kernel): solves of fixed iteration counts of
+    the headline field, of 256 fields of 64 x 64 cells, of 3-D cells (64 x 32 x
+    32), of an FP64 grid (256 x 256) and of one FP64 line of 256 cells."""
+    calibration_copy(torch, dev)
+    F = U.KL(0.1)
+
+    def problem(shape, nb, dtype):
+        rng = np.random.default_rng(0)
+        size = int(np.prod(shape))
+        t = lambda a: torch.tensor(a, dtype=dtype, device=dev)
+        h = tuple(1.0 / n for n in shape)
+        p, q = (t(rng.uniform(0.2, 2.0, (nb, size))) for _ in range(2))
+        return h, p, q, t(np.full(size, float(np.prod(h))))
+
+    kw = dict(tol=0.0, max_iter=100, check_every=100, ctx=ctx)
+    for shape, dtype, eps in (((256, 256), torch.float32, 1e-3), ((64, 32, 32), torch.float32, 5e-3),
+                              ((256, 256), torch.float64, 1e-3), ((256,), torch.float64, 1e-3)):
+        h, p, q, d = problem(shape, 1, dtype)
+        U.solve(U.grid_problem(shape, h, p[0], q[0], d, d, F, F), eps, **kw)
+    h, p, q, d = problem((64, 64), 256, torch.float32)
+    U.solve_fields((64, 64), h, p, q, d, d, F, F, 1e-3, **kw)
+    torch.cuda.synchronize()
+    print("pmc line workload done", flush=True)
+
+
 BF16_MFMA_PEAK = 2.5e15     # MI355X dense BF16 MFMA, FLOP/s
 
 
@@ -856,7 +874,7 @@ def main():
     ap.add_argument("--no-dense", action="store_true")
     ap.add_argument("--no-gemm", action="store_true")
     ap.add_argument("--no-extensions", action="store_true")
-    ap.add_argument("--pmc-workload", nargs="?", const="grid", choices=("grid", "dense", "batch", "gemm"),
+    ap.add_argument("--pmc-workload", nargs="?", const="grid", choices=("grid", "dense", "batch", "lines", "gemm"),
                     help="only run the launches counters are read on: the grid passes (HBM traffic), "
                          "the dense products at 20000^2, the batched product of the ragged workload or the "
                          "training GEMMs of the warm-start net")
@@ -888,6 +906,9 @@ def main():
         return
     if args.pmc_workload == "batch":
         pmc_workload_batch(U, torch, np, dev, U.default_context())
+        return
+    if args.pmc_workload == "lines":
+        pmc_workload_lines(U, torch, np, dev, U.default_context())
         return
     if args.pmc_workload == "gemm":
         calibration_copy(torch, dev)

@@ -35,10 +35,12 @@
 // two passes, epilogue, two passes.  So an iteration of a 2-D or 3-D grid is
 // two launches, and the weights between the half-steps never leave the block.
 //
-// What bounds it: one field is bound by the latency of its launches (launch,
-// one round trip for the taps, two passes of a few dependent exp2 / MFMA
-// chains); batches of fields by the FP32 MFMA, which shares the vector ALUs
-// (per 16 taps of 16 columns: 4 MFMA of 32 cycles, 10 VALU and 4 exp2).
+// What bounds it (counters, 100 iterations each): one field of 256 x 256 cells, 256
+// blocks, by latency (a launch of 16.5 k cycles, 7 us: a block's waves wait 63 % of
+// them, its launch, the round trip for the taps, two passes of a few dependent
+// exp2 / MFMA chains); 256 fields of 64 x 64 by VALU issue (65 % of the 36 k cycles of
+// a launch; the MFMA, which runs beside none of it, another 11 %; 42 VALU to an MFMA,
+// most of them in the joins and the epilogue).
 // ---------------------------------------------------------------------------
 namespace uot {
 
@@ -701,8 +703,9 @@ __global__ __launch_bounds__(NT) void k_plane_pair(const T* __restrict__ in, int
 // registers, and `chunk` iterations are one launch.  The block's first wave
 // also takes the control step's decision.  exy[0], exy[1]: the X and Y
 // epilogues (potentials, log densities, log weights, penalties).
-// It is bound by the latency of a pass (two per iteration): about 2000 cycles
-// in FP32 at 256 cells, one 16-column group whose segments go over 8 waves.
+// It is bound by the latency of a half-step (two per iteration): at 256 cells 5 k
+// cycles in FP32 and 11 k in FP64 (one 16-column group whose segments go over 8
+// waves; of these waves' time 40 % waits for memory or a barrier, 26 % for issue).
 // ---------------------------------------------------------------------------
 template <typename T, int TS, int NT, int EPT>
 __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape S, double h2, Ctrl* c, EpiArgs<T> ex,
@@ -833,9 +836,11 @@ __global__ __launch_bounds__(256) void k_transpose(const T* __restrict__ src, T*
 // longest segment for c (0: the pass does not apply).  FP32: c TS <= 6 and at
 // least 8 taps, i.e. c <= 0.75; beyond that a kernel is a few cells wide and
 // the direct passes take it.
+// (FP64: at most 32 taps, which spill 6 registers in blocks of 512 threads and 40 to 90
+// in those of 1024)
 template <typename T> static int line_ts(double c) {
   const double top = sizeof(T) == 4 ? 6.0 : 63.0;
-  for (int ts = sizeof(T) == 4 ? 64 : 32; ts >= (sizeof(T) == 4 ? 8 : 16); ts /= 2)   // (FP64: 64 taps would spill)
+  for (int ts = sizeof(T) == 4 ? 64 : 32; ts >= (sizeof(T) == 4 ? 8 : 16); ts /= 2)
     if (c * ts <= top) return ts;
   return 0;
 }
@@ -1000,7 +1005,7 @@ void launch_line(const T* in, int64_t A, int n, int64_t B, double h, double c_ma
   do {                                                                                                            \
     line_big_lds(k_line<T, TS, NT, EPT>, lds);                                                                    \
     hipLaunchKernelGGL((k_line<T, TS, NT, EPT>), dim3(blocks), dim3(NT), lds, s, in, A, B, lsh, S, h * h, side, c, \
-                       ep, c32 ? 1 : 0);                                                                                       \
+                       ep, c32 ? 1 : 0);                                                                          \
   } while (0)
   UOT_LINE_TS(UOT_LN)
 #undef UOT_LN
@@ -1066,9 +1071,10 @@ bool line_bary_fits(bool f64, int64_t F, int64_t R, int n, double c_max) {
 // launches and whose older passes (FP32: tile-factored axes, tf) take fewer
 // cells a block.  Measured (us an iteration, TV, paired / a pass per launch /
 // older passes): FP32 16 x 64 x 64 33.1 / 37.0 / 35.2, 10 x 112 x 112 46.0 / 40.5 /
-// 40.2, 48 x 64 x 64 147 / 80 / 83, 10 x 80 x 80 40.0 / 41.5 / 33.1, 30 x 64 x 64 - /
-// 57.1 / 53.4, 20 x 50 x 50 - / 48.4 / 47.3, 10 x 150 x 150 65.5 / 70.3 / 95.6; FP64 8 x 64 x 64 35.4 / 37.3 / 41.0, 24 x 96 x 96 176 / 112 /
-// 214, 12 x 48 x 48 57.4 / 55.5 / 51.7, 12 x 160 x 160 153 / 167 / 373.
+// 40.2, 48 x 64 x 64 147 / 80 / 83, 10 x 80 x 80 40.0 / 41.5 / 33.1, 30 x 64 x 64
+// - / 57.1 / 53.4, 20 x 50 x 50 - / 48.4 / 47.3, 10 x 150 x 150 65.5 / 70.3 / 95.6;
+// FP64 8 x 64 x 64 35.4 / 37.3 / 41.0, 24 x 96 x 96 176 / 112 / 214, 12 x 48 x 48
+// 57.4 / 55.5 / 51.7, 12 x 160 x 160 153 / 167 / 373.
 int line_bary_root_passes(bool f64, int64_t F, int64_t R, int n, bool two_breaks, bool tf) {
   const int64_t cells = F * R * n;
   const int L = bary_lanes((int)F, two_breaks), NT = line_threads((int)F * n, R);
