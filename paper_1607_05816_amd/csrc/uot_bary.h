@@ -166,14 +166,19 @@ __device__ __forceinline__ T bary_mean(const T* t2, int64_t stride, int nm, cons
     if (r == Num<T>::ninf()) return r;
     T acc = T(0), asum = T(0), sum = T(0);
     for (int k = 0; k < nm; ++k) {
-      const T al = T(w.a[k]), t = gam * (t2[k * stride] - r);
+      const T al = T(w.a[k]);
       T e;
-      acc = Num<T>::fma(al, expm1_exp2(t, e), acc);
+      acc = Num<T>::fma(al, expm1_exp2(gam * (t2[k * stride] - r), e), acc);
       sum = Num<T>::fma(al, e, sum);
       asum += al;
     }
-    const T x = acc / asum;
-    const T lg = x < T(-0.5) ? Num<T>::log(sum / asum) : Num<T>::log1p(x);
+    // log y: of the small sum, or of 1 + x with what the addition rounds put back
+    // (x in [-1/2, 0])
+    const bool small = acc < T(-0.5) * asum;
+    const T x = (small ? sum : acc) / asum;
+    const T y = small ? x : T(1) + x;
+    const T lost = small ? T(0) : x - (y - T(1));
+    const T lg = Num<T>::log(y) + lost / y;
     logh = r * T(kLn2) + lg / gam;
   }
   return logh;
