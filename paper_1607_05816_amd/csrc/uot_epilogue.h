@@ -160,6 +160,24 @@ __device__ __forceinline__ T epi_core(int64_t e, T S2, EpiIn<T>& x, const EpiK<T
   return w;
 }
 
+// the same value in every lane, kept in scalar registers
+__device__ __forceinline__ float uniform(float x) {
+  return __builtin_bit_cast(float, __builtin_amdgcn_readfirstlane(__builtin_bit_cast(int, x)));
+}
+__device__ __forceinline__ double uniform(double x) {
+  const int2 v = __builtin_bit_cast(int2, x);
+  return __builtin_bit_cast(double, int2{__builtin_amdgcn_readfirstlane(v.x), __builtin_amdgcn_readfirstlane(v.y)});
+}
+
+template <typename T> __device__ __forceinline__ EpiK<T> uniform(EpiK<T> k) {
+  k.zeta = uniform(k.zeta);
+  k.ke = uniform(k.ke), k.kel = uniform(k.kel);
+  k.kw = uniform(k.kw), k.kwl = uniform(k.kwl);
+  k.k.eps.c = uniform(k.k.eps.c), k.k.eps.cl = uniform(k.k.eps.cl);
+  k.k.coef.c = uniform(k.k.coef.c), k.k.coef.cl = uniform(k.k.coef.cl);
+  return k;
+}
+
 template <typename T>
 __device__ __forceinline__ EpiK<T> epi_consts_of(const Ctrl* __restrict__ c, int side, const EpiArgs<T>& ep) {
   EpiK<T> k{};

@@ -735,7 +735,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape 
   const double tol = c->tol;
   int sn = stage_at(c, l);
   double eps = c->eps_tab[sn], le = kLog2e / eps;
-  EpiK<T> KX = epi_consts<T>(eps, le, eps, le, ctrl_coef(c, 0, eps), 0.0), KY;
+  EpiK<T> KX = uniform(epi_consts<T>(eps, le, eps, le, ctrl_coef(c, 0, eps), 0.0)), KY;
   Op op;
   op.init(line_c<T>(h2, eps, le));
 #pragma unroll
@@ -754,7 +754,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape 
     const int sn1 = stage_at(c, l + 1);
     const double eps1 = sn1 == sn ? eps : c->eps_tab[sn1], le1 = sn1 == sn ? le : kLog2e / eps1;
     if (it == 0 || sn1 != sn || KY.ke != KX.ke)
-      KY = epi_consts<T>(eps, le, eps1, le1, ctrl_coef(c, 1, eps), 0.0);
+      KY = uniform(epi_consts<T>(eps, le, eps1, le1, ctrl_coef(c, 1, eps), 0.0));
     __syncthreads();
     ResAcc<T> ra;
     ra.init();
@@ -794,7 +794,7 @@ __global__ __launch_bounds__(NT, NT == 1024 ? 4 : 2) void k_line_loop(LineShape 
       sn = sn1;
       eps = eps1;
       le = le1;
-      KX = epi_consts<T>(eps, le, eps, le, ctrl_coef(c, 0, eps), 0.0);
+      KX = uniform(epi_consts<T>(eps, le, eps, le, ctrl_coef(c, 0, eps), 0.0));
     }
     if (stopped) break;
   }
