@@ -83,22 +83,25 @@ template <typename T> __device__ __forceinline__ T epi_weight(T pot, T k, T kl, 
 }
 // e^x - 1 at x = t ln 2: the Taylor polynomial to degree 7 for |x| < 1/4
 // (remainder below 4e-10 of x), else 2^t - 1
-// (and e = 2^t)
-__device__ __forceinline__ float expm1_exp2(float t, float& e) {
-  const float x = t * float(kLn2);
+__device__ __forceinline__ float expm1_poly(float x) {
   float p = 1.f / 5040.f;
   p = __builtin_fmaf(p, x, 1.f / 720.f);
   p = __builtin_fmaf(p, x, 1.f / 120.f);
   p = __builtin_fmaf(p, x, 1.f / 24.f);
   p = __builtin_fmaf(p, x, 1.f / 6.f);
   p = __builtin_fmaf(p, x, 0.5f);
-  p = __builtin_fmaf(p * x, x, x);
-  e = __builtin_amdgcn_exp2f(t);
-  return __builtin_fabsf(x) < 0.25f ? p : e - 1.f;
+  return __builtin_fmaf(p * x, x, x);
 }
 __device__ __forceinline__ float expm1_log2(float t) {
-  float e;
-  return expm1_exp2(t, e);
+  const float x = t * float(kLn2);
+  const float p = expm1_poly(x);
+  return __builtin_fabsf(x) < 0.25f ? p : __builtin_amdgcn_exp2f(t) - 1.f;
+}
+// (and e = 2^t)
+__device__ __forceinline__ float expm1_exp2(float t, float& e) {
+  const float x = t * float(kLn2);
+  e = __builtin_amdgcn_exp2f(t);
+  return __builtin_fabsf(x) < 0.25f ? expm1_poly(x) : e - 1.f;
 }
 // ... to degree 12 (remainder below 1e-17 of x)
 __device__ __forceinline__ double expm1_exp2(double t, double& e) {
