@@ -278,7 +278,7 @@ void dense_config(Plan& P, int side) {
 }
 
 int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_kernel = 0, double eps_min = 0.0,
-              int dense_kernel = 1) {
+              int dense_kernel = 1, bool flow = false) {
   if (dtype != UOT_F32 && dtype != UOT_F64) return fail(UOT_E_INVALID, "dtype must be UOT_F32 or UOT_F64");
   if (dense_kernel < 0 || dense_kernel > 4) return fail(UOT_E_INVALID, "dense_kernel must be 0 .. 4");
   if (grid_kernel < 0 || grid_kernel > 4) return fail(UOT_E_INVALID, "grid_kernel must be 0 .. 4");
@@ -338,7 +338,7 @@ int make_plan(Plan& P, int dtype, const uot_geom& g, int nb, int nst, int grid_k
       P.band[k] = (int)g.n[k];
       if (g.cost == UOT_COST_WF) P.band[k] = (int)std::min<double>((double)g.n[k], std::ceil(g.cut / g.h[k]));
     }
-    if (g.dim == 1) P.split1d = grid_contig_splits(dtype == UOT_F64, (int)g.n[0], nb, P.band[0]);
+    if (g.dim == 1) P.split1d = grid_contig_splits(dtype == UOT_F64, (int)g.n[0], nb, P.band[0], flow && nb > 1);
     // the line passes take every axis or none (squared Euclidean cost, the
     // default choice or grid_kernel 2): what they leave to the older passes
     // is kernels of a few cells (c above their limit), the WF cost, the
@@ -1666,7 +1666,7 @@ int validate_flow(const uot_flow_problem* fp, FlowDivs& d) {
 }
 
 int flow_plan(Plan& P, const uot_flow_problem* fp, int nst, int grid_kernel, double eps_min, size_t& o_u) {
-  int rc = make_plan(P, fp->dtype, fp->geom, fp->species, nst, grid_kernel, eps_min);
+  int rc = make_plan(P, fp->dtype, fp->geom, fp->species, nst, grid_kernel, eps_min, 1, true);
   if (rc) return rc;
   o_u = align_up(P.total);
   P.total = align_up(o_u + P.esz * (size_t)fp->species * P.N);

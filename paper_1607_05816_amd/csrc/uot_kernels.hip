@@ -1504,7 +1504,7 @@ void launch_grid_contig(const T* in, int64_t A, int n, const T* gtab, int side, 
 
 // tap slices for few long lines (A x ceil(n/64) blocks well below the chip's
 // width): enough slices for ~2048 blocks, each slice at least 256 taps
-int grid_contig_splits(bool f64, int n, int64_t A, int band) {
+int grid_contig_splits(bool f64, int n, int64_t A, int band, bool hosted) {
   const int bd = (band < 1 || band > n) ? n : band;
   const int64_t blocks1 = (int64_t)ceil_div(n, 64) * A;
   if (blocks1 >= 1024 || A > 65535) return 1;
@@ -1520,10 +1520,13 @@ int grid_contig_splits(bool f64, int n, int64_t A, int band) {
   // slices are 517 blocks, three on five of the units, 44.0 / 38.3 with 10; 4096
   // cells 52.4 with all 16 (55.8 with 8); 2500 36.2 / 33.6 with 6.  Over 51
   // sizes and two cuts FP64 is 0.5 % and FP32 0.8 % above the best (the most
-  // slices: 3.5 and 1.9 %).
+  // slices: 3.5 and 1.9 %).  A launch over several lines that hosts the control step
+  // (flows) has one more column of blocks, most without work: they are dealt like
+  // the others, so 264 blocks (2 x 2000 cells, 4 slices) put two on some units, 45.8
+  // against 39.7 with 7; of 24 flows all take the fastest count.
   int64_t best = sp, least = INT64_MAX;
   for (int64_t k = sp; k >= std::max<int64_t>(1, sp / 2); --k) {
-    const int64_t r = (blocks1 * k + 255) / 256, t = (taps + k - 1) / k;
+    const int64_t r = ((blocks1 + (hosted ? A : 0)) * k + 255) / 256, t = (taps + k - 1) / k;
     const int64_t cost = (f64 ? 5 * r + 1 : r + 2) * t;
     if (cost < least) {
       least = cost;

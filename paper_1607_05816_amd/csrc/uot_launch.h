@@ -106,7 +106,8 @@ void launch_grid_contig(const T* in, int64_t A, int n, const T* gtab, int side, 
                         const EpiArgs<T>& ep, int band, hipStream_t s);
 // few long lines: tap slices (grid_contig_splits) with partial LSEs in pm / ps
 // (nsplit x A x n each), merged by launch_dense_epi over A n outputs
-int grid_contig_splits(bool f64, int n, int64_t A, int band);
+// (hosted: launches of several lines host the control step)
+int grid_contig_splits(bool f64, int n, int64_t A, int band, bool hosted);
 template <typename T>
 void launch_grid_contig_split(const T* in, int64_t A, int n, const T* gtab, int side, const Ctrl* c, int band,
                               int nsplit, T* pm, T* ps, const CtlHost& host, hipStream_t s);

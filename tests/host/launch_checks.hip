@@ -369,21 +369,41 @@ static void routes() {
     }
 }
 
-// the tap slices of lines under the WF cost
+static void flow(int dtype, const uot_geom& g, int species) {
+  note("flow", dtype, g, species, 0.01);
+  uot_flow_problem fp;
+  std::memset(&fp, 0, sizeof(fp));
+  fp.dtype = dtype;
+  fp.kind = UOT_FLOW_GROWTH;
+  fp.species = species;
+  fp.geom = g;
+  fp.p0 = fp.q = fp.dx = kDev;
+  fp.tau = 0.01;
+  fp.alpha = 1.0;
+  uot_params pr = params(0.01);
+  size_t n = 0;
+  EXPECT(uot_flow_workspace_size(&fp, &n) == UOT_OK);
+  EXPECT(uot_flow(ctx, &fp, &pr, 1, kDev, kDev, kDev, n, nullptr) == UOT_OK);
+}
+
+// the tap slices of lines under the WF cost, of solves of several fields and flows of several species
 static void slices() {
   for (int dt : {UOT_F32, UOT_F64})
     for (int nb : {1, 2, 3, 5})
-      for (int n : {700, 1500, 2500, 3000, 4000, 4096})
+      for (int n : {700, 1500, 2000, 2500, 3000, 4000, 4096})
         for (double cut : {0.3, 4.0}) {
           uot_geom g = grid(1, n, 0, 0);
           g.cost = UOT_COST_WF;
           g.cut = cut * n / 64;
-          g_seen.clear();
-          solve(dt, g, nb, 0.01);
-          for (const OffloadEntry* e = __start_llvm_offload_entries; e != __stop_llvm_offload_entries; ++e)
-            if (g_seen.count(e->address) && std::strstr(e->name, "k_grid_contig"))
-              std::printf("slices f%d fields %d cells %d cut %g: %u\n", dt == UOT_F32 ? 32 : 64, nb, n, cut,
-                          g_seen[e->address].grid.z);
+          for (bool flows : {false, true}) {
+            g_seen.clear();
+            if (flows) flow(dt, g, nb);
+            else solve(dt, g, nb, 0.01);
+            for (const OffloadEntry* e = __start_llvm_offload_entries; e != __stop_llvm_offload_entries; ++e)
+              if (g_seen.count(e->address) && std::strstr(e->name, "k_grid_contig"))
+                std::printf("%s f%d fields %d cells %d cut %g: %u\n", flows ? "flow" : "slices", dt == UOT_F32 ? 32 : 64,
+                            nb, n, cut, g_seen[e->address].grid.z);
+          }
         }
 }
 

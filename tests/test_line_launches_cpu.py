@@ -183,6 +183,14 @@ def test_slices_of_lines(driver):
     for m in re.finditer(r"slices (f\d\d) fields (\d+) cells (\d+) cut (\S+): (\d+)", out):
         got[m.group(1)][int(m.group(2)), int(m.group(3)), float(m.group(4))] = int(m.group(5))
     for dtype, want in SLICES.items():
-        assert len(got[dtype]) == 48
+        assert len(got[dtype]) == 56
         for key, k in want.items():
             assert got[dtype][key] == k, (dtype, key)
+    # the launches of a flow of several species have a column of blocks more, for the control step
+    flows = {tuple(int(x) for x in m[:2]): int(m[2])
+             for m in re.findall(r"flow f64 fields (\d+) cells (\d+) cut 4: (\d+)", out)}
+    assert len(flows) == 28
+    for key, k in {(1, 3000): 10, (1, 4096): 16, (2, 1500): 5, (2, 2000): 7, (2, 3000): 8, (2, 4000): 14, (3, 1500): 3,
+                   (3, 3000): 7, (3, 4000): 8}.items():
+        assert flows[key] == k, key
+    assert got["f64"][2, 2000, 4.0] == 4 and got["f64"][3, 3000, 4.0] == 9
