@@ -50,17 +50,16 @@ template <> struct Num<double> {
 
 // 2^x: x = n + f with |f| <= 1/2, the Taylor polynomial of 2^f to degree 13
 // (remainder below 5e-18), scaled by 2^n; arguments below -1100 give 0
-__device__ __forceinline__ double exp2_f64(double x) {
-  const double xc = x < -1100.0 ? -1100.0 : x;
-  const double n = __builtin_rint(xc);
-  const double f = xc - n;
+// (exp2_poly: 2^f = 1 + b f + a f^2)
+__device__ __forceinline__ void exp2_poly(double f, double& a, double& b) {
   constexpr double L = kLn2;
   constexpr double c2 = L * L / 2, c3 = c2 * L / 3, c4 = c3 * L / 4, c5 = c4 * L / 5, c6 = c5 * L / 6,
                    c7 = c6 * L / 7, c8 = c7 * L / 8, c9 = c8 * L / 9, c10 = c9 * L / 10, c11 = c10 * L / 11,
                    c12 = c11 * L / 12, c13 = c12 * L / 13;
   // two interleaved chains in f^2 (even and odd powers)
   const double g = f * f;
-  double a = __builtin_fma(c12, g, c10), b = __builtin_fma(c13, g, c11);
+  a = __builtin_fma(c12, g, c10);
+  b = __builtin_fma(c13, g, c11);
   a = __builtin_fma(a, g, c8);
   b = __builtin_fma(b, g, c9);
   a = __builtin_fma(a, g, c6);
@@ -70,7 +69,14 @@ __device__ __forceinline__ double exp2_f64(double x) {
   a = __builtin_fma(a, g, c2);
   b = __builtin_fma(b, g, c3);
   b = __builtin_fma(b, g, L);
-  const double r = __builtin_fma(b, f, __builtin_fma(a, g, 1.0));
+}
+__device__ __forceinline__ double exp2_f64(double x) {
+  const double xc = x < -1100.0 ? -1100.0 : x;
+  const double n = __builtin_rint(xc);
+  const double f = xc - n;
+  double a, b;
+  exp2_poly(f, a, b);
+  const double r = __builtin_fma(b, f, __builtin_fma(a, f * f, 1.0));
   return __builtin_amdgcn_ldexp(r, (int)n);
 }
 

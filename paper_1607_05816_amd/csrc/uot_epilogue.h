@@ -103,23 +103,17 @@ __device__ __forceinline__ float expm1_exp2(float t, float& e) {
   e = __builtin_amdgcn_exp2f(t);
   return __builtin_fabsf(x) < 0.25f ? expm1_poly(x) : e - 1.f;
 }
-// ... to degree 12 (remainder below 1e-17 of x)
+// ... t = n + f: 2^n (2^f - 1) + (2^n - 1), which is 2^f - 1 as it is for n = 0 and
+// cancels less than two bits otherwise (|2^f - 1| <= 0.42)
 __device__ __forceinline__ double expm1_exp2(double t, double& e) {
-  const double x = t * kLn2;
-  double p = 1.0 / 479001600.0;
-  p = __builtin_fma(p, x, 1.0 / 39916800.0);
-  p = __builtin_fma(p, x, 1.0 / 3628800.0);
-  p = __builtin_fma(p, x, 1.0 / 362880.0);
-  p = __builtin_fma(p, x, 1.0 / 40320.0);
-  p = __builtin_fma(p, x, 1.0 / 5040.0);
-  p = __builtin_fma(p, x, 1.0 / 720.0);
-  p = __builtin_fma(p, x, 1.0 / 120.0);
-  p = __builtin_fma(p, x, 1.0 / 24.0);
-  p = __builtin_fma(p, x, 1.0 / 6.0);
-  p = __builtin_fma(p, x, 0.5);
-  p = __builtin_fma(p * x, x, x);
-  e = exp2_f64(t);
-  return __builtin_fabs(x) < 0.25 ? p : e - 1.0;
+  const double tc = t < -1100.0 ? -1100.0 : t;
+  const double n = __builtin_rint(tc);
+  const double f = tc - n;
+  double a, b;
+  exp2_poly(f, a, b);
+  const double m = __builtin_fma(b, f, a * (f * f)), s = __builtin_amdgcn_ldexp(1.0, (int)n);
+  e = __builtin_fma(s, m, s);
+  return __builtin_fma(s, m, s - 1.0);
 }
 __device__ __forceinline__ double expm1_log2(double t) { return ::expm1(t * kLn2); }
 
