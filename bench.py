@@ -361,11 +361,11 @@ FP16_PASS_NAMES = ["k_grid_tf<false, 4>", "k_grid_tf<true, 4>"]
 # on (sha256 of the passes' files and the headers they include) and are reported
 # as null otherwise.
 TRAFFIC_SOURCES = ["uot_grid_tf.hip", "uot_grid_line.hip", "uot_epilogue.h", "uot_device.h", "uot_launch.h", "uot_bary.h"]
-TRAFFIC_SOURCE_SHA256 = "0b900c413dc802c5385f76b31bf862341b3143bf6a56ebc6b220ef91ac0c8f3f"
+TRAFFIC_SOURCE_SHA256 = "3b6d0e2166b5d3c7198d7ee4d0c0b664344155b9fb035f1cba898ce97d2b4b47"
 TRAFFIC_BYTES = {
     ("k_line, last axis", 1): (384838, 262144),
     ("k_line, last axis", 256): (67339402, 67108864),
-    ("k_line, first axis + epilogue", 1): (1181384, 528384),
+    ("k_line, first axis + epilogue", 1): (1181007, 528384),
     ("k_line, first axis + epilogue", 256): (203691170, 134479872),
 }
 
@@ -375,11 +375,11 @@ TRAFFIC_BYTES = {
 # runs of `bench.py --pmc-workload batch`; valid for the source they were
 # taken on (sha256 of the product's file and the headers it includes).
 BATCH_TRAFFIC_SOURCES = ["uot_dense_mf.hip", "uot_epilogue.h", "uot_device.h", "uot_launch.h"]
-BATCH_TRAFFIC_SHA256 = "919e9e11f61287e78417146bfe7edb36ff5775c692419faee8623eacdbb72c8a"
+BATCH_TRAFFIC_SHA256 = "6a5de2aa30fe97306853f1259d7173ad5fcb6c1ded2d54d2129881df3f0b9e37"
 # (kernel, rows per item) -> (bytes read, bytes written, pair evaluations) of
 # one launch that holds every problem (the counter workload: all 4096
 # problems active, warm maxima)
-BATCH_TRAFFIC_BYTES = {("k_batch_mf", 256): (285789415, 106170408, 3782323547)}
+BATCH_TRAFFIC_BYTES = {("k_batch_mf", 256): (285714730, 106163232, 3782323547)}
 
 
 def _sha256(names):

@@ -836,8 +836,8 @@ __global__ __launch_bounds__(256) void k_transpose(const T* __restrict__ src, T*
 // longest segment for c (0: the pass does not apply).  FP32: c TS <= 6 and at
 // least 8 taps, i.e. c <= 0.75; beyond that a kernel is a few cells wide and
 // the direct passes take it.
-// (FP64: at most 32 taps, which spill 6 registers in blocks of 512 threads and 40 to 90
-// in those of 1024)
+// FP64: at most 32 taps, which take all 256 registers of a thread in blocks of 512 and
+// spill 12 to 88 in those of 1024.
 template <typename T> static int line_ts(double c) {
   const double top = sizeof(T) == 4 ? 6.0 : 63.0;
   for (int ts = sizeof(T) == 4 ? 64 : 32; ts >= (sizeof(T) == 4 ? 8 : 16); ts /= 2)
